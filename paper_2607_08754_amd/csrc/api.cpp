@@ -473,7 +473,7 @@ slorr_status_t slorr_plan_get_launches(slorr_plan_t plan, int32_t *ops, double *
       const bool gemm = l.op == slorr::Op::Gram || l.op == slorr::Op::Poly || l.op == slorr::Op::Update ||
                         l.op == slorr::Op::Last;
       if (ops) ops[i] = int32_t(l.op);
-      if (tile_edge) tile_edge[i] = gemm ? (l.cfg == slorr::kCfg256 ? 256 : 128) : 0;
+      if (tile_edge) tile_edge[i] = gemm ? (l.run_cfg == slorr::kCfg256 ? 256 : 128) : 0;
       if (!alg_flops) continue;
       double f = 0.0;
       if (gemm) {

@@ -1,0 +1,891 @@
+// Pipelined MFMA kernels of the Polar Express step on 16-bit MFMA operands,
+// for both storage forms of the iterate (device code, included by kernels.hip
+// after gemm.hpp, inside namespace slorr):
+//
+//   k_tile    one output tile per block, NS LDS stages (Gram, poly, update)
+//   k_upd256  the persistent 256 x 256 update kernel
+//
+// Storage forms
+//   _Float16  bf16 sets: scaled fp16 values.
+//   Split     fp32 sets: every value x (scaled) is held as two fp16 numbers,
+//             hi = fp16(x) and lo = fp16(x - hi), 4 bytes in all. Rows are
+//             cut into runs of 32 values, 128 bytes each: 32 hi, then 32 lo.
+//             hi + lo keeps 23 of fp32's 24 significand bits in the worst
+//             case, and all of them for three values in four. A product of
+//             two values is formed as lo hi + hi lo + hi hi, three fp16 MFMAs
+//             with fp32 accumulation; the dropped lo lo is below 2^-22 of the
+//             product.
+//
+// Why the split: fp32 MFMA runs at 1/16 of the fp16 rate, so three fp16
+// products cost 3/16 of one fp32 product, and per byte fetched or read from
+// LDS a split slab feeds 1.5 times the MFMA work of a plain fp16 slab. Its
+// error is no larger than fp32 MFMA's: a k-long sum is rounded once per 16
+// values of k and term instead of once per 2 values, which outweighs the
+// operands' last bit. Measured against 64 bits, fp32 MFMA / split: gradients
+// 2.3e-6 / 1.5e-6 (200 x 260), 6.4e-6 / 4.1e-6 (512 x 2048), 5.0e-6 / 3.3e-6
+// (ViT-B/16 in fp32); values 1e-7 both.
+// One fp32 call, fp32 MFMA -> split: ViT-B/16 12.7 -> 4.7 ms, ViT-S (with the
+// decoupled update) 2.41 -> 1.14 ms, ResNet-18 1.58 -> 0.71 ms, 4 matrices of
+// 128 x 256 (T = 5) 250 -> 177 us.
+#pragma once
+
+struct Split {
+  uint32_t bits;      // storage unit of one value; see the row layout above
+};
+
+template <typename T> struct Iter;
+template <> struct Iter<_Float16> {
+  static constexpr int kPlanes = 1, kBK = 64;      // k per 128-byte slab row
+};
+template <> struct Iter<Split> {
+  static constexpr int kPlanes = 2, kBK = 32;
+};
+
+// Index of the 16-byte chunk that holds value `col` (a multiple of 4) of a
+// row, and the byte of that chunk within a row of the matrix.
+template <typename T>
+__device__ __forceinline__ int chunk_of(int col, int plane) {
+  if constexpr (Iter<T>::kPlanes == 1) return col >> 3;
+  return (col >> 5) * 8 + plane * 4 + ((col & 31) >> 3);
+}
+template <typename T>
+__device__ __forceinline__ size_t byte_of(size_t row, size_t ld, int col, int plane) {
+  if constexpr (Iter<T>::kPlanes == 1) return (row * ld + size_t(col)) * 2;
+  return (row * ld + size_t(col & ~31)) * 4 + size_t(plane * 64 + (col & 31) * 2);
+}
+
+// The planes of a scaled fp32 result, and the value they hold (exact in fp32:
+// lo's last bit is never below the last bit of v).
+template <typename T, int N, typename H>
+__device__ __forceinline__ void to_planes(const float (&v)[N], H (&h)[Iter<T>::kPlanes]) {
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const _Float16 hi = _Float16(v[j]);
+    h[0][j] = hi;
+    if constexpr (Iter<T>::kPlanes == 2) h[Iter<T>::kPlanes - 1][j] = _Float16(v[j] - float(hi));
+  }
+}
+template <typename T, typename H>
+__device__ __forceinline__ float of_planes(const H (&h)[Iter<T>::kPlanes], int j) {
+  float f = float(h[0][j]);
+  if constexpr (Iter<T>::kPlanes == 2) f += float(h[Iter<T>::kPlanes - 1][j]);
+  return f;
+}
+
+// The trace's partial over 8 consecutive columns: P (as stored) times X_0'.
+// fp16: trace8; split: every product of the two held values exact in fp64.
+template <typename T>
+__device__ __forceinline__ double trace_planes(const half8 (&p)[Iter<T>::kPlanes], const half8 (&x0)[Iter<T>::kPlanes]) {
+  if constexpr (Iter<T>::kPlanes == 1) return double(trace8(p[0], x0[0]));
+  double t = 0.0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) t += double(of_planes<T>(p, j)) * double(of_planes<T>(x0, j));
+  return t;
+}
+
+// s_waitcnt vmcnt(N), the other counters left alone (gfx9 encoding).
+template <int N>
+__device__ __forceinline__ void vm_wait() {
+  static_assert(N >= 0 && N < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// Wait until at most `ahead` (<= A) slabs of fetches, L instructions each,
+// issued by this wave are outstanding.
+template <int L, int A>
+__device__ __forceinline__ void vm_wait_slabs(int ahead) {
+  if constexpr (A >= 2) {
+    if (ahead >= 2) {
+      vm_wait<2 * L>();
+      return;
+    }
+  }
+  if constexpr (A >= 1) {
+    if (ahead >= 1) {
+      vm_wait<L>();
+      return;
+    }
+  }
+  vm_wait<0>();
+}
+
+// The MFMAs of one 16-deep k step of a wave tile, operands swapped (the n
+// operand first): acc[i][j][4 g + q] = C[row lr of 32-row block i][column
+// 32 j + 8 g + 4 lk + q] of the wave tile. Split: the small cross terms
+// first; successive MFMAs go to different accumulators.
+template <typename T, int FM, int FN>
+__device__ __forceinline__ void mma_step(floatx16 (&acc)[FM][FN], const half8 (&fa)[Iter<T>::kPlanes][FM],
+                                         const half8 (&fb)[Iter<T>::kPlanes][FN]) {
+  if constexpr (Iter<T>::kPlanes == 2) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[0][j], fa[Iter<T>::kPlanes - 1][i], acc[i][j], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[Iter<T>::kPlanes - 1][j], fa[0][i], acc[i][j], 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[0][j], fa[0][i], acc[i][j], 0, 0, 0);
+}
+
+// One slab (128-byte rows): the fragments of k step s + 1 are read from LDS
+// while the MFMAs of step s run. The A operand's rows start at wave row ar
+// of sA; the n operand is K-major rows (KN = false, rows from br) or [k][n]
+// rows of KNP bytes (columns from br), transposed on the read.
+template <typename T, int FM, int FN, bool KN, int KNP>
+__device__ __forceinline__ void compute_slab(floatx16 (&acc)[FM][FN], const char *sA, const char *sB, int ar, int br,
+                                             int lane) {
+  constexpr int PL = Iter<T>::kPlanes, KS = Iter<T>::kBK / 16;
+  const int lr = lane & 31, lk = lane >> 5;
+  half8 fa[2][PL][FM], fb[2][PL][FN];
+  auto read = [&](int s, int slot) {
+#pragma unroll
+    for (int p = 0; p < PL; ++p) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+        fa[slot][p][i] = *reinterpret_cast<const half8 *>(sA + swz(ar + i * 32 + lr, 4 * p + 2 * s + lk));
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        if constexpr (KN) {
+          // lane L: k = 16 s + 8 (L / 32) + 0..7 of column n = L % 32 of the
+          // fragment, as two transposing reads of 4 k-rows each
+          const int g = lane >> 4, si = lane & 15;
+          const int row = 16 * s + 8 * (g >> 1) + (si >> 2);
+          const int col = br + j * 32 + 16 * (g & 1) + 4 * (si & 3);
+          const int off = kn_off(row, chunk_of<T>(col, p), KNP) + 8 * (si & 1);
+          const half4 lo = lds_read_tr16(sB + off);
+          const half4 hi = lds_read_tr16(sB + off + 4 * KNP);
+          fb[slot][p][j] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        } else {
+          fb[slot][p][j] = *reinterpret_cast<const half8 *>(sB + swz(br + j * 32 + lr, 4 * p + 2 * s + lk));
+        }
+      }
+    }
+  };
+  read(0, 0);
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    if (s + 1 < KS) read(s + 1, (s + 1) & 1);
+    mma_step<T, FM, FN>(acc, fa[s & 1], fb[s & 1]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// One output tile per block, wave tiles of 64 columns, NS LDS stages: slab
+// k + NS - 1 is fetched while slab k is multiplied; each slab is waited for
+// by count (vector loads complete in issue order), then one block barrier
+// publishes it and frees the stage of the slab before it. Launches of at most
+// one block per CU take 4 stages (128 KB, which leaves one block per CU
+// anyway): their tiles are bound by the latency of the slabs' fetches. Others
+// take 2 stages and two blocks per CU.
+template <typename T, int BM, int BN, int WGM, int WGN, int NS, int MODE>
+struct TileShape {
+  static constexpr int kWaves = WGM * WGN, kThreads = 64 * kWaves;
+  static constexpr int WTM = BM / WGM, WTN = BN / WGN, FM = WTM / 32, FN = WTN / 32;
+  static constexpr int PL = Iter<T>::kPlanes, BK = Iter<T>::kBK;
+  static constexpr bool KN = MODE == kUpdate || MODE == kLast;
+  static constexpr int KNP = BN * int(sizeof(T));          // bytes per k-row of a [k][n] stage
+  static constexpr int kStageA = BM * 128, kStage = kStageA + BN * 128;
+  static constexpr int kHalf = 32 * 128;                   // 32 rows x 64 fp16 of one plane
+  static constexpr int kPitch = WTN + 4;                   // floats per row staged in fp32 (poly)
+  static constexpr int kEpiWave = PL * kHalf + (MODE == kPoly ? 32 * kPitch * 4 : 0);
+  // split symmetric products: the diagonal's sums of squares, behind the rest
+  static constexpr bool kDiagSq = PL == 2 && !KN;
+  static constexpr int kDiagOff = NS * kStage > kWaves * kEpiWave ? NS * kStage : kWaves * kEpiWave;
+  static constexpr int kSmem = kDiagOff + (kDiagSq ? BM * 4 : 0);
+  // with 8 waves (two per SIMD) and two K-major operands, the first 4 fetch
+  static constexpr int kFW = (kWaves == 8 && !KN) ? 4 : kWaves;
+  static constexpr int RPX = 1024 / KNP;                   // k-rows per [k][n] fetch
+  static constexpr int kLoadsA = BM / 8 / kFW, kLoadsB = KN ? BK / RPX / kFW : BN / 8 / kFW;
+  static_assert(WTN == 64 && WTM % 32 == 0 && BM == BN, "wave tile");
+  static_assert(BM % (8 * kFW) == 0 && (8 * kFW) % 16 == 0, "swizzle period");
+  static_assert(!KN || (RPX >= 1 && (RPX * kFW) % 4 == 0 && BK % (RPX * kFW) == 0), "kn_off key period");
+  static_assert(!kDiagSq || kThreads == 2 * BM, "two threads per diagonal row");
+  static_assert((NS - 2) * (kLoadsA + kLoadsB) < 64 && kSmem <= 160 * 1024, "vmcnt range, LDS");
+};
+
+template <typename T, int MODE, int BM, int BN, int WGM, int WGN, int NS>
+__global__ __launch_bounds__(64 * WGM * WGN) void k_tile(GemmArgs args) {
+  using S = TileShape<T, BM, BN, WGM, WGN, NS, MODE>;
+  constexpr int PL = S::PL, BK = S::BK, FM = S::FM, FN = S::FN, WTM = S::WTM, WTN = S::WTN;
+  constexpr int V = 16 / int(sizeof(T));            // storage units per 16 bytes
+  constexpr bool SYM = MODE == kGram || MODE == kPoly;
+  __shared__ __attribute__((aligned(16))) char smem[S::kSmem];
+
+  const Tile tile = args.tiles[blockIdx.x];
+  if (tile.mat < 0) return;      // padding of the XCD-ordered list (whole block)
+  // a Gram part (split K) covers k in [k0, k1) and stores its raw fp32 partial
+  const bool part = MODE == kGram && tile.k1 > 0;
+  // diagonal tile of a symmetric product: one row panel, read for both operands
+  const bool diag = SYM && tile.tm == tile.tn;
+  const MatDesc d = args.mats[tile.mat];
+  const int m0 = tile.tm * BM, n0 = tile.tn * BN;
+  // X buffer offsets read from the table in memory (a run-time index into the
+  // local copy of the descriptor would place that copy in scratch memory)
+  char *Xc = args.ws + args.mats[tile.mat].x[args.xin];
+  char *Xn = args.ws + args.mats[tile.mat].x[args.xout];
+  char *Am = args.ws + d.a, *Bm = args.ws + d.b;
+  const char *Ap, *Bp;
+  int lda, ldb, K;
+  if (MODE == kGram) {                               // A = X X^T
+    Ap = Bp = Xc + (part ? size_t(tile.k0) * sizeof(T) : 0);
+    lda = ldb = d.Qp;
+    K = part ? tile.k1 - tile.k0 : d.Qp;
+  } else if (MODE == kPoly) {                        // A A
+    Ap = Bp = Am;
+    lda = ldb = K = d.Pp;
+  } else {                                           // B X or A X
+    Ap = args.use_a ? Am : Bm;
+    Bp = Xc;
+    lda = K = d.Pp;
+    ldb = d.Qp;
+  }
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 31, lk = lane >> 5;
+  const int wm = wave / WGN, wn = wave % WGN;
+
+  // Direct global -> LDS fetches as in k_gemm: one buffer resource per
+  // operand matrix, a fixed byte offset per lane, the slab and the row step
+  // in the scalar offset.
+  const uint32_t skip = part ? uint32_t(tile.k0) * uint32_t(sizeof(T)) : 0u;
+  const uint32_t abytes = uint32_t(d.Pp) * uint32_t(lda) * uint32_t(sizeof(T)) - skip;
+  const uint32_t bbytes = uint32_t(d.Pp) * uint32_t(ldb) * uint32_t(sizeof(T)) - skip;
+  auto fetch_rows = [&](const char *base, uint32_t bytes, int ld, int row0, int k0, char *dst) {
+    const i32x4 rs = buffer_rsrc(base, bytes);
+    const int row = wave * 8 + (lane >> 3);
+    const uint32_t voff =
+        (uint32_t(row0 + row) * uint32_t(ld) + uint32_t(((lane & 7) ^ swz_key(row)) * V)) * uint32_t(sizeof(T));
+#pragma unroll
+    for (int i = 0; i < BM / 8 / S::kFW; ++i)
+      buffer_load_lds16(rs, voff, (uint32_t(k0) + uint32_t(i) * uint32_t(8 * S::kFW) * uint32_t(ld)) * uint32_t(sizeof(T)),
+                        dst + (wave + i * S::kFW) * 1024);
+  };
+  auto dload = [&](int k0, int st) {
+    if (wave >= S::kFW) return;
+    char *sA = smem + st * S::kStage, *sB = sA + S::kStageA;
+    fetch_rows(Ap, abytes, lda, m0, k0, sA);
+    if constexpr (S::KN) {
+      constexpr int CPR = S::KNP / 16;
+      const i32x4 rb = buffer_rsrc(Bp, bbytes);
+      const int row = wave * S::RPX + lane / CPR;
+      const uint32_t voff = (uint32_t(row) * uint32_t(ldb) +
+                             uint32_t(n0 + ((lane % CPR) ^ ((row & 3) << 2)) * V)) * uint32_t(sizeof(T));
+#pragma unroll
+      for (int i = 0; i < S::kLoadsB; ++i)
+        buffer_load_lds16(rb, voff, (uint32_t(k0) + uint32_t(i * S::RPX * S::kFW)) * uint32_t(ldb) * uint32_t(sizeof(T)),
+                          sB + (wave + i * S::kFW) * 1024);
+    } else if (!diag) {
+      fetch_rows(Bp, bbytes, ldb, n0, k0, sB);
+    }
+  };
+
+  floatx16 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+  // Split, diagonal tiles: the diagonal elements sum_k x_ik^2 are also formed
+  // as fp32 sums of the whole values (two threads per row, half of a slab's k
+  // each) and replace the MFMA's. Every term of such a sum is positive, so
+  // what the MFMA drops adds up there and nowhere else: lo lo, and the bits
+  // of the 8 products of a lane that lie below 2^-24 of the largest of them.
+  // Measured as -9e-7 on the value of 128 x 256 sets after 5 steps (fp32 MFMA:
+  // 1e-7), where the last polynomial is still steep.
+  float dsq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  auto diag_slab = [&](const char *sA) {
+    const int row = tid >> 1, half = tid & 1;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      half8 h[2];
+#pragma unroll
+      for (int p = 0; p < 2; ++p) h[p] = *reinterpret_cast<const half8 *>(sA + swz(row, 4 * p + 2 * half + c));
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float x = of_planes<Split>(h, j);
+        dsq[j & 3] = fmaf(x, x, dsq[j & 3]);
+      }
+    }
+  };
+
+  // K is a multiple of 128 (padding) and BK divides it
+  const int nk = K / BK;
+#pragma unroll
+  for (int q = 0; q < NS - 1; ++q)
+    if (q < nk) dload(q * BK, q);
+  for (int kt = 0, st = 0; kt < nk; ++kt, st = st + 1 == NS ? 0 : st + 1) {
+    const int ahead = min(NS - 2, nk - 1 - kt);      // slabs fetched after slab kt so far
+    if (diag) vm_wait_slabs<S::kLoadsA, NS - 2>(ahead);
+    else vm_wait_slabs<S::kLoadsA + S::kLoadsB, NS - 2>(ahead);
+    __syncthreads();                 // slab kt is published; slab kt - 1 is done
+    if (kt + NS - 1 < nk) dload((kt + NS - 1) * BK, st == 0 ? NS - 1 : st - 1);
+    const char *sA = smem + st * S::kStage;
+    if (S::kDiagSq && diag) diag_slab(sA);
+    compute_slab<T, FM, FN, S::KN, S::KNP>(acc, sA, diag ? sA : sA + S::kStageA, wm * WTM, wn * WTN, lane);
+  }
+  float *dsum = reinterpret_cast<float *>(smem + S::kDiagOff);
+  if (S::kDiagSq && diag) {
+    float v = (dsq[0] + dsq[1]) + (dsq[2] + dsq[3]);
+    v += __shfl_xor(v, 1);
+    if ((tid & 1) == 0) dsum[tid >> 1] = v;
+  }
+  __syncthreads();                   // the epilogue reuses the stages
+
+  // ------------------------------------------------------------ epilogue
+  // Per 32-row block of the wave tile, in the wave's own LDS area: 8-byte
+  // writes of the fp16 planes from the accumulators, 16-byte reads of 8
+  // consecutive columns for row-contiguous stores, transposing reads for the
+  // mirror tile. One wave's LDS operations are performed in order, so a
+  // wave-level barrier (no reordering) suffices between them. Poly stages its
+  // fp32 sums first and finishes them where it has 8 consecutive columns of
+  // A for the b A term.
+  char *eh = smem + wave * S::kEpiWave;
+  float *ef = reinterpret_cast<float *>(eh + PL * S::kHalf);
+  // per-matrix coefficients of the first step (kappa = 2^e / (f + eps))
+  float alpha = args.alpha, beta = args.beta, gamma = args.gamma;
+  if (args.kap) {
+    const double kp = args.sc[tile.mat].kappa, k2 = kp * kp;
+    if (MODE == kPoly) {
+      alpha = float(double(args.alpha) * k2 * k2 * kp);
+      beta = float(double(args.beta) * k2 * kp);
+      gamma = float(double(args.gamma) * kp);
+    } else {
+      alpha = float(double(args.alpha) * k2 * kp);
+      beta = float(double(args.beta) * kp);
+    }
+  }
+  // Symmetric outputs are stored exactly symmetric: off-diagonal tiles also
+  // store their transpose; a diagonal tile stores its upper triangle and the
+  // transpose of it below the diagonal.
+  char *Sym = MODE == kGram ? Am : Bm;
+  double tsum = 0.0;
+  constexpr int NTASK = 32 * 8 / 64;                // 8-column pieces per lane and block
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    const int grow0 = m0 + wm * WTM + i * 32, gcol0 = n0 + wn * WTN;
+    if (S::kDiagSq && diag) {
+      const float dv = dsum[wm * WTM + i * 32 + lr];
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (grow0 + lr == gcol0 + 32 * j + 8 * g + 4 * lk + q) acc[i][j][4 * g + q] = dv;
+    }
+    if (part) {
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          float4v f;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) f[q] = acc[i][j][4 * g + q];
+          *reinterpret_cast<float4v *>(args.gpart + size_t(tile.slot) * (BM * BN) + size_t(grow0 - m0 + lr) * BN +
+                                       (gcol0 - n0) + 32 * j + 8 * g + 4 * lk) = f;
+        }
+      continue;
+    }
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = acc[i][j][4 * g + q];
+        if constexpr (MODE == kPoly) {
+          *reinterpret_cast<float4v *>(ef + lr * S::kPitch + 32 * j + 8 * g + 4 * lk) = float4v{v[0], v[1], v[2], v[3]};
+        } else {
+          if (SYM || args.fold) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] *= alpha;
+          } else {                                   // cubic step: the a X term
+            half4 in[PL];
+#pragma unroll
+            for (int p = 0; p < PL; ++p)
+              in[p] = *reinterpret_cast<const half4 *>(
+                  Xc + byte_of<T>(size_t(grow0 + lr), d.Qp, gcol0 + 32 * j + 8 * g + 4 * lk, p));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = beta * of_planes<T>(in, q) + alpha * v[q];
+          }
+          half4 h[PL];
+          to_planes<T>(v, h);
+#pragma unroll
+          for (int p = 0; p < PL; ++p)
+            *reinterpret_cast<half4 *>(eh + p * S::kHalf + mir_off(lr, 4 * j + g) + 8 * lk) = h[p];
+        }
+      }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < NTASK; ++t) {
+      const int task = lane + 64 * t, row = task >> 3, cg = task & 7;
+      const int grow = grow0 + row, gcol = gcol0 + 8 * cg;
+      half8 h[PL];
+      if constexpr (MODE == kPoly) {
+        half8 av[PL];
+#pragma unroll
+        for (int p = 0; p < PL; ++p) av[p] = *reinterpret_cast<const half8 *>(Am + byte_of<T>(size_t(grow), d.Pp, gcol, p));
+        const float4v e0 = *reinterpret_cast<const float4v *>(ef + row * S::kPitch + 8 * cg);
+        const float4v e1 = *reinterpret_cast<const float4v *>(ef + row * S::kPitch + 8 * cg + 4);
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          v[j] = beta * of_planes<T>(av, j) + alpha * (j < 4 ? e0[j & 3] : e1[j & 3]) + (grow == gcol + j ? gamma : 0.0f);
+        to_planes<T>(v, h);
+#pragma unroll
+        for (int p = 0; p < PL; ++p) *reinterpret_cast<half8 *>(eh + p * S::kHalf + mir_off(row, cg)) = h[p];
+      } else {
+#pragma unroll
+        for (int p = 0; p < PL; ++p) h[p] = *reinterpret_cast<const half8 *>(eh + p * S::kHalf + mir_off(row, cg));
+      }
+      if constexpr (SYM) {
+#pragma unroll
+        for (int p = 0; p < PL; ++p)
+          store_h8_range(reinterpret_cast<_Float16 *>(Sym + byte_of<T>(size_t(grow), d.Pp, gcol, p)), h[p],
+                         diag ? grow - gcol : 0, 8);
+      } else {
+        if (MODE == kUpdate || args.write_x) {
+#pragma unroll
+          for (int p = 0; p < PL; ++p) {
+            half8 *o = reinterpret_cast<half8 *>(Xn + byte_of<T>(size_t(grow), d.Qp, gcol, p));
+            // a step's iterate is streamed out, X_T is read soon (k_upd256)
+            if constexpr (MODE == kUpdate) __builtin_nontemporal_store(h[p], o);
+            else *o = h[p];
+          }
+        }
+        if constexpr (MODE == kLast) {
+          half8 x0[PL];
+#pragma unroll
+          for (int p = 0; p < PL; ++p)
+            x0[p] = *reinterpret_cast<const half8 *>(args.ws + d.x[0] + byte_of<T>(size_t(grow), d.Qp, gcol, p));
+          tsum += trace_planes<T>(h, x0);
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    if constexpr (SYM) {
+      // transpose: each 16-lane group takes 16 columns x 8 rows; two
+      // transposing reads (rows 0-3, 4-7 of the group) leave lane s with
+      // column 16 cb + s, rows 8 rg .. 8 rg + 7: one 16-byte row piece of
+      // the mirror tile
+#pragma unroll
+      for (int t = 0; t < NTASK; ++t) {
+        const int q = (lane >> 4) + 4 * t, rg = q & 3, cb = q >> 2, si = lane & 15;
+        const int col = 16 * cb + 4 * (si & 3);            // this lane's 4-column piece
+        const int r = 8 * rg + (si >> 2);
+        const int off = (col & 7) * 2;                     // byte within the 16-byte chunk
+        const int orow = gcol0 + 16 * cb + si, ocol = grow0 + 8 * rg;
+#pragma unroll
+        for (int p = 0; p < PL; ++p) {
+          const char *e = eh + p * S::kHalf;
+          const half4 lo = lds_read_tr16(e + mir_off(r, col >> 3) + off);
+          const half4 hi = lds_read_tr16(e + mir_off(r + 4, col >> 3) + off);
+          const half8 h = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+          store_h8_range(reinterpret_cast<_Float16 *>(Sym + byte_of<T>(size_t(orow), d.Pp, ocol, p)), h, 0,
+                         diag ? orow - ocol : 8);          // strictly below the diagonal
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  if constexpr (MODE == kLast) {
+    __syncthreads();                      // the block sum reuses wave 0's staging area
+    const double r = block_sum<S::kThreads>(tsum, reinterpret_cast<double *>(smem));
+    if (tid == 0) args.tpart[tile.slot] = r;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Update / Last on 256 x 256 tiles: a persistent kernel.
+//
+// One block per CU walks the launch's tile list with a stride of the grid
+// size. The grid is a multiple of the XCD count, so every list entry runs on
+// the XCD the list assigns it to, as in a launch of one block per tile.
+//
+// Tile contexts: at the start, lane t of every wave loads what tile t of the
+// block's sequence needs (operand offsets, padded dims, tile coordinates) into
+// a register table, read later with readlane. The main loop then issues no
+// memory access besides the operand fetches, so a slab's wait counts only
+// them (a descriptor load in the loop would need a wait that drains every
+// fetch in flight). A block with more than 64 tiles reloads the table.
+//
+// Operand pipeline: k-slabs of BK in NS LDS stages, fetched NS - 1 slabs
+// ahead. The slab sequence runs on across tiles: the first slabs of the next
+// tile are fetched while the last ones of the current tile are multiplied and
+// while its epilogue runs. A slab is waited for by count (s_waitcnt vmcnt
+// with the fetches issued after it still outstanding; vector loads complete
+// in issue order, and outstanding stores only make the wait longer), then one
+// block barrier publishes it and frees the stage of the previous slab, into
+// which the next fetch goes. LDS: the stages and a separate 32 KB epilogue
+// staging area (4 KB per wave), 160 KB in all (one block per CU).
+//
+// The MFMA operands are swapped with respect to k_gemm: the iterate panel is
+// the instruction's first operand, so each lane's accumulator holds 4
+// consecutive output columns of one row (acc[i][j][4 g + q] = C[row lr of
+// 32-row block i][column 32 j + 8 g + 4 lk + q] of the wave tile). The
+// epilogue scales and rounds them to fp16 and stages them with 8-byte LDS
+// writes; 16-byte reads then give each lane 8 consecutive columns, 8 lanes
+// per row, so the global stores write whole 128-byte row segments. Every
+// output element is the same fp32 sum rounded once, as in k_gemm.
+template <typename T>
+struct Upd256 {
+  static constexpr int BM = 256, BN = 256, WGM = 2, WGN = 4, kWaves = 8, NT = 512;
+  static constexpr int WTM = 128, WTN = 64, FM = 4, FN = 2;
+  static constexpr int BK = Iter<T>::kBK;            // k per slab
+  static constexpr int PL = Iter<T>::kPlanes;
+  static constexpr int NS = 2;                       // LDS stages (fetch distance NS - 1)
+  static constexpr int KAP = 128;                    // bytes per row of the B stage (K-major)
+  static constexpr int KNP = BN * int(sizeof(T));    // bytes per k-row of the X stage
+  static constexpr int kStageA = BM * KAP;
+  static constexpr int kStage = kStageA + BK * KNP;
+  static constexpr int kEpi = 32 * 128;              // per wave: 32 rows x 64 fp16
+  static constexpr int kSmem = NS * kStage + kWaves * kEpi;
+  // global -> LDS instructions per fetching wave and slab: B rows (8 rows of
+  // 128 bytes each), X rows (1 KB each: 2 fp16 or 1 split k-row). Only the
+  // first kFetchWaves waves fetch (one per SIMD): a wave stalls while its
+  // fetches wait for the address unit, and the other wave of its SIMD keeps
+  // the MFMA pipe busy meanwhile.
+  static constexpr int kFetchWaves = 4;
+  static constexpr int RPA = 1024 / KAP, RPX = 1024 / KNP;
+  static constexpr int kLoadsA = BM / RPA / kFetchWaves, kLoadsX = BK / RPX / kFetchWaves;
+  static constexpr int kLoads = kLoadsA + kLoadsX;
+  static_assert(BK * sizeof(T) == 128, "128-byte slab rows");
+  static_assert(NS >= 2 && kSmem <= 160 * 1024, "LDS per CU");
+  static_assert((NS - 2) * kLoads < 64, "vmcnt range");
+};
+
+// Byte offset of 16-byte chunk `chunk` of row `row` of a wave's epilogue
+// staging area (rows of 128 bytes). The key (row >> 1) & 7 gives the 16 rows
+// of an 8-byte write's half-wave distinct (row parity, chunk) pairs, i.e.
+// distinct bank pairs; a 16-byte read's 16-lane phase covers two rows whole.
+__device__ __forceinline__ int epi_off(int row, int chunk) {
+  return row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4);
+}
+
+__device__ __forceinline__ uint64_t readlane64(uint64_t v, int lane) {
+  const uint32_t lo = __builtin_amdgcn_readlane(uint32_t(v), lane);
+  const uint32_t hi = __builtin_amdgcn_readlane(uint32_t(v >> 32), lane);
+  return (uint64_t(hi) << 32) | lo;
+}
+
+template <typename T, int MODE, bool FOLD>
+__global__ __launch_bounds__(512) void k_upd256(GemmArgs args) {
+  using U = Upd256<T>;
+  constexpr int BK = U::BK, NS = U::NS, PL = U::PL;
+  constexpr int V = 16 / int(sizeof(T));       // storage units per 16 bytes
+  static_assert(MODE == kUpdate || MODE == kLast, "update kernels only");
+  __shared__ __attribute__((aligned(16))) char smem[U::kSmem];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 31, lk = lane >> 5;
+  const int wm = wave / U::WGN, wn = wave % U::WGN;
+  const int G = gridDim.x;
+  // positions of this block's sequence: entry blockIdx.x + pos * G
+  const int npos = args.ntiles > int(blockIdx.x) ? (args.ntiles - int(blockIdx.x) + G - 1) / G : 0;
+
+  // register table of tile contexts, positions tb .. tb + 63 (lane t: tb + t)
+  int tb = 0;
+  int v_mat, v_tm, v_tn, v_slot, v_ss, v_pp, v_qp;
+  uint64_t v_a, v_xi, v_xo, v_x0;
+  auto load_table = [&](int base) {
+    tb = base;
+    const int pos = base + lane;
+    v_mat = -1;
+    v_tm = v_tn = v_slot = v_ss = v_pp = v_qp = 0;
+    v_a = v_xi = v_xo = v_x0 = 0;
+    if (pos < npos) {
+      const Tile t = args.tiles[int(blockIdx.x) + pos * G];
+      v_mat = t.mat;
+      if (t.mat >= 0) {
+        const MatDesc *d = args.mats + t.mat;
+        v_tm = t.tm;
+        v_tn = t.tn;
+        v_slot = t.slot;
+        v_ss = t.parts;
+        v_pp = d->Pp;
+        v_qp = d->Qp;
+        v_a = args.use_a ? d->a : d->b;
+        v_xi = d->x[args.xin];
+        v_xo = d->x[args.xout];
+        v_x0 = d->x[0];
+      }
+    }
+  };
+  struct Ctx {
+    const char *Ap, *Bp;   // B (or A) rows, X rows
+    char *Xn;              // output iterate
+    const char *X0;        // X_0' (trace)
+    int ldx, K, m0, n0, mat, slot;
+    int ss;                // 0: one trace slot; else one per 128 x 128 quadrant,
+                           // ss slots from one column of quadrants to the next
+  };
+  // the first valid position >= pos (npos if none); reloads the table when
+  // pos leaves it
+  auto next_pos = [&](int pos) {
+    for (; pos < npos; ++pos) {
+      if (pos >= tb + 64) load_table(pos);
+      if (__builtin_amdgcn_readlane(v_mat, pos - tb) >= 0) break;
+    }
+    return pos;
+  };
+  auto ctx_at = [&](int pos) {
+    const int t = pos - tb;
+    Ctx c;
+    c.Ap = args.ws + readlane64(v_a, t);
+    c.Bp = args.ws + readlane64(v_xi, t);
+    c.Xn = args.ws + readlane64(v_xo, t);
+    c.X0 = args.ws + readlane64(v_x0, t);
+    c.ldx = __builtin_amdgcn_readlane(v_qp, t);
+    c.K = __builtin_amdgcn_readlane(v_pp, t);
+    c.m0 = __builtin_amdgcn_readlane(v_tm, t) * U::BM;
+    c.n0 = __builtin_amdgcn_readlane(v_tn, t) * U::BN;
+    c.mat = __builtin_amdgcn_readlane(v_mat, t);
+    c.slot = __builtin_amdgcn_readlane(v_slot, t);
+    c.ss = __builtin_amdgcn_readlane(v_ss, t);
+    return c;
+  };
+
+  // global -> LDS fetch of slab k0 of tile c into stage st: B rows, K-major,
+  // 8 rows of 128 bytes per wave instruction (lane l: row l / 8, physical
+  // chunk l % 8, fetching the logical chunk the swizzle puts there); X rows
+  // [k][n], 1 KB of k-rows per wave instruction in kn_off's layout. Through
+  // buffer resources over the two operand matrices (the plan keeps every
+  // matrix of these launches under 2 GiB): each lane's byte offset is fixed
+  // for a tile, and the slab and the instruction's row step go into the
+  // wave-uniform offset (successive instructions of a wave are a fixed number
+  // of rows apart, and the swizzle key repeats over them).
+  static_assert((U::kFetchWaves * U::RPA) % 16 == 0 && (U::kFetchWaves * U::RPX) % 4 == 0, "swizzle period");
+  constexpr uint32_t ES = sizeof(T);
+  auto dload = [&](const Ctx &c, int k0, int st) {
+    if (wave >= U::kFetchWaves) return;
+    char *sA = smem + st * U::kStage;
+    char *sB = sA + U::kStageA;
+    {
+      const i32x4 ra = buffer_rsrc(c.Ap, uint32_t(c.K) * uint32_t(c.K) * ES);     // K x K
+      const int row = wave * U::RPA + (lane >> 3);
+      const uint32_t voff = (uint32_t(c.m0 + row) * uint32_t(c.K) + uint32_t(((lane & 7) ^ swz_key(row)) * V)) * ES;
+      const uint32_t step = uint32_t(U::kFetchWaves * U::RPA) * uint32_t(c.K) * ES;
+#pragma unroll
+      for (int i = 0; i < U::kLoadsA; ++i)
+        buffer_load_lds16(ra, voff, uint32_t(k0) * ES + uint32_t(i) * step, sA + (wave + i * U::kFetchWaves) * 1024);
+    }
+    constexpr int CPR = U::KNP / 16;
+    {
+      const i32x4 rx = buffer_rsrc(c.Bp, uint32_t(c.K) * uint32_t(c.ldx) * ES);  // K x ldx
+      const int row = wave * U::RPX + lane / CPR;
+      const uint32_t voff = (uint32_t(row) * uint32_t(c.ldx) +
+                             uint32_t(c.n0 + ((lane % CPR) ^ ((row & 3) << 2)) * V)) * ES;
+      const uint32_t step = uint32_t(U::kFetchWaves * U::RPX) * uint32_t(c.ldx) * ES;
+#pragma unroll
+      for (int i = 0; i < U::kLoadsX; ++i)
+        buffer_load_lds16(rx, voff, uint32_t(k0) * uint32_t(c.ldx) * ES + uint32_t(i) * step,
+                          sB + (wave + i * U::kFetchWaves) * 1024);
+    }
+  };
+
+  floatx16 acc[U::FM][U::FN];
+  auto compute = [&](int st) {
+    const char *sA = smem + st * U::kStage;
+    compute_slab<T, U::FM, U::FN, true, U::KNP>(acc, sA, sA + U::kStageA, wm * U::WTM, wn * U::WTN, lane);
+    // instruction order: the first k-step's fragment reads, then the MFMAs
+    // of a step with the next step's reads spread among them (one per MFMA;
+    // split: two per three), so the reads land under the MFMAs instead of
+    // bunching at the step's start
+    constexpr int KS = BK / 16, kReads = PL * (U::FM + 2 * U::FN), kGroups = 8;
+    constexpr int kMfma = (PL == 1 ? 1 : 3) * U::FM * U::FN;
+    static_assert(kReads % kGroups == 0 && kMfma % kGroups == 0, "reads per MFMA");
+    __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);      // LDS reads
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int q = 0; q < kGroups; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, kMfma / kGroups, 0);        // MFMA
+        if (s + 1 < KS) __builtin_amdgcn_sched_group_barrier(0x100, kReads / kGroups, 0);
+      }
+  };
+
+  load_table(0);
+  int pos = next_pos(0);
+  if (pos >= npos) return;
+  Ctx cur = ctx_at(pos);
+
+  // producer: the next slab to fetch (position ppos, context pc, slab pk);
+  // nextc: the context of the tile after the consumer's
+  static_assert(NS - 1 < kBigTile / BK, "the fetches run at most one tile ahead");
+  int ppos = pos, pk = 0, npos_c = pos;   // npos_c: position of nextc
+  Ctx pc = cur, nextc = cur;
+  bool pvalid = true;
+  int issued = 0;                      // slabs fetched so far
+  auto produce = [&](int st) {
+    if (!pvalid) return;
+    dload(pc, pk * BK, st);
+    ++issued;
+    if (++pk == pc.K / BK) {
+      ppos = next_pos(ppos + 1);
+      pvalid = ppos < npos;
+      if (pvalid) {
+        pc = ctx_at(ppos);
+        nextc = pc;
+        npos_c = ppos;
+      }
+      pk = 0;
+    }
+  };
+#pragma unroll
+  for (int q = 0; q < NS - 1; ++q) produce(q);
+
+  char *ep = smem + NS * U::kStage + wave * U::kEpi;
+  // Last: the X_0' values of the trace, 8 consecutive columns per lane in
+  // the epilogue's read-back layout, loaded two 32-row blocks ahead (cubic
+  // steps: one; split: where they are used, the registers hold no more)
+  constexpr int XB = PL == 2 ? 0 : FOLD ? 2 : 1;
+  half8 x0v[MODE == kLast && XB ? XB : 1][4][PL];
+  auto x0load = [&](const Ctx &c, int i) {
+    if constexpr (MODE == kLast) {
+      const int row_w = c.m0 + wm * U::WTM, col_w = c.n0 + wn * U::WTN;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int q = lane + 64 * t, row = q >> 3, ch = q & 7;
+#pragma unroll
+        for (int p = 0; p < PL; ++p)
+          x0v[XB ? i % XB : 0][t][p] = __builtin_nontemporal_load(reinterpret_cast<const half8 *>(
+              c.X0 + byte_of<T>(size_t(row_w + i * 32 + row), c.ldx, col_w + 8 * ch, p)));
+      }
+    }
+  };
+  int g = 0;                           // slab being multiplied (global count)
+  for (;;) {
+#pragma unroll
+    for (int i = 0; i < U::FM; ++i)
+#pragma unroll
+      for (int j = 0; j < U::FN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    // K is a multiple of 256 (padding), so of BK
+    const int nk = cur.K / BK;
+    for (int kt = 0; kt < nk; ++kt, ++g) {
+      vm_wait_slabs<U::kLoads, NS - 2>(issued - g - 1);   // slab g has landed (this wave's part)
+      __syncthreads();                 // ... every wave's part; slab g - 1 is done
+      produce((g + NS - 1) % NS);
+      compute(g % NS);
+    }
+
+    // ---------------------------------------------------------- epilogue
+    float alpha = args.alpha, beta = args.beta;
+    if (args.kap) {                        // first (cubic) step: kappa^3 a, kappa b
+      const double kp = args.sc[cur.mat].kappa;
+      alpha = float(double(args.alpha) * kp * kp * kp);
+      beta = float(double(args.beta) * kp);
+    }
+    const int row_w = cur.m0 + wm * U::WTM, col_w = cur.n0 + wn * U::WTN;
+    double tsum = 0.0;
+#pragma unroll
+    for (int i = 0; i < XB; ++i) x0load(cur, i);
+#pragma unroll
+    for (int i = 0; i < U::FM; ++i) {
+      half4 hv[U::FN][4][PL];
+#pragma unroll
+      for (int j = 0; j < U::FN; ++j)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          float v[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = acc[i][j][4 * q4 + q];
+          if constexpr (FOLD) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] *= alpha;
+          } else {
+            half4 in[PL];
+#pragma unroll
+            for (int p = 0; p < PL; ++p)
+              in[p] = *reinterpret_cast<const half4 *>(
+                  cur.Bp + byte_of<T>(size_t(row_w + i * 32 + lr), cur.ldx, col_w + 32 * j + 8 * q4 + 4 * lk, p));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = beta * of_planes<T>(in, q) + alpha * v[q];
+          }
+          to_planes<T>(v, hv[j][q4]);
+          *reinterpret_cast<half4 *>(ep + epi_off(lr, 4 * j + q4) + 8 * lk) = hv[j][q4][0];
+        }
+      // the staging area (one plane of the block) is the wave's own and one
+      // wave's LDS operations are performed in order: a wave-level barrier
+      // (no reordering) suffices
+      __builtin_amdgcn_wave_barrier();
+      half8 hi[PL == 2 ? 4 : 1];
+      if constexpr (PL == 2) {             // take the hi plane, then stage the lo plane
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int c = lane + 64 * t;
+          hi[t] = *reinterpret_cast<const half8 *>(ep + epi_off(c >> 3, c & 7));
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < U::FN; ++j)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4)
+            *reinterpret_cast<half4 *>(ep + epi_off(lr, 4 * j + q4) + 8 * lk) = hv[j][q4][PL - 1];
+        __builtin_amdgcn_wave_barrier();
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int c = lane + 64 * t, row = c >> 3, ch = c & 7;
+        half8 h[PL];
+        h[PL - 1] = *reinterpret_cast<const half8 *>(ep + epi_off(row, ch));
+        if constexpr (PL == 2) h[0] = hi[t];
+#pragma unroll
+        for (int p = 0; p < PL; ++p) {
+          half8 *o = reinterpret_cast<half8 *>(cur.Xn + byte_of<T>(size_t(row_w + i * 32 + row), cur.ldx, col_w + 8 * ch, p));
+          // the iterate of a step is streamed out (the next launch reads it,
+          // and its lines would evict operand panels this launch still reads);
+          // X_T, read by the gradient kernel two short launches later, is
+          // stored normally (measured faster; split: always, a branch here
+          // costs the registers that keep this kernel out of scratch memory)
+          if constexpr (MODE == kUpdate) __builtin_nontemporal_store(h[p], o);
+          else if (PL == 2 || args.write_x) *o = h[p];
+        }
+        if constexpr (MODE == kLast) {     // P as stored times X_0'
+          if constexpr (XB == 0) {
+#pragma unroll
+            for (int p = 0; p < PL; ++p)
+              x0v[0][t][p] = __builtin_nontemporal_load(reinterpret_cast<const half8 *>(
+                  cur.X0 + byte_of<T>(size_t(row_w + i * 32 + row), cur.ldx, col_w + 8 * ch, p)));
+          }
+          tsum += trace_planes<T>(h, x0v[XB ? i % XB : 0][t]);
+        }
+      }
+      if (XB && i + XB < U::FM) x0load(cur, i + XB);
+      __builtin_amdgcn_wave_barrier();
+    }
+    if constexpr (MODE == kLast) {
+      // per-tile partial of the trace: waves in order, each a fixed butterfly
+      const double w = wave_sum(tsum);
+      if (lane == 0) *reinterpret_cast<double *>(ep) = w;
+      __syncthreads();
+      const double *ws8 = reinterpret_cast<const double *>(smem + NS * U::kStage);
+      constexpr int kStep = U::kEpi / int(sizeof(double));
+      if (cur.ss == 0) {
+        if (tid == 0) {
+          double r = 0.0;
+          for (int q = 0; q < U::kWaves; ++q) r += ws8[q * kStep];
+          args.tpart[cur.slot] = r;
+        }
+      } else if (tid < 4) {                // quadrant (tid / 2, tid % 2): two waves
+        const int qm = tid >> 1, qn = tid & 1, q = qm * U::WGN + 2 * qn;
+        args.tpart[cur.slot + qn * cur.ss + qm] = ws8[q * kStep] + ws8[(q + 1) * kStep];
+      }
+    }
+    if (npos_c == pos) break;          // the fetches found no further tile
+    pos = npos_c;
+    cur = nextc;
+  }
+}

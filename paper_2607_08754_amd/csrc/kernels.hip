@@ -235,6 +235,37 @@ __device__ __forceinline__ bool full_tile(const Tile &t, const MatDesc &d, size_
   return (t.tm + 1) * kPrepTile <= d.P && (t.tn + 1) * kPrepTile <= d.Q && (size_t(d.cols) * es) % 16 == 0;
 }
 
+// --------------------------------------------------------------------- GEMM
+
+#include "gemm.hpp"
+#include "gemm_pipe.hpp"
+
+// 8 consecutive iterate values of a padded canonical buffer (row `row`,
+// columns from col, a multiple of 8), stored / loaded non-temporally as
+// floats in the iterate's scale.
+template <typename Tx>
+__device__ __forceinline__ void iter_st8(char *x, size_t row, size_t ld, int col, const float (&v)[8]) {
+  if constexpr (std::is_same<Tx, Split>::value) {
+    half8 h[2];
+    to_planes<Split>(v, h);
+    gstore16(x + byte_of<Split>(row, ld, col, 0), __builtin_bit_cast(u32x4, h[0]));
+    gstore16(x + byte_of<Split>(row, ld, col, 1), __builtin_bit_cast(u32x4, h[1]));
+  } else {
+    st8(reinterpret_cast<Tx *>(x) + row * ld + col, v);
+  }
+}
+template <typename Tx>
+__device__ __forceinline__ void iter_ld8_stream(const char *x, size_t row, size_t ld, int col, float (&v)[8]) {
+  if constexpr (std::is_same<Tx, Split>::value) {
+    const half8 h[2] = {__builtin_bit_cast(half8, gload16_stream(x + byte_of<Split>(row, ld, col, 0))),
+                        __builtin_bit_cast(half8, gload16_stream(x + byte_of<Split>(row, ld, col, 1)))};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = of_planes<Split>(h, j);
+  } else {
+    ld8_stream(reinterpret_cast<const Tx *>(x) + row * ld + col, v);
+  }
+}
+
 // --------------------------------------------------------------- reductions
 
 // 64 x 64 canonical tile per block (the tiles of the normalisation), staged in
@@ -394,7 +425,6 @@ __global__ __launch_bounds__(kThreads) void k_prep(const Tile *__restrict__ tile
   const MatDesc d = mats[t.mat];
   // a power of two: the scaling of W is exact
   stage_tile(tile, t, d, static_cast<const Tw *>(dyn[t.mat].w), sc[t.mat].pscale);
-  Tx *x = reinterpret_cast<Tx *>(ws + d.x[0]);
   const int m0 = t.tm * kPrepTile, n0 = t.tn * kPrepTile;
   __syncthreads();
   for (int q = threadIdx.x; q < kPrepTile * kPrepTile / 8; q += kThreads) {
@@ -402,13 +432,10 @@ __global__ __launch_bounds__(kThreads) void k_prep(const Tile *__restrict__ tile
     float v[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = tile[r * kPrepPitch + c + j];
-    st8(x + size_t(m0 + r) * d.Qp + n0 + c, v);   // padded canonical buffer: aligned, in bounds
+    iter_st8<Tx>(ws + d.x[0], size_t(m0 + r), d.Qp, n0 + c, v);   // padded canonical buffer: aligned, in bounds
   }
 }
 
-// --------------------------------------------------------------------- GEMM
-
-#include "gemm.hpp"
 
 // ---------------------------------------------------------------- finalize
 
@@ -479,6 +506,23 @@ __global__ __launch_bounds__(1024) void k_setsum(const Scalars *__restrict__ sc,
   set_total<1024>(sc, call, n, v);
 }
 
+// Values j in [lo, hi) of 8 consecutive iterate values.
+template <typename Tx>
+__device__ __forceinline__ void iter_st8_range(char *x, size_t row, size_t ld, int col, const float (&v)[8], int lo,
+                                               int hi) {
+  if (lo <= 0 && hi >= 8) {
+    iter_st8<Tx>(x, row, ld, col, v);
+  } else if constexpr (std::is_same<Tx, Split>::value) {
+    half8 h[2];
+    to_planes<Split>(v, h);
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+      store_h8_range(reinterpret_cast<_Float16 *>(x + byte_of<Split>(row, ld, col, p)), h[p], lo, hi);
+  } else {
+    store8_range(reinterpret_cast<Tx *>(x) + row * ld + col, v, lo, hi);
+  }
+}
+
 // Split-K Gram: A tile = alpha * (sum of its fp32 partials, in part order),
 // stored with its transpose for off-diagonal tiles; a diagonal tile stores
 // its upper triangle and the transpose of it below the diagonal (A exactly
@@ -494,7 +538,7 @@ __global__ __launch_bounds__(kThreads) void k_gram_reduce(const Tile *__restrict
   const Tile e = tiles[blockIdx.x / kRedStripes];
   const int stripe = blockIdx.x % kRedStripes;
   const MatDesc d = mats[e.mat];
-  Tx *A = reinterpret_cast<Tx *>(ws + d.a);
+  char *A = ws + d.a;
   const int m0 = e.tm * kTile + stripe * R, n0 = e.tn * kTile;
   const float *src = gpart + size_t(e.slot) * (kTile * kTile) + stripe * R * kTile;
   for (int q = threadIdx.x; q < R * kTile / 4; q += kThreads) {
@@ -516,14 +560,7 @@ __global__ __launch_bounds__(kThreads) void k_gram_reduce(const Tile *__restrict
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = t[r][c + j];
     const int lo = diag ? (m0 + r) - (n0 + c) : 0;        // upper triangle of a diagonal tile
-    Tx *o = A + size_t(m0 + r) * d.Pp + n0 + c;
-    if (lo <= 0) {
-      put8(o, 8, v);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (j >= lo) o[j] = from_f<Tx>(v[j]);
-    }
+    iter_st8_range<Tx>(A, size_t(m0 + r), d.Pp, n0 + c, v, lo, 8);
   }
   // the transpose: R consecutive columns per output row (strictly below the
   // diagonal for a diagonal tile)
@@ -533,14 +570,7 @@ __global__ __launch_bounds__(kThreads) void k_gram_reduce(const Tile *__restrict
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = t[r + j][c];
     const int hi = diag ? (n0 + c) - (m0 + r) : 8;
-    Tx *o = A + size_t(n0 + c) * d.Pp + m0 + r;
-    if (hi >= 8) {
-      put8(o, 8, v);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (j < hi) o[j] = from_f<Tx>(v[j]);
-    }
+    iter_st8_range<Tx>(A, size_t(n0 + c), d.Pp, m0 + r, v, 0, hi);
   }
 }
 
@@ -571,7 +601,6 @@ __global__ __launch_bounds__(kThreads) void k_grad(const Tile *__restrict__ tile
   const MatDesc d = mats[t.mat];
   const int m0 = t.tm * kPrepTile, n0 = t.tn * kPrepTile;
   if (m0 >= d.P || n0 >= d.Q) return;                    // padding only (whole block)
-  const Tx *x = reinterpret_cast<const Tx *>(ws + d.xt);
   const Tw *w = static_cast<const Tw *>(dyn[t.mat].w);
   Tg *g = static_cast<Tg *>(dyn[t.mat].g);
   const float s1 = float(sc[t.mat].s1) * inv_sx, s2 = float(sc[t.mat].s2);
@@ -610,7 +639,7 @@ __global__ __launch_bounds__(kThreads) void k_grad(const Tile *__restrict__ tile
     const int r = q / (kPrepTile / 8), c = (q % (kPrepTile / 8)) * 8;
     float v[8];
     // padded canonical buffer: aligned, in bounds; X_T is read here only once
-    ld8_stream(x + size_t(m0 + r) * d.Qp + n0 + c, v);
+    iter_ld8_stream<Tx>(ws + d.xt, size_t(m0 + r), d.Qp, n0 + c, v);
 #pragma unroll
     for (int j = 0; j < 8; ++j) tile[r * kPrepPitch + c + j] = v[j];
   }
@@ -695,10 +724,6 @@ void go(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStream_t s, const Ev
     hipLaunchKernelGGL(kernel, grid, block, 0, s, args...);
 }
 
-// Slab depth and LDS stages of the persistent update kernel (64-deep slabs
-// in two stages measured faster than 32-deep ones in three or four).
-constexpr int kUpdBK = 64, kUpdNS = 2;
-
 // Grid of a persistent kernel over `entries` tile-list entries: one block per
 // CU, rounded down to a multiple of the XCD count (entry e then runs on XCD
 // e % kXcds, as with one block per entry); never more blocks than entries.
@@ -721,6 +746,44 @@ int persistent_grid(int entries) {
   return entries < n ? entries : n;
 }
 
+// The persistent update kernel (256-tiles, 16-bit MFMA operands).
+template <typename Tx>
+void launch_upd256(Op op, const GemmArgs &a, hipStream_t s, const EvPair *ev) {
+  const dim3 grid(persistent_grid(a.ntiles)), block(Upd256<Tx>::NT);
+  if (a.fold) {
+    if (op == Op::Update) go(k_upd256<Tx, kUpdate, true>, grid, block, s, ev, a);
+    else go(k_upd256<Tx, kLast, true>, grid, block, s, ev, a);
+  } else if constexpr (!std::is_same<Tx, Split>::value) {
+    if (op == Op::Update) go(k_upd256<Tx, kUpdate, false>, grid, block, s, ev, a);
+    else go(k_upd256<Tx, kLast, false>, grid, block, s, ev, a);
+  } else {
+    throw HipError("no split 256-tile kernel for a cubic step");
+  }
+}
+
+// The products of the split iterate.
+template <int BM, int BN, int WGM, int WGN, int NS>
+void launch_tile(Op op, dim3 grid, const GemmArgs &a, hipStream_t s, const EvPair *ev) {
+  const dim3 block(64 * WGM * WGN);
+  switch (op) {
+    case Op::Gram:
+      go(k_tile<Split, kGram, BM, BN, WGM, WGN, NS>, grid, block, s, ev, a);
+      break;
+    case Op::Poly:
+      go(k_tile<Split, kPoly, BM, BN, WGM, WGN, NS>, grid, block, s, ev, a);
+      break;
+    case Op::Update:
+    default:
+      if constexpr (BM == kTile) {
+        if (op == Op::Update) go(k_tile<Split, kUpdate, BM, BN, WGM, WGN, NS>, grid, block, s, ev, a);
+        else go(k_tile<Split, kLast, BM, BN, WGM, WGN, NS>, grid, block, s, ev, a);
+      } else {
+        launch_upd256<Split>(op, a, s, ev);
+      }
+      break;
+  }
+}
+
 template <typename Tx, typename Tw, int BM, int BN, int WGM, int WGN>
 void launch_gemm(Op op, dim3 grid, const GemmArgs &a, hipStream_t s, const EvPair *ev) {
   const dim3 block(GemmShape<BM, BN, WGM, WGN>::kThreads);
@@ -736,18 +799,12 @@ void launch_gemm(Op op, dim3 grid, const GemmArgs &a, hipStream_t s, const EvPai
       go(k_gemm<Tx, Tw, kPoly, BM, BN, WGM, WGN>, grid, block, s, ev, a);
       break;
     case Op::Update:
-      if constexpr (kPersist) {
-        if (a.fold) go(k_upd256<kUpdate, true, kUpdBK, kUpdNS>, dim3(persistent_grid(a.ntiles)), block, s, ev, a);
-        else go(k_upd256<kUpdate, false, kUpdBK, kUpdNS>, dim3(persistent_grid(a.ntiles)), block, s, ev, a);
-      }
+      if constexpr (kPersist) launch_upd256<Tx>(op, a, s, ev);
       else if constexpr (kUpd) go(k_gemm<Tx, Tw, kUpdate, BM, BN, WGM, WGN>, grid, block, s, ev, a);
       else throw HipError("no fp32 256-tile update kernel");
       break;
     default:
-      if constexpr (kPersist) {
-        if (a.fold) go(k_upd256<kLast, true, kUpdBK, kUpdNS>, dim3(persistent_grid(a.ntiles)), block, s, ev, a);
-        else go(k_upd256<kLast, false, kUpdBK, kUpdNS>, dim3(persistent_grid(a.ntiles)), block, s, ev, a);
-      }
+      if constexpr (kPersist) launch_upd256<Tx>(op, a, s, ev);
       else if constexpr (kUpd) go(k_gemm<Tx, Tw, kLast, BM, BN, WGM, WGN>, grid, block, s, ev, a);
       else throw HipError("no fp32 256-tile update kernel");
       break;
@@ -761,7 +818,7 @@ void launch_grad(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev
   const DynDesc *dyn = reinterpret_cast<const DynDesc *>(ws + p.off_dyn);
   const Scalars *sc = reinterpret_cast<const Scalars *>(ws + p.off_scal);
   const CallParams *call = reinterpret_cast<const CallParams *>(ws + p.off_call);
-  const float inv_sx = 1.0f / (sizeof(Tx) == 2 ? kScaleX16 : 1.0f);
+  const float inv_sx = 1.0f / (std::is_same<Tx, float>::value ? 1.0f : kScaleX16);
   const int acc = (p.flags & SLORR_ACCUMULATE) ? 1 : 0;
   if (p.grad_dtype == SLORR_BF16)
     go(k_grad<Tw, Tx, bf16_t>, dim3(l.grid), dim3(kThreads), s, ev, tiles, mats, dyn, sc, call, ws, inv_sx, acc,
@@ -781,8 +838,7 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
   Scalars *sc = reinterpret_cast<Scalars *>(ws + p.off_scal);
   double *sumsq = reinterpret_cast<double *>(ws + p.off_sumsq);
   double *trace = reinterpret_cast<double *>(ws + p.off_trace);
-  const bool f16 = sizeof(Tx) == 2;
-  const float sx = f16 ? kScaleX16 : 1.0f;
+  const float sx = std::is_same<Tx, float>::value ? 1.0f : kScaleX16;
   {
     const dim3 grid(l.grid), block(kThreads);
     switch (l.op) {
@@ -801,7 +857,7 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
       case Op::Update:
       case Op::Last: {
         GemmArgs a;
-        a.tiles = tiles + l.tile_first;
+        a.tiles = tiles + l.run_first;
         a.mats = mats;
         a.dyn = dyn;
         a.ws = ws;
@@ -818,11 +874,18 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
         a.gamma = l.gamma;
         a.inv_sx = 1.0f / sx;
         a.gpart = reinterpret_cast<float *>(ws + p.off_gpart);
-        a.ntiles = l.grid;
-        if (l.cfg == kCfg256)
-          launch_gemm<Tx, Tw, kBigTile, kBigTile, 2, 4>(l.op, grid, a, s, ev);
-        else
-          launch_gemm<Tx, Tw, kTile, kTile, 2, 2>(l.op, grid, a, s, ev);
+        a.ntiles = l.run_grid;
+        const dim3 g(l.run_grid);
+        if constexpr (std::is_same<Tx, Split>::value) {
+          // at most one block per CU: 4 stages (see k_tile)
+          if (l.run_cfg == kCfg256) launch_tile<kBigTile, kBigTile, 2, 4, 2>(l.op, g, a, s, ev);
+          else if (l.run_grid <= kCus) launch_tile<kTile, kTile, 2, 2, 4>(l.op, g, a, s, ev);
+          else launch_tile<kTile, kTile, 2, 2, 2>(l.op, g, a, s, ev);
+        } else if (l.run_cfg == kCfg256) {
+          launch_gemm<Tx, Tw, kBigTile, kBigTile, 2, 4>(l.op, g, a, s, ev);
+        } else {
+          launch_gemm<Tx, Tw, kTile, kTile, 2, 2>(l.op, g, a, s, ev);
+        }
         break;
       }
       case Op::Finalize:
@@ -852,6 +915,8 @@ void enqueue(const Plan &p, hipStream_t s, hipEvent_t *events, void *ws) {
     const EvPair pair{events ? events[2 * li] : nullptr, events ? events[2 * li + 1] : nullptr};
     if (p.dtype == SLORR_BF16)
       launch_one<bf16_t, _Float16>(p, p.launches[li], s, events ? &pair : nullptr, w);
+    else if (p.split)
+      launch_one<float, Split>(p, p.launches[li], s, events ? &pair : nullptr, w);
     else
       launch_one<float, float>(p, p.launches[li], s, events ? &pair : nullptr, w);
   }
@@ -880,6 +945,8 @@ void enqueue_grad(const Plan &p, hipStream_t s) {
   for (const Launch &l : p.grad_launches) {
     if (p.dtype == SLORR_BF16)
       launch_one<bf16_t, _Float16>(p, l, s, nullptr, w);
+    else if (p.split)
+      launch_one<float, Split>(p, l, s, nullptr, w);
     else
       launch_one<float, float>(p, l, s, nullptr, w);
   }

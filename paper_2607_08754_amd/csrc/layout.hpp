@@ -20,7 +20,8 @@ constexpr int kXcds = 8;         // XCDs of an MI355X; workgroup b runs on XCD b
 constexpr int kCus = 256;        // compute units of an MI355X
 constexpr int kRedStripes = 4;   // split-K Gram reduce: blocks (row stripes) per tile
 
-// Power-of-two operand scales of the fp16 iterate (bf16 weights). With the
+// Power-of-two operand scales of the fp16 iterate (bf16 weights) and of the
+// split iterate (fp32 weights: two fp16 numbers per value). With the
 // input normalised by ||W||_F every singular value of X stays <= u_t <= 2, so
 // |X_ij| <= 2, |A_ij| <= 4 and |B_ij| <= max |b t + c t^2| over t in [0, 4]
 // (< 9 for the default schedule); the scales keep these far below the fp16

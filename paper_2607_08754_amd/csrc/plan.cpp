@@ -46,6 +46,41 @@ int32_t round_up(int32_t x, int32_t m) { return (x + m - 1) / m * m; }
 // step's trace reads it), later iterates alternate between x[1] and x[2].
 int32_t xbuf(int t) { return t == 0 ? 0 : 1 + ((t - 1) & 1); }
 
+// Whether every intermediate of an fp32 set's iteration fits the split form's
+// fp16 range, from the coefficient table alone: u bounds the singular values
+// of the iterate (X_0' = W / 2^e has none above 1, and the first step's
+// polynomial sees kappa X_0' = X_0, also <= 1), so |X_ij| <= u, |A_ij| <= u^2
+// and |B_ij| <= max |a + b x^2 + c x^4| on [0, u] (times kappa < 2 in the
+// first step). The scales (4096, 4096, 1024) leave fp16 (65504) room for
+// u <= 3.5 and |B_ij| <= 58. The built-in schedules stay below 2.1 and 9;
+// an explicit table that may exceed the range keeps the fp32 MFMA kernels.
+bool split_fits(const std::vector<double> &coeffs, int iters) {
+  constexpr double kMaxX = 3.5, kMaxB = 58.0;
+  double u = 1.0;
+  for (int t = 0; t < iters; ++t) {
+    const double a = coeffs[3 * t], b = coeffs[3 * t + 1], c = coeffs[3 * t + 2];
+    auto g = [&](double z) { return std::fabs(a + z * (b + z * c)); };   // |p(x) / x|, z = x^2
+    const double z1 = u * u;
+    double gmax = std::max(g(0.0), g(z1));
+    if (c != 0.0 && -b / (2 * c) > 0.0 && -b / (2 * c) < z1) gmax = std::max(gmax, g(-b / (2 * c)));
+    if (gmax * (t == 0 ? 2.0 : 1.0) > kMaxB) return false;
+    // extrema of p on [0, u]: a + 3 b z + 5 c z^2 = 0
+    double pmax = u * g(z1);
+    const double disc = 9 * b * b - 20 * a * c;
+    if (c == 0.0) {
+      if (b != 0.0 && -a / (3 * b) > 0.0 && -a / (3 * b) < z1) pmax = std::max(pmax, std::sqrt(-a / (3 * b)) * g(-a / (3 * b)));
+    } else if (disc >= 0.0) {
+      for (double r : {-3 * b + std::sqrt(disc), -3 * b - std::sqrt(disc)}) {
+        const double z = r / (10 * c);
+        if (z > 0.0 && z < z1) pmax = std::max(pmax, std::sqrt(z) * g(z));
+      }
+    }
+    u = pmax * 1.001;                  // rounding of the iterate
+    if (!(u <= kMaxX)) return false;
+  }
+  return true;
+}
+
 }  // namespace
 
 size_t Plan::dyn_bytes() const { return off_call + sizeof(CallParams) - off_dyn; }
@@ -85,7 +120,9 @@ void build_plan(Plan &p) {
     if (!std::isfinite(c)) throw std::invalid_argument("non-finite coefficient");
 
   const bool f16 = p.dtype == SLORR_BF16;
-  const float sx = f16 ? kScaleX16 : 1.0f, sa = f16 ? kScaleA16 : 1.0f, sb = f16 ? kScaleB16 : 1.0f;
+  p.split = p.dtype == SLORR_F32 && split_fits(p.coeffs, p.iters);
+  const bool scaled = f16 || p.split;      // 16-bit MFMA operands
+  const float sx = scaled ? kScaleX16 : 1.0f, sa = scaled ? kScaleA16 : 1.0f, sb = scaled ? kScaleB16 : 1.0f;
   bool any_quintic = false;
   for (int t = 0; t < p.iters; ++t) any_quintic |= p.coeffs[3 * t + 2] != 0.0;
 
@@ -305,6 +342,35 @@ void build_plan(Plan &p) {
     }
     for (int c = 0; c < kNumCfg; ++c) p.pq[c] = TileRange{};
     p.pq[cfg] = emit(std::move(jobs));
+    // The 128-tile list of a split set again as 256-tiles for the persistent
+    // update kernel, by the same rule; each 256-tile names the trace slot of
+    // its first 128-tile and the slots per column of 128-tiles (parts). Tables
+    // with a cubic step stay on 128-tiles (the 256-tile's a X term does not
+    // fit the registers next to the split trace).
+    p.upd = TileRange{};
+    bool run_big = p.split && !order.empty();
+    for (int t = 0; t < T; ++t) run_big &= p.coeffs[3 * t + 2] != 0.0;
+    int64_t nrun = 0;
+    for (int i : order) {
+      const MatDesc &d = p.mats[i];
+      run_big &= d.Pp % kBigTile == 0 && d.Qp % kBigTile == 0;
+      nrun += int64_t(d.Pp / kBigTile) * (d.Qp / kBigTile);
+    }
+    if (run_big && nrun >= kMinBigTiles) {
+      jobs.clear();
+      for (int i : order) {
+        const MatDesc &d = p.mats[i];
+        Job j{i, double(d.Pp), {}};
+        const int col = d.Pp / kTile;                       // slots per column
+        for (int tn = 0; tn < d.Qp / kBigTile; ++tn)
+          for (int tm = 0; tm < d.Pp / kBigTile; ++tm) {
+            j.tiles.push_back(make_tile(i, tm, tn, d.trace_begin + 2 * tn * col + 2 * tm));
+            j.tiles.back().parts = col;
+          }
+        jobs.push_back(std::move(j));
+      }
+      p.upd = emit(std::move(jobs));
+    }
   }
   p.trace_slots = slot;
   // canonical 64 x 64 tiles: the norm (one partial slot each, contiguous per
@@ -395,6 +461,14 @@ void build_plan(Plan &p) {
       l.grid = r[cfg].count;
       l.tile_first = r[cfg].first;
       l.cfg = cfg;
+      l.run_cfg = cfg;
+      l.run_first = l.tile_first;
+      l.run_grid = l.grid;
+      if ((op == Op::Update || op == Op::Last) && p.upd.count) {
+        l.run_cfg = kCfg256;
+        l.run_first = p.upd.first;
+        l.run_grid = p.upd.count;
+      }
       p.launches.push_back(l);
     }
   };
@@ -415,7 +489,9 @@ void build_plan(Plan &p) {
       g.op = Op::Gram;
       g.grid = p.gsplit.count;
       g.tile_first = p.gsplit.first;
-      g.cfg = kCfg128;
+      g.cfg = g.run_cfg = kCfg128;
+      g.run_first = g.tile_first;
+      g.run_grid = g.grid;
       p.launches.push_back(g);                // fp32 partials
       Launch l = plain(Op::GramReduce, p.gred.count * kRedStripes, p.gred.first);
       l.alpha = g.alpha;

@@ -41,7 +41,9 @@ struct Launch {
   Op op;
   int32_t grid;        // blocks
   int32_t tile_first;  // first entry of the launch's tile list (GEMM, prep)
-  int32_t cfg;         // GemmCfg of a GEMM launch
+  int32_t cfg;         // GemmCfg of a GEMM launch's tile list
+  int32_t run_cfg, run_first, run_grid;  // the kernel instance and list that run: those of
+                       // cfg, or 256-tiles that each cover four 128-tiles of the list
   int32_t xin, xout;   // X buffers read / written (MatDesc::x index)
   int32_t use_a;       // update operand is A (cubic step) instead of B
   int32_t fold;        // update: a_t I already folded into B (no a X term)
@@ -63,6 +65,7 @@ struct Plan {
   double ell = 1e-3;
   double safety = 0.01;                // stabilisation of the built-in schedule (0: none)
   float eps = 0.0f;
+  bool split = false;                  // fp32 set iterated in split form (two fp16 per value)
   uint32_t flags = 0;
   int32_t grad_dtype = SLORR_F32;    // slorr_dtype_t
   std::vector<slorr_shape_t> shapes;
@@ -75,6 +78,7 @@ struct Plan {
   TileRange pp[kNumCfg];               // P x P poly outputs, per GemmCfg
   TileRange pq[kNumCfg];               // P x Q outputs (update, last), per GemmCfg
   TileRange prep;                      // prep tiles over Pp x Qp
+  TileRange upd;                       // the 128-tile update list as 256-tiles (empty: not used)
   TileRange gsplit, gred;              // split-K Gram: part entries, reduce entries
   int32_t gram_parts = 0;              // fp32 partial tiles in the workspace
   int32_t trace_slots = 0;             // one per update tile

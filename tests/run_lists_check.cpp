@@ -1,0 +1,94 @@
+// The tile lists that launches run in place of the plan's own (Launch::run_*),
+// checked on the plan built for one weight set: every 128-tile of the update
+// list is covered once by the 256-tiles that run, each of its trace slots is
+// the one the run tile's slot and stride name, and entries stay on one XCD's
+// queue with padding at its end. Input as for plan_check.cpp (stdin); built
+// by tests/test_run_lists.py.
+#include <cstdio>
+#include <iostream>
+#include <map>
+#include <tuple>
+
+#include "plan.hpp"
+
+using namespace slorr;
+
+int main() {
+  int dtype, kind, iters, ncoef, n;
+  unsigned flags;
+  if (!(std::cin >> dtype >> kind >> iters >> flags >> ncoef)) return 2;
+  Plan p;
+  p.dtype = dtype;
+  p.kind = kind;
+  p.iters = iters;
+  p.flags = flags;
+  if (ncoef) {
+    p.coeffs.resize(size_t(3) * iters);
+    for (double &c : p.coeffs) std::cin >> c;
+  }
+  std::cin >> n;
+  p.n = n;
+  for (int i = 0; i < n; ++i) {
+    slorr_shape_t s;
+    std::cin >> s.rows >> s.cols;
+    p.shapes.push_back(s);
+  }
+  p.mats.resize(size_t(n));
+  build_plan(p);
+  int bad = 0;
+  auto fail = [&](const char *m, int a, int b, int c) {
+    if (++bad < 20) std::printf("FAIL %s: %d %d %d\n", m, a, b, c);
+  };
+  std::map<std::tuple<int, int, int>, int> slot_of;      // 128-tile -> its slot in the plan's list
+  for (int e = 0; e < p.pq[kCfg128].count; ++e) {
+    const Tile &t = p.tiles[p.pq[kCfg128].first + e];
+    if (t.mat >= 0) slot_of[{t.mat, t.tm, t.tn}] = t.slot;
+  }
+  if (p.upd.count) {
+    if (p.upd.count % kXcds) fail("entries per XCD", p.upd.count, 0, 0);
+    if (p.upd.first < 0 || size_t(p.upd.first) + p.upd.count > p.tiles.size()) fail("list range", p.upd.first, p.upd.count, 0);
+    bool pad[kXcds] = {};
+    std::map<std::tuple<int, int, int>, int> seen;
+    for (int e = 0; e < p.upd.count; ++e) {
+      const Tile &t = p.tiles[p.upd.first + e];
+      if (t.mat < 0) {
+        pad[e % kXcds] = true;
+        continue;
+      }
+      if (pad[e % kXcds]) fail("tile after padding", e, 0, 0);
+      const MatDesc &d = p.mats[t.mat];
+      for (int qm = 0; qm < 2; ++qm)
+        for (int qn = 0; qn < 2; ++qn) {
+          const int tm = 2 * t.tm + qm, tn = 2 * t.tn + qn;
+          if (tm * kTile >= d.Pp || tn * kTile >= d.Qp) {
+            if (qm + qn == 0) fail("run tile outside its matrix", t.mat, t.tm, t.tn);
+            continue;
+          }
+          seen[{t.mat, tm, tn}]++;
+          auto it = slot_of.find({t.mat, tm, tn});
+          if (it == slot_of.end()) fail("no such 128-tile", t.mat, tm, tn);
+          else if (it->second != t.slot + qn * t.parts + qm) fail("slot", it->second, t.slot, t.parts);
+        }
+    }
+    for (const auto &kv : slot_of) {
+      auto it = seen.find(kv.first);
+      if (it == seen.end() || it->second != 1)
+        fail("128-tile not covered once", std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first));
+    }
+  }
+  int run = 0;
+  for (const Launch &l : p.launches) {
+    if (l.op == Op::Gram || l.op == Op::Poly) {
+      if (l.run_cfg != l.cfg || l.run_first != l.tile_first || l.run_grid != l.grid) fail("Gram / poly run list", l.cfg, l.run_cfg, 0);
+    } else if (l.op == Op::Update || l.op == Op::Last) {
+      const bool big = p.upd.count > 0;
+      run += big;
+      if (big ? (l.run_cfg != kCfg256 || l.run_first != p.upd.first || l.run_grid != p.upd.count)
+              : (l.run_cfg != l.cfg || l.run_first != l.tile_first || l.run_grid != l.grid))
+        fail("update run list", l.cfg, l.run_cfg, l.run_grid);
+    }
+  }
+  if (bad) return 1;
+  std::printf("OK split=%d run256=%d\n", p.split ? 1 : 0, run);
+  return 0;
+}

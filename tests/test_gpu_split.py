@@ -1,0 +1,72 @@
+"""fp32 sets iterated in split form (two fp16 numbers per value) against the
+oracle at the edges of its tiles, the 256-tile kernels against 64-bit torch,
+and a table outside the split form's range, which keeps fp32 MFMA."""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+from oracle.pe_schedule import default_table  # noqa: E402
+from parity_util import compare, run_gpu, run_oracle  # noqa: E402
+from workloads import gaussian  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+# rows and columns around the 32-value runs, the 64-column wave tiles and the
+# 128-tiles; single rows; a long thin one (split-K Gram)
+EDGES = [(31, 33), (32, 32), (33, 31), (64, 65), (127, 129), (128, 256), (1, 40), (65, 4100), (385, 384)]
+
+
+@pytest.mark.parametrize("iters", [5, 6])
+def test_split_edges(iters):
+    """fp32 tolerance (1e-4) on every measure; the values to 2e-6: T steps of
+    fp32 accumulation (rounding 2^-24 per 16 terms) scaled by the unconverged
+    last polynomial's slope, about 10 at T = 5."""
+    arrs = [gaussian(s, seed=60, std=0.05, dtype="f32", index=i) for i, s in enumerate(EDGES)]
+    stationary = [min(s) == 1 for s in EDGES]
+    vals, grads, _ = run_gpu(arrs, "f32", "hoyer", iters)
+    refs = run_oracle(arrs, "f32", "hoyer", iters)
+    compare(vals, grads, refs, "hoyer", "f32", label=f"split edges T={iters}", stationary=stationary)
+    assert max(abs(vals[i] - r.value) / r.value for i, r in enumerate(refs)) <= 2e-6
+
+
+@pytest.mark.parametrize("shape,n", [((512, 2048), 32), ((2048, 512), 32)])
+def test_split_256_tiles(shape, n):
+    """The smallest set whose update runs on 256-tiles: every matrix against
+    the same iteration in float64."""
+    import torch
+    from paper_2607_08754_amd import Plan
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(9)
+    W = [torch.randn(shape, generator=gen, device="cuda:0") * 0.02 for _ in range(n)]
+    G = [torch.empty(shape, device="cuda:0") for _ in range(n)]
+    plan = Plan([shape] * n, dtype="f32", iters=6)
+    assert any(op == "update" and edge == 256 for op, _, edge in plan.launches())
+    vals = plan(W, G).double()
+    for i, w in enumerate(W):
+        w = w.double()
+        y = w if shape[0] <= shape[1] else w.t().contiguous()
+        f = y.norm()
+        x = y / f
+        for a, b, c in default_table(6):
+            s = x @ x.t()
+            x = a * x + (b * s + c * (s @ s)) @ x
+        nh = (y * x).sum()
+        g = 2 * nh / f ** 2 * x - 2 * nh ** 2 / f ** 4 * y
+        g = g if shape[0] <= shape[1] else g.t()
+        assert abs(vals[i] - (nh / f) ** 2) <= 1e-6 * (nh / f) ** 2, i
+        assert (G[i] - g).norm() <= 2e-5 * g.norm(), i
+
+
+def test_table_outside_the_split_range():
+    """An explicit table whose iterate reaches 16 (65536 in fp16's scale)."""
+    table = np.array([[16.0, 0.0, 0.0], [1 / 16, 0.0, 0.0], [1.875, -1.25, 0.375]])
+    shapes = [(80, 150), (150, 80)]
+    arrs = [gaussian(s, seed=22, std=1.0, dtype="f32", index=i) for i, s in enumerate(shapes)]
+    vals, grads, _ = run_gpu(arrs, "f32", "nuclear", 3, coeffs=table)
+    refs = run_oracle(arrs, "f32", "nuclear", 3, table=table)
+    compare(vals, grads, refs, "nuclear", "f32", label="outside the split range")

@@ -1,0 +1,71 @@
+"""The planner's run lists (128-tiles of the update list run as 256-tiles) and
+the rule that takes fp32 sets to the split form, on the CPU: tests/
+run_lists_check.cpp is built with g++ against the planner's own sources."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+from workloads import CONFIGS  # noqa: E402
+
+CSRC = os.path.join(ROOT, "paper_2607_08754_amd", "csrc")
+F32, BF16 = 0, 1
+
+
+@pytest.fixture(scope="module")
+def checker(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    exe = str(tmp_path_factory.mktemp("run_lists") / "run_lists_check")
+    cmd = ["g++", "-std=c++17", "-O1", "-I", CSRC, "-I", os.path.join(ROOT, "include"),
+           os.path.join(ROOT, "tests", "run_lists_check.cpp"), os.path.join(CSRC, "plan.cpp"),
+           os.path.join(CSRC, "pe_schedule.cpp"), "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    return exe
+
+
+def run(checker, shapes, dtype, iters=6, coeffs=None):
+    head = f"{dtype} 0 {iters} 0 {1 if coeffs is not None else 0}\n"
+    if coeffs is not None:
+        head += " ".join(repr(float(c)) for c in coeffs) + "\n"
+    body = f"{len(shapes)}\n" + "".join(f"{r} {c}\n" for r, c in shapes)
+    r = subprocess.run([checker], input=head + body, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.startswith("OK"), r.stdout[-4000:] + r.stderr[-2000:]
+    return dict(kv.split("=") for kv in r.stdout.split()[1:])
+
+
+@pytest.mark.parametrize("name", sorted(CONFIGS))
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_run_lists(checker, name, dtype):
+    got = run(checker, CONFIGS[name].shapes, dtype, CONFIGS[name].iters)
+    assert got["split"] == ("1" if dtype == F32 else "0")
+
+
+def test_run_lists_edges(checker):
+    assert run(checker, [(512, 2048)] * 32, F32)["run256"] == "6"       # 512 256-tiles: the smallest such set
+    assert run(checker, [(512, 2048)] * 31, F32)["run256"] == "0"
+    run(checker, [(1, 300), (7, 13), (130, 257), (0, 5)], F32)
+    cubic = [1.5, -0.5, 0.0] * 6
+    assert run(checker, [(512, 2048)] * 32, F32, coeffs=cubic)["run256"] == "0"
+
+
+# the range rule of the split form: |X| <= 3.5 and |B| <= 58 over the whole
+# table (twice |B| in the first step, whose matrix is scaled by kappa < 2)
+@pytest.mark.parametrize("coeffs,split", [
+    ([15 / 8, -10 / 8, 3 / 8] * 2, 1),          # Newton-Schulz
+    ([3.4445, -4.7750, 2.0315] * 3, 1),         # maps [0, 1] into [0, 1.3]
+    ([1.5, -0.5, 0.0] * 2, 1),                  # cubic
+    ([3.4, 0.0, 0.0, 0.2, 0.0, 0.0], 1),        # X up to 3.4
+    ([3.6, 0.0, 0.0, 0.2, 0.0, 0.0], 0),        # X up to 3.6
+    ([28.0, -40.0, 13.0, 1.0, 0.0, 0.0], 0),    # an interior extremum of X beyond the range
+    ([30.0, -100.0, 71.0, 1.0, 0.0, 0.0], 0),   # 2 |B| up to 60 at x = 0
+    ([1.0, 0.0, 0.0, 1.0, 60.0, -61.0], 0),     # interior extrema in a later step
+])
+def test_split_rule(checker, coeffs, split):
+    assert run(checker, [(64, 96)], F32, iters=len(coeffs) // 3, coeffs=coeffs)["split"] == str(split)
+    assert run(checker, [(64, 96)], BF16, iters=len(coeffs) // 3, coeffs=coeffs)["split"] == "0"
