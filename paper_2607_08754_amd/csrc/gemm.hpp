@@ -79,6 +79,8 @@ struct GemmArgs {
   int kap;        // first step: coefficients times powers of the matrix's kappa
   float alpha, beta, gamma, inv_sx;
   float *gpart;   // Gram parts (split K): fp32 partial tiles, BM x BN each, at tile.slot
+  int quads;      // k_upd256 over a list of 128-tiles: a trace slot per 128 x 128 quadrant
+                  // (slot of the first, Pp / 128 slots from one column of quadrants to the next)
   int ntiles;     // entries of the tile list (a persistent kernel's grid can be smaller)
 };
 
@@ -128,9 +130,9 @@ __device__ __forceinline__ i32x4 buffer_rsrc(const void *base, uint32_t bytes) {
   r[3] = 0x00020000;                                                         // raw 32-bit dwords
   return r;
 }
-__device__ __forceinline__ void buffer_load_lds16(i32x4 rsrc, uint32_t voff, uint32_t soff, void *lds_base) {
+__device__ __forceinline__ void buffer_load_lds16(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_base) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  const uint32_t m = __builtin_amdgcn_readfirstlane(uint32_t(uintptr_t(lds_base)));
+  const uint32_t m = __builtin_amdgcn_readfirstlane(lds_base);
   const uint32_t so = __builtin_amdgcn_readfirstlane(soff);
   asm volatile("buffer_load_dwordx4 %1, %2, %3 offen lds" : : "{m0}"(m), "v"(voff), "s"(rsrc), "s"(so) : "memory");
 #else
@@ -139,6 +141,9 @@ __device__ __forceinline__ void buffer_load_lds16(i32x4 rsrc, uint32_t voff, uin
   (void)soff;
   (void)lds_base;
 #endif
+}
+__device__ __forceinline__ void buffer_load_lds16(i32x4 rsrc, uint32_t voff, uint32_t soff, void *lds_base) {
+  buffer_load_lds16(rsrc, voff, soff, uint32_t(uintptr_t(lds_base)));
 }
 
 // Transposing LDS read of 16-bit values (ds_read_b64_tr_b16). Within each

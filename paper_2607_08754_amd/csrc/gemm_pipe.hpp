@@ -83,6 +83,17 @@ __device__ __forceinline__ double trace_planes(const half8 (&p)[Iter<T>::kPlanes
   return t;
 }
 
+// LDS byte offset of a shared array. The fetches below take offsets, not
+// pointers: a generic pointer would be cast back to LDS with a null check.
+__device__ __forceinline__ uint32_t lds_offset(const char *smem) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return uint32_t(uintptr_t((const __attribute__((address_space(3))) char *)smem));
+#else
+  (void)smem;
+  return 0;
+#endif
+}
+
 // s_waitcnt vmcnt(N), the other counters left alone (gfx9 encoding).
 template <int N>
 __device__ __forceinline__ void vm_wait() {
@@ -258,7 +269,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_tile(GemmArgs args) {
   const uint32_t skip = part ? uint32_t(tile.k0) * uint32_t(sizeof(T)) : 0u;
   const uint32_t abytes = uint32_t(d.Pp) * uint32_t(lda) * uint32_t(sizeof(T)) - skip;
   const uint32_t bbytes = uint32_t(d.Pp) * uint32_t(ldb) * uint32_t(sizeof(T)) - skip;
-  auto fetch_rows = [&](const char *base, uint32_t bytes, int ld, int row0, int k0, char *dst) {
+  auto fetch_rows = [&](const char *base, uint32_t bytes, int ld, int row0, int k0, uint32_t dst) {
     const i32x4 rs = buffer_rsrc(base, bytes);
     const int row = wave * 8 + (lane >> 3);
     const uint32_t voff =
@@ -268,9 +279,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_tile(GemmArgs args) {
       buffer_load_lds16(rs, voff, (uint32_t(k0) + uint32_t(i) * uint32_t(8 * S::kFW) * uint32_t(ld)) * uint32_t(sizeof(T)),
                         dst + (wave + i * S::kFW) * 1024);
   };
+  const uint32_t lds0 = lds_offset(smem);
   auto dload = [&](int k0, int st) {
     if (wave >= S::kFW) return;
-    char *sA = smem + st * S::kStage, *sB = sA + S::kStageA;
+    const uint32_t sA = lds0 + uint32_t(st) * S::kStage, sB = sA + S::kStageA;
     fetch_rows(Ap, abytes, lda, m0, k0, sA);
     if constexpr (S::KN) {
       constexpr int CPR = S::KNP / 16;
@@ -537,6 +549,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_tile(GemmArgs args) {
 // writes; 16-byte reads then give each lane 8 consecutive columns, 8 lanes
 // per row, so the global stores write whole 128-byte row segments. Every
 // output element is the same fp32 sum rounded once, as in k_gemm.
+//
+// Edge tiles: the padded dims are multiples of 128, so a matrix whose dims are
+// not multiples of 256 ends in tiles of which a half lies outside. The fetches
+// stay inside the matrix, and the waves whose tile lies outside only fetch and
+// keep the barriers.
 template <typename T>
 struct Upd256 {
   static constexpr int BM = 256, BN = 256, WGM = 2, WGN = 4, kWaves = 8, NT = 512;
@@ -572,12 +589,6 @@ __device__ __forceinline__ int epi_off(int row, int chunk) {
   return row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4);
 }
 
-__device__ __forceinline__ uint64_t readlane64(uint64_t v, int lane) {
-  const uint32_t lo = __builtin_amdgcn_readlane(uint32_t(v), lane);
-  const uint32_t hi = __builtin_amdgcn_readlane(uint32_t(v >> 32), lane);
-  return (uint64_t(hi) << 32) | lo;
-}
-
 template <typename T, int MODE, bool FOLD>
 __global__ __launch_bounds__(512) void k_upd256(GemmArgs args) {
   using U = Upd256<T>;
@@ -596,29 +607,23 @@ __global__ __launch_bounds__(512) void k_upd256(GemmArgs args) {
 
   // register table of tile contexts, positions tb .. tb + 63 (lane t: tb + t)
   int tb = 0;
-  int v_mat, v_tm, v_tn, v_slot, v_ss, v_pp, v_qp;
-  uint64_t v_a, v_xi, v_xo, v_x0;
+  int v_mat, v_tmn, v_slot, v_pq;
+  uint32_t v_x;        // byte offset of the matrix's buffers / 256
   auto load_table = [&](int base) {
     tb = base;
     const int pos = base + lane;
     v_mat = -1;
-    v_tm = v_tn = v_slot = v_ss = v_pp = v_qp = 0;
-    v_a = v_xi = v_xo = v_x0 = 0;
+    v_tmn = v_slot = v_pq = 0;
+    v_x = 0;
     if (pos < npos) {
       const Tile t = args.tiles[int(blockIdx.x) + pos * G];
       v_mat = t.mat;
       if (t.mat >= 0) {
         const MatDesc *d = args.mats + t.mat;
-        v_tm = t.tm;
-        v_tn = t.tn;
+        v_tmn = t.tm | t.tn << 8;      // tm < 64, tn < 4096 (the plan's size limits)
         v_slot = t.slot;
-        v_ss = t.parts;
-        v_pp = d->Pp;
-        v_qp = d->Qp;
-        v_a = args.use_a ? d->a : d->b;
-        v_xi = d->x[args.xin];
-        v_xo = d->x[args.xout];
-        v_x0 = d->x[0];
+        v_pq = d->Pp / kTile | d->Qp / kTile << 8;   // Pp <= 16384, Qp <= 2^20
+        v_x = uint32_t(d->x[0] >> 8);
       }
     }
   };
@@ -627,8 +632,6 @@ __global__ __launch_bounds__(512) void k_upd256(GemmArgs args) {
     char *Xn;              // output iterate
     const char *X0;        // X_0' (trace)
     int ldx, K, m0, n0, mat, slot;
-    int ss;                // 0: one trace slot; else one per 128 x 128 quadrant,
-                           // ss slots from one column of quadrants to the next
   };
   // the first valid position >= pos (npos if none); reloads the table when
   // pos leaves it
@@ -642,17 +645,21 @@ __global__ __launch_bounds__(512) void k_upd256(GemmArgs args) {
   auto ctx_at = [&](int pos) {
     const int t = pos - tb;
     Ctx c;
-    c.Ap = args.ws + readlane64(v_a, t);
-    c.Bp = args.ws + readlane64(v_xi, t);
-    c.Xn = args.ws + readlane64(v_xo, t);
-    c.X0 = args.ws + readlane64(v_x0, t);
-    c.ldx = __builtin_amdgcn_readlane(v_qp, t);
-    c.K = __builtin_amdgcn_readlane(v_pp, t);
-    c.m0 = __builtin_amdgcn_readlane(v_tm, t) * U::BM;
-    c.n0 = __builtin_amdgcn_readlane(v_tn, t) * U::BN;
+    const int pq = __builtin_amdgcn_readlane(v_pq, t);
+    c.ldx = (pq >> 8) * kTile;
+    c.K = (pq & 255) * kTile;
+    // a matrix's buffers follow each other: x[0], x[1], x[2], a, b (MatDesc)
+    const size_t px = size_t(c.K) * c.ldx * sizeof(T), pa = size_t(c.K) * c.K * sizeof(T);
+    char *base = args.ws + (size_t(uint32_t(__builtin_amdgcn_readlane(int(v_x), t))) << 8);
+    c.X0 = base;
+    c.Bp = base + size_t(args.xin) * px;
+    c.Xn = base + size_t(args.xout) * px;
+    c.Ap = base + 3 * px + (args.use_a ? 0 : pa);
+    const int tmn = __builtin_amdgcn_readlane(v_tmn, t);
+    c.m0 = (tmn & 255) * U::BM;
+    c.n0 = (tmn >> 8) * U::BN;
     c.mat = __builtin_amdgcn_readlane(v_mat, t);
     c.slot = __builtin_amdgcn_readlane(v_slot, t);
-    c.ss = __builtin_amdgcn_readlane(v_ss, t);
     return c;
   };
 
@@ -667,25 +674,31 @@ __global__ __launch_bounds__(512) void k_upd256(GemmArgs args) {
   // of rows apart, and the swizzle key repeats over them).
   static_assert((U::kFetchWaves * U::RPA) % 16 == 0 && (U::kFetchWaves * U::RPX) % 4 == 0, "swizzle period");
   constexpr uint32_t ES = sizeof(T);
+  const uint32_t lds0 = lds_offset(smem);
   auto dload = [&](const Ctx &c, int k0, int st) {
     if (wave >= U::kFetchWaves) return;
-    char *sA = smem + st * U::kStage;
-    char *sB = sA + U::kStageA;
+    const uint32_t sA = lds0 + uint32_t(st) * U::kStage, sB = sA + U::kStageA;
     {
       const i32x4 ra = buffer_rsrc(c.Ap, uint32_t(c.K) * uint32_t(c.K) * ES);     // K x K
       const int row = wave * U::RPA + (lane >> 3);
       const uint32_t voff = (uint32_t(c.m0 + row) * uint32_t(c.K) + uint32_t(((lane & 7) ^ swz_key(row)) * V)) * ES;
       const uint32_t step = uint32_t(U::kFetchWaves * U::RPA) * uint32_t(c.K) * ES;
 #pragma unroll
-      for (int i = 0; i < U::kLoadsA; ++i)
+      for (int i = 0; i < U::kLoadsA / 2; ++i)
         buffer_load_lds16(ra, voff, uint32_t(k0) * ES + uint32_t(i) * step, sA + (wave + i * U::kFetchWaves) * 1024);
+      if (c.m0 + U::BM / 2 < c.K) {          // the lower half lies inside the matrix
+#pragma unroll
+        for (int i = U::kLoadsA / 2; i < U::kLoadsA; ++i)
+          buffer_load_lds16(ra, voff, uint32_t(k0) * ES + uint32_t(i) * step, sA + (wave + i * U::kFetchWaves) * 1024);
+      }
     }
     constexpr int CPR = U::KNP / 16;
     {
       const i32x4 rx = buffer_rsrc(c.Bp, uint32_t(c.K) * uint32_t(c.ldx) * ES);  // K x ldx
       const int row = wave * U::RPX + lane / CPR;
-      const uint32_t voff = (uint32_t(row) * uint32_t(c.ldx) +
-                             uint32_t(c.n0 + ((lane % CPR) ^ ((row & 3) << 2)) * V)) * ES;
+      int col = c.n0 + ((lane % CPR) ^ ((row & 3) << 2)) * V;
+      col -= col >= c.ldx ? U::BN / 2 : 0;   // right half outside the matrix: the left half again, unused
+      const uint32_t voff = (uint32_t(row) * uint32_t(c.ldx) + uint32_t(col)) * ES;
       const uint32_t step = uint32_t(U::kFetchWaves * U::RPX) * uint32_t(c.ldx) * ES;
 #pragma unroll
       for (int i = 0; i < U::kLoadsX; ++i)
@@ -772,13 +785,15 @@ __global__ __launch_bounds__(512) void k_upd256(GemmArgs args) {
       for (int j = 0; j < U::FN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-    // K is a multiple of 256 (padding), so of BK
+    // K is a multiple of 128 (padding), so of BK
     const int nk = cur.K / BK;
+    // a wave tile of an edge tile lies wholly inside the matrix or outside it
+    const bool active = cur.m0 + wm * U::WTM < cur.K && cur.n0 + wn * U::WTN < cur.ldx;
     for (int kt = 0; kt < nk; ++kt, ++g) {
       vm_wait_slabs<U::kLoads, NS - 2>(issued - g - 1);   // slab g has landed (this wave's part)
       __syncthreads();                 // ... every wave's part; slab g - 1 is done
       produce((g + NS - 1) % NS);
-      compute(g % NS);
+      if (active) compute(g % NS);
     }
 
     // ---------------------------------------------------------- epilogue
@@ -790,81 +805,83 @@ __global__ __launch_bounds__(512) void k_upd256(GemmArgs args) {
     }
     const int row_w = cur.m0 + wm * U::WTM, col_w = cur.n0 + wn * U::WTN;
     double tsum = 0.0;
+    if (active) {
 #pragma unroll
-    for (int i = 0; i < XB; ++i) x0load(cur, i);
+      for (int i = 0; i < XB; ++i) x0load(cur, i);
 #pragma unroll
-    for (int i = 0; i < U::FM; ++i) {
-      half4 hv[U::FN][4][PL];
-#pragma unroll
-      for (int j = 0; j < U::FN; ++j)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          float v[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = acc[i][j][4 * q4 + q];
-          if constexpr (FOLD) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] *= alpha;
-          } else {
-            half4 in[PL];
-#pragma unroll
-            for (int p = 0; p < PL; ++p)
-              in[p] = *reinterpret_cast<const half4 *>(
-                  cur.Bp + byte_of<T>(size_t(row_w + i * 32 + lr), cur.ldx, col_w + 32 * j + 8 * q4 + 4 * lk, p));
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = beta * of_planes<T>(in, q) + alpha * v[q];
-          }
-          to_planes<T>(v, hv[j][q4]);
-          *reinterpret_cast<half4 *>(ep + epi_off(lr, 4 * j + q4) + 8 * lk) = hv[j][q4][0];
-        }
-      // the staging area (one plane of the block) is the wave's own and one
-      // wave's LDS operations are performed in order: a wave-level barrier
-      // (no reordering) suffices
-      __builtin_amdgcn_wave_barrier();
-      half8 hi[PL == 2 ? 4 : 1];
-      if constexpr (PL == 2) {             // take the hi plane, then stage the lo plane
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int c = lane + 64 * t;
-          hi[t] = *reinterpret_cast<const half8 *>(ep + epi_off(c >> 3, c & 7));
-        }
-        __builtin_amdgcn_wave_barrier();
+      for (int i = 0; i < U::FM; ++i) {
+        half4 hv[U::FN][4][PL];
 #pragma unroll
         for (int j = 0; j < U::FN; ++j)
 #pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4)
-            *reinterpret_cast<half4 *>(ep + epi_off(lr, 4 * j + q4) + 8 * lk) = hv[j][q4][PL - 1];
+          for (int q4 = 0; q4 < 4; ++q4) {
+            float v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = acc[i][j][4 * q4 + q];
+            if constexpr (FOLD) {
+#pragma unroll
+              for (int q = 0; q < 4; ++q) v[q] *= alpha;
+            } else {
+              half4 in[PL];
+#pragma unroll
+              for (int p = 0; p < PL; ++p)
+                in[p] = *reinterpret_cast<const half4 *>(
+                    cur.Bp + byte_of<T>(size_t(row_w + i * 32 + lr), cur.ldx, col_w + 32 * j + 8 * q4 + 4 * lk, p));
+#pragma unroll
+              for (int q = 0; q < 4; ++q) v[q] = beta * of_planes<T>(in, q) + alpha * v[q];
+            }
+            to_planes<T>(v, hv[j][q4]);
+            *reinterpret_cast<half4 *>(ep + epi_off(lr, 4 * j + q4) + 8 * lk) = hv[j][q4][0];
+          }
+        // the staging area (one plane of the block) is the wave's own and one
+        // wave's LDS operations are performed in order: a wave-level barrier
+        // (no reordering) suffices
+        __builtin_amdgcn_wave_barrier();
+        half8 hi[PL == 2 ? 4 : 1];
+        if constexpr (PL == 2) {             // take the hi plane, then stage the lo plane
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const int c = lane + 64 * t;
+            hi[t] = *reinterpret_cast<const half8 *>(ep + epi_off(c >> 3, c & 7));
+          }
+          __builtin_amdgcn_wave_barrier();
+#pragma unroll
+          for (int j = 0; j < U::FN; ++j)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+              *reinterpret_cast<half4 *>(ep + epi_off(lr, 4 * j + q4) + 8 * lk) = hv[j][q4][PL - 1];
+          __builtin_amdgcn_wave_barrier();
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int c = lane + 64 * t, row = c >> 3, ch = c & 7;
+          half8 h[PL];
+          h[PL - 1] = *reinterpret_cast<const half8 *>(ep + epi_off(row, ch));
+          if constexpr (PL == 2) h[0] = hi[t];
+#pragma unroll
+          for (int p = 0; p < PL; ++p) {
+            half8 *o = reinterpret_cast<half8 *>(cur.Xn + byte_of<T>(size_t(row_w + i * 32 + row), cur.ldx, col_w + 8 * ch, p));
+            // the iterate of a step is streamed out (the next launch reads it,
+            // and its lines would evict operand panels this launch still reads);
+            // X_T, read by the gradient kernel two short launches later, is
+            // stored normally (measured faster; split: always, a branch here
+            // costs the registers that keep this kernel out of scratch memory)
+            if constexpr (MODE == kUpdate) __builtin_nontemporal_store(h[p], o);
+            else if (PL == 2 || args.write_x) *o = h[p];
+          }
+          if constexpr (MODE == kLast) {     // P as stored times X_0'
+            if constexpr (XB == 0) {
+#pragma unroll
+              for (int p = 0; p < PL; ++p)
+                x0v[0][t][p] = __builtin_nontemporal_load(reinterpret_cast<const half8 *>(
+                    cur.X0 + byte_of<T>(size_t(row_w + i * 32 + row), cur.ldx, col_w + 8 * ch, p)));
+            }
+            tsum += trace_planes<T>(h, x0v[XB ? i % XB : 0][t]);
+          }
+        }
+        if (XB && i + XB < U::FM) x0load(cur, i + XB);
         __builtin_amdgcn_wave_barrier();
       }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int c = lane + 64 * t, row = c >> 3, ch = c & 7;
-        half8 h[PL];
-        h[PL - 1] = *reinterpret_cast<const half8 *>(ep + epi_off(row, ch));
-        if constexpr (PL == 2) h[0] = hi[t];
-#pragma unroll
-        for (int p = 0; p < PL; ++p) {
-          half8 *o = reinterpret_cast<half8 *>(cur.Xn + byte_of<T>(size_t(row_w + i * 32 + row), cur.ldx, col_w + 8 * ch, p));
-          // the iterate of a step is streamed out (the next launch reads it,
-          // and its lines would evict operand panels this launch still reads);
-          // X_T, read by the gradient kernel two short launches later, is
-          // stored normally (measured faster; split: always, a branch here
-          // costs the registers that keep this kernel out of scratch memory)
-          if constexpr (MODE == kUpdate) __builtin_nontemporal_store(h[p], o);
-          else if (PL == 2 || args.write_x) *o = h[p];
-        }
-        if constexpr (MODE == kLast) {     // P as stored times X_0'
-          if constexpr (XB == 0) {
-#pragma unroll
-            for (int p = 0; p < PL; ++p)
-              x0v[0][t][p] = __builtin_nontemporal_load(reinterpret_cast<const half8 *>(
-                  cur.X0 + byte_of<T>(size_t(row_w + i * 32 + row), cur.ldx, col_w + 8 * ch, p)));
-          }
-          tsum += trace_planes<T>(h, x0v[XB ? i % XB : 0][t]);
-        }
-      }
-      if (XB && i + XB < U::FM) x0load(cur, i + XB);
-      __builtin_amdgcn_wave_barrier();
     }
     if constexpr (MODE == kLast) {
       // per-tile partial of the trace: waves in order, each a fixed butterfly
@@ -873,7 +890,7 @@ __global__ __launch_bounds__(512) void k_upd256(GemmArgs args) {
       __syncthreads();
       const double *ws8 = reinterpret_cast<const double *>(smem + NS * U::kStage);
       constexpr int kStep = U::kEpi / int(sizeof(double));
-      if (cur.ss == 0) {
+      if (!args.quads) {
         if (tid == 0) {
           double r = 0.0;
           for (int q = 0; q < U::kWaves; ++q) r += ws8[q * kStep];
@@ -881,7 +898,8 @@ __global__ __launch_bounds__(512) void k_upd256(GemmArgs args) {
         }
       } else if (tid < 4) {                // quadrant (tid / 2, tid % 2): two waves
         const int qm = tid >> 1, qn = tid & 1, q = qm * U::WGN + 2 * qn;
-        args.tpart[cur.slot + qn * cur.ss + qm] = ws8[q * kStep] + ws8[(q + 1) * kStep];
+        if (cur.m0 + qm * kTile < cur.K && cur.n0 + qn * kTile < cur.ldx)
+          args.tpart[cur.slot + qn * (cur.K / kTile) + qm] = ws8[q * kStep] + ws8[(q + 1) * kStep];
       }
     }
     if (npos_c == pos) break;          // the fetches found no further tile

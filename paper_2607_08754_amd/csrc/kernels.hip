@@ -874,6 +874,7 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
         a.gamma = l.gamma;
         a.inv_sx = 1.0f / sx;
         a.gpart = reinterpret_cast<float *>(ws + p.off_gpart);
+        a.quads = l.run_cfg != l.cfg;
         a.ntiles = l.run_grid;
         const dim3 g(l.run_grid);
         if constexpr (std::is_same<Tx, Split>::value) {

@@ -40,7 +40,9 @@ struct MatDesc {
   int32_t trace_begin, trace_end;   // slots in the trace-partials array
   int32_t pad0, pad1;
   uint64_t x[3];                    // byte offsets in the workspace: X_0 (kept for the
-                                    // trace), then the iterates alternate in x[1], x[2]
+                                    // trace), then the iterates alternate in x[1], x[2].
+                                    // x[0], x[1], x[2], a, b (quintic tables) follow each
+                                    // other without gaps: k_upd256 keeps x[0] alone
   uint64_t a, b;
   uint64_t xt;                      // buffer holding X_T once the schedule has run
 };

@@ -1,7 +1,7 @@
 // The tile lists that launches run in place of the plan's own (Launch::run_*),
 // checked on the plan built for one weight set: every 128-tile of the update
 // list is covered once by the 256-tiles that run, each of its trace slots is
-// the one the run tile's slot and stride name, and entries stay on one XCD's
+// the one that the run tile's slot and Pp / 128 name, and entries stay on one XCD's
 // queue with padding at its end. Input as for plan_check.cpp (stdin); built
 // by tests/test_run_lists.py.
 #include <cstdio>
@@ -67,7 +67,7 @@ int main() {
           seen[{t.mat, tm, tn}]++;
           auto it = slot_of.find({t.mat, tm, tn});
           if (it == slot_of.end()) fail("no such 128-tile", t.mat, tm, tn);
-          else if (it->second != t.slot + qn * t.parts + qm) fail("slot", it->second, t.slot, t.parts);
+          else if (it->second != t.slot + qn * (d.Pp / kTile) + qm) fail("slot", it->second, t.slot, d.Pp);
         }
     }
     for (const auto &kv : slot_of) {
@@ -75,6 +75,17 @@ int main() {
       if (it == seen.end() || it->second != 1)
         fail("128-tile not covered once", std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first));
     }
+  }
+  // a matrix's buffers follow each other without gaps, at multiples of 256
+  bool quintic = false;
+  for (int t = 0; t < p.iters; ++t) quintic |= p.coeffs[3 * t + 2] != 0.0;
+  for (int i = 0; i < p.n; ++i) {
+    const MatDesc &d = p.mats[i];
+    if (d.empty) continue;
+    const size_t px = size_t(d.Pp) * d.Qp * p.iter_bytes(), pa = size_t(d.Pp) * d.Pp * p.iter_bytes();
+    if (d.x[0] % 256 || (d.x[0] >> 8) >> 32 || d.x[1] != d.x[0] + px || d.x[2] != d.x[1] + px || d.a != d.x[2] + px ||
+        d.b != d.a + (quintic ? pa : 0))
+      fail("buffers", i, d.Pp, d.Qp);
   }
   int run = 0;
   for (const Launch &l : p.launches) {

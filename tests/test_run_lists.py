@@ -49,6 +49,11 @@ def test_run_lists(checker, name, dtype):
 def test_run_lists_edges(checker):
     assert run(checker, [(512, 2048)] * 32, F32)["run256"] == "6"       # 512 256-tiles: the smallest such set
     assert run(checker, [(512, 2048)] * 31, F32)["run256"] == "0"
+    # dims that are no multiples of 256: edge tiles, while they waste at most a quarter
+    for dt in (F32, BF16):
+        assert run(checker, [(640, 3456)] * 32, dt)["run256"] == "6"    # 3 x 14 tiles for 2.5 x 13.5
+        assert run(checker, [(384, 3200)] * 64, dt)["run256"] == "0"    # 2 x 13 for 1.5 x 12.5
+        assert run(checker, [(3456, 1280), (1280, 1280)] * 8, dt)["run256"] == "6"
     run(checker, [(1, 300), (7, 13), (130, 257), (0, 5)], F32)
     cubic = [1.5, -0.5, 0.0] * 6
     assert run(checker, [(512, 2048)] * 32, F32, coeffs=cubic)["run256"] == "0"
