@@ -121,7 +121,12 @@ void build_plan(Plan &p) {
     if (!std::isfinite(c)) throw std::invalid_argument("non-finite coefficient");
 
   const bool f16 = p.dtype == SLORR_BF16;
-  p.split = p.dtype == SLORR_F32 && split_fits(p.coeffs, p.iters);
+  // Gradients rounded to bf16 keep the fp32 MFMA kernels: both forms are off
+  // by the same 1.7e-3 there (bf16's own rounding), but their fp32 gradients
+  // differ by 5e-6, which moves 1 gradient in 700 to the next bf16 number
+  // (2e-4 of the gradient, 40 times the forms' difference), and such sets'
+  // results stay bit for bit.
+  p.split = p.dtype == SLORR_F32 && p.grad_dtype == SLORR_F32 && split_fits(p.coeffs, p.iters);
   const bool scaled = f16 || p.split;      // 16-bit MFMA operands
   const float sx = scaled ? kScaleX16 : 1.0f, sa = scaled ? kScaleA16 : 1.0f, sb = scaled ? kScaleB16 : 1.0f;
   bool any_quintic = false;

@@ -33,6 +33,8 @@ int main() {
     std::cin >> s.rows >> s.cols;
     p.shapes.push_back(s);
   }
+  int grad_dtype;
+  if (std::cin >> grad_dtype) p.grad_dtype = grad_dtype;     // optional; fp32 otherwise
   p.mats.resize(size_t(n));
   build_plan(p);
   int bad = 0;

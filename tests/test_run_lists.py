@@ -29,11 +29,11 @@ def checker(tmp_path_factory):
     return exe
 
 
-def run(checker, shapes, dtype, iters=6, coeffs=None):
+def run(checker, shapes, dtype, iters=6, coeffs=None, grad=F32):
     head = f"{dtype} 0 {iters} 0 {1 if coeffs is not None else 0}\n"
     if coeffs is not None:
         head += " ".join(repr(float(c)) for c in coeffs) + "\n"
-    body = f"{len(shapes)}\n" + "".join(f"{r} {c}\n" for r, c in shapes)
+    body = f"{len(shapes)}\n" + "".join(f"{r} {c}\n" for r, c in shapes) + f"{grad}\n"
     r = subprocess.run([checker], input=head + body, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.startswith("OK"), r.stdout[-4000:] + r.stderr[-2000:]
     return dict(kv.split("=") for kv in r.stdout.split()[1:])
@@ -74,3 +74,9 @@ def test_run_lists_edges(checker):
 def test_split_rule(checker, coeffs, split):
     assert run(checker, [(64, 96)], F32, iters=len(coeffs) // 3, coeffs=coeffs)["split"] == str(split)
     assert run(checker, [(64, 96)], BF16, iters=len(coeffs) // 3, coeffs=coeffs)["split"] == "0"
+
+
+def test_split_needs_fp32_gradients(checker):
+    """bf16 gradients of fp32 weights stay on fp32 MFMA, on 128-tiles."""
+    got = run(checker, [(512, 2048)] * 32, F32, grad=BF16)
+    assert got["split"] == "0" and got["run256"] == "0"
