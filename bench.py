@@ -36,7 +36,7 @@ def kernel_instance(op, edge):
     kernel k_upd256)."""
     if op in ("update", "last") and edge == 256:
         return f"k_upd256<{op}>"
-    return f"k_gemm<{op}, {edge}x{edge}>"
+    return f"k_tile<{op}, {edge}x{edge}>"
 
 
 def _alg_bytes_per_launch(shapes, dtype, op):

@@ -1,16 +1,12 @@
-// MFMA GEMM core of the Polar Express step (device code, included by
-// kernels.hip). One launch covers every matrix of the set: each block takes
-// one output tile from the launch's tile list.
+// GEMM core of the Polar Express step (device code, included by kernels.hip).
+// One launch covers every matrix of the set: each block takes one output tile
+// from the launch's tile list.
 //
 //   Gram    A  = X X^T                 NT: both operands are rows of X (k = Q)
 //   Poly    B  = b A + c A A^T + a I   NT on the symmetric A (A A^T = A A); the
 //                                      a X term of the step is folded into B
 //   Update  X' = B X                   B symmetric (rows of B = columns of B);
-//                                      X is read as [k][n]: fp16 stages keep
-//                                      that layout in LDS and transpose on the
-//                                      LDS read (ds_read_b64_tr_b16); fp32 is
-//                                      transposed into the K-major layout on
-//                                      the way in.
+//                                      X is read as [k][n].
 //                                      Cubic steps (no Poly) use X' = a X + b A X
 //                                      with the a X term in the epilogue.
 //   Last    X_T = B X, stored like an update, with the per-tile partial
@@ -25,34 +21,27 @@
 // Gram and Poly outputs are symmetric: only tiles with tm <= tn are computed
 // and off-diagonal tiles are also stored transposed (mirror).
 //
-// LDS layout: each operand row of a k-slab is 128 bytes (64 fp16 or 32 fp32
-// values of consecutive k) split into eight 16-byte chunks stored at chunk
-// index (c ^ (row & 7)). A wave's 16-byte fragment reads touch 8 consecutive
-// rows per 8-lane phase, which then land in 8 distinct bank groups; the
-// stores of the NK loader (8 lanes per row) and of the transposing KN loader
-// (16 lanes per row, 8-byte pieces) are conflict-free too.
+// This file holds what the kernels share and k_gemm, the products on fp32
+// MFMA: fp32 sets outside the split form's range, and those whose gradients
+// are bf16. gemm_pipe.hpp has the products on 16-bit operands.
 //
-// Pipeline: two LDS stages, one barrier per k-slab. The K-major operands and
-// the fp16 [k][n] operand go global -> LDS directly (no registers); the fp32
-// [k][n] operand is loaded into registers and stored transposed. The loads of
-// slab k + 1 are in flight while the MFMAs of slab k run.
+// k_gemm's LDS layout: each operand row of a k-slab is 128 bytes (32 values
+// of consecutive k) split into eight 16-byte chunks stored at chunk index
+// c ^ key(row). A wave's 16-byte fragment reads touch 8 consecutive
+// rows per 8-lane phase, which then land in 8 distinct bank groups; the
+// stores of the transposing loader (16 lanes per row) are conflict-free too.
+// Two LDS stages, one barrier per k-slab: the K-major operands go
+// global -> LDS directly, the [k][n] operand is loaded into registers and
+// stored transposed; the loads of slab k + 1 are in flight while the MFMAs of
+// slab k run.
 // Included inside namespace slorr, after the helpers of kernels.hip.
 #pragma once
 
-// MFMA per operand type. A lane feeds 16 bytes of one row of each operand
-// (8 fp16 or 4 fp32 consecutive k); lanes 0-31 and 32-63 take the two halves
-// of a 16 (fp16) / 8 (fp32) wide k step. Both operands use the same lane -> k
-// map, so the instruction's internal k order does not matter for the sum.
-template <typename T> struct Mfma;
-template <> struct Mfma<_Float16> {
-  typedef half8 frag;
-  static constexpr int V = 8;
-  __device__ static __forceinline__ void mma(floatx16 &c, const frag &a, const frag &b) {
-    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-  }
-};
-// fp32 operands: fp32 sets with a table outside the split form's range.
-template <> struct Mfma<float> {
+// fp32 MFMA. A lane feeds 16 bytes of one row of each operand (4 consecutive
+// k); lanes 0-31 and 32-63 take the two halves of an 8 wide k step. Both
+// operands use the same lane -> k map, so the instruction's internal k order
+// does not matter for the sum.
+struct Mfma {
   typedef float4v frag;
   static constexpr int V = 4;
   __device__ static __forceinline__ void mma(floatx16 &c, const frag &a, const frag &b) {
@@ -93,8 +82,7 @@ struct GemmShape {
   static constexpr int kStage = (BM + BN) * 128;         // bytes per LDS stage
   static constexpr int kEpiPitch = WTN + 4;              // floats per staged row
   static constexpr int kEpiWave = 32 * kEpiPitch * 4;    // staged bytes per wave
-  static constexpr int kEpiHalf = 32 * WTN * 2;          // per wave: the fp16 block a mirror transposes
-  static constexpr int kEpiAll = kWaves * (kEpiWave + kEpiHalf);
+  static constexpr int kEpiAll = kWaves * kEpiWave;
   static constexpr int kSmem = (2 * kStage > kEpiAll) ? 2 * kStage : kEpiAll;
 };
 
@@ -180,15 +168,8 @@ __device__ __forceinline__ void lds_dma_wait() {
 #endif
 }
 
-// 8 consecutive iterate values (fp16 or fp32) as loaded, for a load issued
-// ahead of its use.
-template <typename T> struct XChunk;
-template <> struct XChunk<_Float16> {
-  half8 h;
-  __device__ __forceinline__ void load(const _Float16 *p) { h = *reinterpret_cast<const half8 *>(p); }
-  __device__ __forceinline__ float get(int j) const { return float(h[j]); }
-};
-template <> struct XChunk<float> {
+// 8 consecutive iterate values as loaded, for a load issued ahead of its use.
+struct XChunk {
   float4v a, b;
   __device__ __forceinline__ void load(const float *p) {
     a = reinterpret_cast<const float4v *>(p)[0];
@@ -197,44 +178,29 @@ template <> struct XChunk<float> {
   __device__ __forceinline__ float get(int j) const { return j < 4 ? a[j] : b[j - 4]; }
 };
 
-// 8 consecutive values of type T from global memory (16-byte aligned).
-template <typename T>
-__device__ __forceinline__ void load8(const T *p, float (&v)[8]) {
-  if constexpr (sizeof(T) == 2) {
-    const half8 h = *reinterpret_cast<const half8 *>(p);
+// 8 consecutive values from global memory (16-byte aligned).
+__device__ __forceinline__ void load8(const float *p, float (&v)[8]) {
+  const float4v a = reinterpret_cast<const float4v *>(p)[0];
+  const float4v b = reinterpret_cast<const float4v *>(p)[1];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = float(h[j]);
-  } else {
-    const float4v a = reinterpret_cast<const float4v *>(p)[0];
-    const float4v b = reinterpret_cast<const float4v *>(p)[1];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      v[j] = a[j];
-      v[4 + j] = b[j];
-    }
+  for (int j = 0; j < 4; ++j) {
+    v[j] = a[j];
+    v[4 + j] = b[j];
   }
 }
 
 // As store8, marked non-temporal: the iterate written by an update is read
 // only by the next launch, so its lines are not kept in this launch's L2,
 // where they would evict operand panels that other tiles still read.
-template <typename T>
-__device__ __forceinline__ void store8_stream(T *p, const float (&v)[8]) {
-  if constexpr (sizeof(T) == 2) {
-    half8 h;
+__device__ __forceinline__ void store8_stream(float *p, const float (&v)[8]) {
+  float4v a, b;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) h[j] = _Float16(v[j]);
-    __builtin_nontemporal_store(h, reinterpret_cast<half8 *>(p));
-  } else {
-    float4v a, b;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      a[j] = v[j];
-      b[j] = v[4 + j];
-    }
-    __builtin_nontemporal_store(a, reinterpret_cast<float4v *>(p));
-    __builtin_nontemporal_store(b, reinterpret_cast<float4v *>(p) + 1);
+  for (int j = 0; j < 4; ++j) {
+    a[j] = v[j];
+    b[j] = v[4 + j];
   }
+  __builtin_nontemporal_store(a, reinterpret_cast<float4v *>(p));
+  __builtin_nontemporal_store(b, reinterpret_cast<float4v *>(p) + 1);
 }
 
 template <typename T>
@@ -288,14 +254,6 @@ __device__ __forceinline__ void store_h8_range(_Float16 *p, const half8 &h, int 
     if (j >= lo && j < hi) p[j] = h[j];
 }
 
-// The value the iterate buffer holds for an fp32 result v (the rounding of
-// the store), as a float.
-template <typename T>
-__device__ __forceinline__ float as_stored(float v) {
-  if constexpr (sizeof(T) == 2) return float(_Float16(v));
-  return v;
-}
-
 // The trace's partial over 8 consecutive columns of one row of an fp16 tile:
 // sum of P (as stored) times X_0', four v_dot2_f32_f16 in column order with
 // an fp32 running sum (each pair's products are formed exactly). The callers
@@ -308,23 +266,20 @@ __device__ __forceinline__ float trace8(const half8 &p, const half8 &x0) {
   return f;
 }
 
-template <typename T, typename Tw, int MODE, int BM, int BN, int WGM, int WGN>
+template <int MODE, int BM, int BN, int WGM, int WGN>
 __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(GemmArgs args) {
   using S = GemmShape<BM, BN, WGM, WGN>;
+  typedef float T;
   constexpr int NT = S::kThreads;
-  constexpr int V = Mfma<T>::V;
+  constexpr int V = Mfma::V;
   constexpr int BK = 8 * V;                      // k per slab (128-byte rows)
   constexpr int FM = S::FM, FN = S::FN, WTM = S::WTM, WTN = S::WTN;
   constexpr bool KN = (MODE == kUpdate || MODE == kLast);
-  // fp16 [k][n] operand: global -> LDS directly in its own layout, transposed
-  // on the LDS read; fp32 goes through registers and is stored transposed
-  constexpr bool TR = KN && sizeof(T) == 2;
-  constexpr int KNP = BN * int(sizeof(T));       // bytes per k-row of a [k][n] stage
   constexpr int QB = (BK / 4) * (BN / V) / NT;   // 4 x V blocks per thread, B slab (KN)
   static_assert(BM % (8 * S::kWaves) == 0 && BN % (8 * S::kWaves) == 0, "tile / wave mismatch");
   static_assert(!KN || QB * NT == (BK / 4) * (BN / V), "KN loader mismatch");
   static_assert(FM >= 1 && FN >= 1 && WTM % 32 == 0 && WTN % 32 == 0, "wave tile");
-  typedef typename Mfma<T>::frag frag;
+  typedef Mfma::frag frag;
   typedef T quad_t __attribute__((ext_vector_type(4)));
   __shared__ __attribute__((aligned(16))) char smem[S::kSmem];
 
@@ -396,21 +351,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(GemmArgs args) {
         buffer_load_lds16(ra, voff, (uint32_t(k0) + uint32_t(i) * kRowStep * uint32_t(lda)) * sizeof(T),
                           sA + (wave + i * kFW) * 8 * 128);
     }
-    if constexpr (TR) {
-      // one wave instruction fills 1024 / KNP consecutive k-rows; lane l lands
-      // at physical chunk l % (KNP / 16) of its row and fetches the logical
-      // chunk that kn_off puts there
-      constexpr int CPR = KNP / 16, RPI = 1024 / KNP;
-      static_assert((RPI * S::kWaves) % 4 == 0, "kn_off key period");
-      const int xsub = lane / CPR, xch = lane % CPR;
-      const i32x4 rb = buffer_rsrc(Bbase, bbytes);
-      const int row = wave * RPI + xsub;
-      const uint32_t voff = (uint32_t(row) * uint32_t(ldb) + uint32_t(n0 + (xch ^ ((row & 3) << 2)) * V)) * sizeof(T);
-#pragma unroll
-      for (int i = 0; i < BK / RPI / S::kWaves; ++i)
-        buffer_load_lds16(rb, voff, (uint32_t(k0) + uint32_t(i * RPI * S::kWaves)) * uint32_t(ldb) * sizeof(T),
-                          sB + (wave + i * S::kWaves) * RPI * KNP);
-    }
     if constexpr (!KN) {
       if (diag) return;                 // both operands are the same rows: one copy
       const i32x4 rb = buffer_rsrc(Bbase, bbytes);
@@ -423,9 +363,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(GemmArgs args) {
     }
   };
   // the transposing loader of the [k][n] operand (update) into registers
-  frag rk[KN && !TR ? 4 * QB : 1];
+  frag rk[KN ? 4 * QB : 1];
   auto kload = [&](int k0) {
-    if constexpr (KN && !TR) {
+    if constexpr (KN) {
 #pragma unroll
       for (int i = 0; i < QB; ++i) {
         const int q = tid + i * NT, kq = q % (BK / 4), nc = q / (BK / 4);
@@ -436,7 +376,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(GemmArgs args) {
     }
   };
   auto kstore = [&](int buf) {
-    if constexpr (KN && !TR) {
+    if constexpr (KN) {
       char *sB = smem + buf * S::kStage + BM * 128;
 #pragma unroll
       for (int i = 0; i < QB; ++i) {
@@ -464,13 +404,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(GemmArgs args) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-  // fp16 Gram: the MFMA operands are swapped (the B-operand fragment first),
-  // so that each lane's accumulator holds 4 consecutive output columns of one
-  // row: acc[i][j][4 g + q] = C[row lr of 32-row block i][column
-  // 32 j + 8 g + 4 lk + q] of the wave tile, as in the persistent update
-  // kernel. (The poly product measured slower this way: its b A term then
-  // needs twice as many, 8-byte, loads of A.)
-  constexpr bool kSwap = sizeof(T) == 2 && MODE == kGram && WTN == 64;
   // fragments of k-step s + 1 are read from LDS while the MFMAs of k-step s run
   auto compute = [&](int buf) {
     const char *sA = smem + buf * S::kStage;
@@ -482,19 +415,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(GemmArgs args) {
         fa[slot][i] = *reinterpret_cast<const frag *>(sA + swz(wm * WTM + i * 32 + lr, 2 * s + lk));
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
-        if constexpr (TR) {
-          // lane L: k = 16 s + 8 (L / 32) + 0..7 of column n = L % 32 of the
-          // fragment, as two transposing reads of 4 k-rows each
-          const int g = lane >> 4, si = lane & 15;
-          const int row = 16 * s + 8 * (g >> 1) + (si >> 2);
-          const int col = wn * WTN + j * 32 + 16 * (g & 1) + 4 * (si & 3);
-          const int off = kn_off(row, col >> 3, KNP) + 8 * (si & 1);
-          const half4 lo = lds_read_tr16(sB + off);
-          const half4 hi = lds_read_tr16(sB + off + 4 * KNP);
-          fb[slot][j] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        } else {
-          fb[slot][j] = *reinterpret_cast<const frag *>(sB + swz(wn * WTN + j * 32 + lr, 2 * s + lk));
-        }
+        fb[slot][j] = *reinterpret_cast<const frag *>(sB + swz(wn * WTN + j * 32 + lr, 2 * s + lk));
       }
     };
     read(0, 0);
@@ -504,12 +425,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(GemmArgs args) {
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          if constexpr (kSwap)
-            Mfma<T>::mma(acc[i][j], fb[s & 1][j], fa[s & 1][i]);
-          else
-            Mfma<T>::mma(acc[i][j], fa[s & 1][i], fb[s & 1][j]);
-        }
+        for (int j = 0; j < FN; ++j) Mfma::mma(acc[i][j], fa[s & 1][i], fb[s & 1][j]);
     }
   };
 
@@ -543,9 +459,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(GemmArgs args) {
   constexpr int P = S::kEpiPitch;
   constexpr int CG = WTN / 8;                     // 8-column groups per staged row
   float *ep = reinterpret_cast<float *>(smem + wave * S::kEpiWave);
-  // fp16 sets: the mirror's block in fp16, transposed by ds_read_b64_tr_b16
-  constexpr bool kHalfMirror = sizeof(T) == 2 && WTN == 64;
-  char *eh = smem + S::kWaves * S::kEpiWave + wave * S::kEpiHalf;
   // per-matrix coefficients of the first step (kappa = 2^e / (f + eps))
   float alpha = args.alpha, beta = args.beta, gamma = args.gamma;
   if (args.kap) {
@@ -569,82 +482,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(GemmArgs args) {
   const bool dtile = mirror && tile.tm == tile.tn;
   double tsum = 0.0;
 
-  if constexpr (kSwap) {
-    // Per 32-row block: the results (scaled, rounded to fp16 once) go to the
-    // wave's fp16 block with 8-byte writes; 16-byte reads give
-    // 8 consecutive columns for the stores, 8 rows of 128 bytes per
-    // instruction; the mirror transposes the same block with transposing
-    // reads. Gram parts store their fp32 partial straight from the
-    // accumulators.
-    constexpr int NT16 = 32 * 8 / 64;               // 16-byte pieces per lane and block
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int grow0 = m0 + wm * WTM + i * 32, gcol0 = n0 + wn * WTN;
-      if (part) {
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            float4v f;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) f[q] = acc[i][j][4 * g + q];
-            *reinterpret_cast<float4v *>(args.gpart + size_t(tile.slot) * (BM * BN) +
-                                         size_t(grow0 - m0 + lr) * BN + (gcol0 - n0) + 32 * j + 8 * g + 4 * lk) = f;
-          }
-        continue;
-      }
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          half4 h;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) h[q] = _Float16(acc[i][j][4 * g + q] * alpha);
-          *reinterpret_cast<half4 *>(eh + mir_off(lr, 4 * j + g) + 8 * lk) = h;
-        }
-      // the block is the wave's own and one wave's LDS operations are
-      // performed in order: a wave-level barrier (no reordering) suffices
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int t = 0; t < NT16; ++t) {
-        const int task = lane + 64 * t, row = task >> 3, cg = task & 7;
-        const half8 h = *reinterpret_cast<const half8 *>(eh + mir_off(row, cg));
-        const int grow = grow0 + row, gcol = gcol0 + 8 * cg;
-        store_h8_range(reinterpret_cast<_Float16 *>(Sym) + size_t(grow) * d.Pp + gcol, h, dtile ? grow - gcol : 0, 8);
-      }
-      if (mirror) {
-        // transpose: each 16-lane group takes 16 columns x 8 rows; two
-        // transposing reads (rows 0-3, 4-7 of the group) leave lane s with
-        // column 16 cb + s, rows 8 rg .. 8 rg + 7: one 16-byte row piece of
-        // the mirror tile
-#pragma unroll
-        for (int t = 0; t < NT16; ++t) {
-          const int q = (lane >> 4) + 4 * t, rg = q & 3, cb = q >> 2, si = lane & 15;
-          const int col = 16 * cb + 4 * (si & 3);          // this lane's 4-column piece
-          const int r = 8 * rg + (si >> 2);
-          const int off = (col & 7) * 2;                   // byte within the 16-byte chunk
-          const half4 lo = lds_read_tr16(eh + mir_off(r, col >> 3) + off);
-          const half4 hi4 = lds_read_tr16(eh + mir_off(r + 4, col >> 3) + off);
-          const half8 h = __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
-          const int orow = gcol0 + 16 * cb + si, ocol = grow0 + 8 * rg;
-          const int hi = dtile ? orow - ocol : 8;         // strictly below the diagonal
-          store_h8_range(reinterpret_cast<_Float16 *>(Sym) + size_t(orow) * d.Pp + ocol, h, 0, hi);
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
-    return;
-  }
-
-  // Poly: the A values of the b A term; Last: the X_0' values of the trace.
-  // Loaded one 32-row block ahead (two register buffers). Task t of a lane:
+  // Poly: the A values of the b A term, loaded one 32-row block ahead (two register buffers). Task t of a lane:
   // row task / CG, 8 columns from (task % CG) 8 of the staged block.
   constexpr int NTASK = 32 * CG / 64;
   static_assert(NTASK * 64 == 32 * CG, "epilogue task split");
-  // fp32 iterate in the last step: no prefetch (registers), X_0' is loaded
-  // where it is used
-  constexpr bool APRE = MODE == kPoly || (MODE == kLast && sizeof(T) == 2);
-  XChunk<T> apre[APRE ? 2 : 1][NTASK];
+  // (the last step's X_0' is loaded where it is used: registers)
+  constexpr bool APRE = MODE == kPoly;
+  XChunk apre[APRE ? 2 : 1][NTASK];
   const T *asrc = MODE == kLast ? reinterpret_cast<const T *>(args.ws + d.x[0]) : Am;
   const int apitch = MODE == kLast ? d.Qp : d.Pp;
   auto aprefetch = [&](int i, int b) {
@@ -710,59 +554,25 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(GemmArgs args) {
         }
         if (MODE == kUpdate || args.write_x) store8_stream(Xn + size_t(grow) * d.Qp + gcol, v);
         if (MODE == kLast) {
-          // P as stored times X_0' (both in the iterate's scale); fp32 sets:
-          // each product exact in fp64
-          if constexpr (MODE == kLast && sizeof(T) == 2) {
-            half8 ph;
+          // P as stored times X_0' (both in the iterate's scale): each product
+          // exact in fp64
 #pragma unroll
-            for (int j = 0; j < 8; ++j) ph[j] = _Float16(v[j]);
-            tsum += double(trace8(ph, apre[i & 1][t].h));
-          } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-              tsum += double(as_stored<T>(v[j])) * double(float(asrc[size_t(grow) * apitch + gcol + j]));
-          }
+          for (int j = 0; j < 8; ++j) tsum += double(v[j]) * double(asrc[size_t(grow) * apitch + gcol + j]);
         }
       }
       if (mirror) {
-        if constexpr (kHalfMirror) {
-          half8 hv;
+        float4v e0, e1;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) hv[j] = _Float16(v[j]);
-          *reinterpret_cast<half8 *>(eh + mir_off(row, cg)) = hv;
-        } else {
-          float4v e0, e1;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            e0[j] = v[j];
-            e1[j] = v[4 + j];
-          }
-          e[0] = e0;
-          e[1] = e1;
+        for (int j = 0; j < 4; ++j) {
+          e0[j] = v[j];
+          e1[j] = v[4 + j];
         }
+        e[0] = e0;
+        e[1] = e1;
       }
     }
     __builtin_amdgcn_wave_barrier();
-    if (mirror && kHalfMirror) {
-      // transpose: each 16-lane group takes 16 columns x 8 rows; two
-      // transposing reads (rows 0-3, 4-7 of the group) leave lane s with
-      // column 16 cb + s, rows 8 rg .. 8 rg + 7: one 16-byte row piece of
-      // the mirror tile
-#pragma unroll
-      for (int t = 0; t < NTASK; ++t) {
-        const int q = (lane >> 4) + 4 * t, rg = q & 3, cb = q >> 2, si = lane & 15;
-        const int col = 16 * cb + 4 * (si & 3);            // this lane's 4-column piece
-        const int r = 8 * rg + (si >> 2);
-        const int off = (col & 7) * 2;                     // byte within the 16-byte chunk
-        const half4 lo = lds_read_tr16(eh + mir_off(r, col >> 3) + off);
-        const half4 hi4 = lds_read_tr16(eh + mir_off(r + 4, col >> 3) + off);
-        const half8 h = __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
-        const int orow = gcol0 + 16 * cb + si, ocol = grow0 + 8 * rg;
-        const int hi = dtile ? orow - ocol : 8;           // strictly below the diagonal
-        store_h8_range(reinterpret_cast<_Float16 *>(Sym) + size_t(orow) * d.Pp + ocol, h, 0, hi);
-      }
-      __builtin_amdgcn_wave_barrier();
-    } else if (mirror) {
+    if (mirror) {
       // transpose: output row = this tile's column, 8 consecutive source rows
 #pragma unroll
       for (int t = 0; t < NTASK; ++t) {

@@ -8,13 +8,14 @@
 //              padded, in the iterate type; X_0 = W / (f + eps) = kappa X_0'
 //              with kappa applied by the first step's coefficients (Sec. 3
 //              "Computing the polar factor"; App. D remark on normalisation)
-//   k_gemm     the Polar Express step (Sec. 3; App. E.1) as three MFMA GEMMs:
+//   k_tile     the Polar Express step (Sec. 3; App. E.1) as three MFMA GEMMs
+//              (k_gemm where the iterate is fp32):
 //                Gram    A = X X^T
 //                Poly    B = b A + c A A + a I      (A symmetric: A A = A A^T)
 //                                                   (first step: kappa a, kappa^3 b,
 //                                                   kappa^5 c)
-//                Update  X' = B X                   (B symmetric; k_upd256 for
-//                                                   the fp16 iterate on 256-tiles)
+//                Update  X' = B X                   (B symmetric; k_upd256 on
+//                                                   256-tiles)
 //                Last    X_T = B X with the per-tile partials of the trace
 //                        sum(X_0' * P), P = X_T as stored; 2^e times it is
 //                        sum(W * P) (Sec. 3 "Computing the nuclear and
@@ -761,52 +762,45 @@ void launch_upd256(Op op, const GemmArgs &a, hipStream_t s, const EvPair *ev) {
   }
 }
 
-// The products of the split iterate.
-template <int BM, int BN, int WGM, int WGN, int NS>
+// The products on 16-bit MFMA operands, one tile per block.
+template <typename Tx, int BM, int BN, int WGM, int WGN, int NS>
 void launch_tile(Op op, dim3 grid, const GemmArgs &a, hipStream_t s, const EvPair *ev) {
   const dim3 block(64 * WGM * WGN);
   switch (op) {
     case Op::Gram:
-      go(k_tile<Split, kGram, BM, BN, WGM, WGN, NS>, grid, block, s, ev, a);
+      go(k_tile<Tx, kGram, BM, BN, WGM, WGN, NS>, grid, block, s, ev, a);
       break;
     case Op::Poly:
-      go(k_tile<Split, kPoly, BM, BN, WGM, WGN, NS>, grid, block, s, ev, a);
+      go(k_tile<Tx, kPoly, BM, BN, WGM, WGN, NS>, grid, block, s, ev, a);
       break;
     case Op::Update:
     default:
       if constexpr (BM == kTile) {
-        if (op == Op::Update) go(k_tile<Split, kUpdate, BM, BN, WGM, WGN, NS>, grid, block, s, ev, a);
-        else go(k_tile<Split, kLast, BM, BN, WGM, WGN, NS>, grid, block, s, ev, a);
+        if (op == Op::Update) go(k_tile<Tx, kUpdate, BM, BN, WGM, WGN, NS>, grid, block, s, ev, a);
+        else go(k_tile<Tx, kLast, BM, BN, WGM, WGN, NS>, grid, block, s, ev, a);
       } else {
-        launch_upd256<Split>(op, a, s, ev);
+        launch_upd256<Tx>(op, a, s, ev);
       }
       break;
   }
 }
 
-template <typename Tx, typename Tw, int BM, int BN, int WGM, int WGN>
+// The products on fp32 MFMA.
+template <int BM, int BN, int WGM, int WGN>
 void launch_gemm(Op op, dim3 grid, const GemmArgs &a, hipStream_t s, const EvPair *ev) {
   const dim3 block(GemmShape<BM, BN, WGM, WGN>::kThreads);
-  // the planner gives fp32 sets 128-tiles for the update launches
-  constexpr bool kUpd = sizeof(Tx) == 2 || BM == kTile;
-  // fp16 iterate, 256-tiles: the persistent update kernel
-  constexpr bool kPersist = sizeof(Tx) == 2 && BM == kBigTile && BN == kBigTile;
   switch (op) {
     case Op::Gram:
-      go(k_gemm<Tx, Tw, kGram, BM, BN, WGM, WGN>, grid, block, s, ev, a);
+      go(k_gemm<kGram, BM, BN, WGM, WGN>, grid, block, s, ev, a);
       break;
     case Op::Poly:
-      go(k_gemm<Tx, Tw, kPoly, BM, BN, WGM, WGN>, grid, block, s, ev, a);
-      break;
-    case Op::Update:
-      if constexpr (kPersist) launch_upd256<Tx>(op, a, s, ev);
-      else if constexpr (kUpd) go(k_gemm<Tx, Tw, kUpdate, BM, BN, WGM, WGN>, grid, block, s, ev, a);
-      else throw HipError("no fp32 256-tile update kernel");
+      go(k_gemm<kPoly, BM, BN, WGM, WGN>, grid, block, s, ev, a);
       break;
     default:
-      if constexpr (kPersist) launch_upd256<Tx>(op, a, s, ev);
-      else if constexpr (kUpd) go(k_gemm<Tx, Tw, kLast, BM, BN, WGM, WGN>, grid, block, s, ev, a);
-      else throw HipError("no fp32 256-tile update kernel");
+      // the planner gives these sets 128-tiles for the update launches
+      if constexpr (BM != kTile) throw HipError("no fp32 256-tile update kernel");
+      else if (op == Op::Update) go(k_gemm<kUpdate, BM, BN, WGM, WGN>, grid, block, s, ev, a);
+      else go(k_gemm<kLast, BM, BN, WGM, WGN>, grid, block, s, ev, a);
       break;
   }
 }
@@ -877,15 +871,15 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
         a.quads = l.run_cfg != l.cfg;
         a.ntiles = l.run_grid;
         const dim3 g(l.run_grid);
-        if constexpr (std::is_same<Tx, Split>::value) {
-          // at most one block per CU: 4 stages (see k_tile)
-          if (l.run_cfg == kCfg256) launch_tile<kBigTile, kBigTile, 2, 4, 2>(l.op, g, a, s, ev);
-          else if (l.run_grid <= kCus) launch_tile<kTile, kTile, 2, 2, 4>(l.op, g, a, s, ev);
-          else launch_tile<kTile, kTile, 2, 2, 2>(l.op, g, a, s, ev);
+        if constexpr (std::is_same<Tx, float>::value) {
+          if (l.run_cfg == kCfg256) launch_gemm<kBigTile, kBigTile, 2, 4>(l.op, g, a, s, ev);
+          else launch_gemm<kTile, kTile, 2, 2>(l.op, g, a, s, ev);
         } else if (l.run_cfg == kCfg256) {
-          launch_gemm<Tx, Tw, kBigTile, kBigTile, 2, 4>(l.op, g, a, s, ev);
+          launch_tile<Tx, kBigTile, kBigTile, 2, 4, 2>(l.op, g, a, s, ev);
+        } else if (l.run_grid <= kCus) {           // at most one block per CU: 4 stages (see k_tile)
+          launch_tile<Tx, kTile, kTile, 2, 2, 4>(l.op, g, a, s, ev);
         } else {
-          launch_gemm<Tx, Tw, kTile, kTile, 2, 2>(l.op, g, a, s, ev);
+          launch_tile<Tx, kTile, kTile, 2, 2, 2>(l.op, g, a, s, ev);
         }
         break;
       }
