@@ -196,10 +196,10 @@ __device__ __forceinline__ void compute_slab(floatx16 (&acc)[FM][FN], const char
 // publishes it and frees the stage of the slab before it. Launches of at most
 // one block per CU take 4 stages (128 KB, which leaves one block per CU
 // anyway): their tiles are bound by the latency of the slabs' fetches. Others
-// take 2 stages and two blocks per CU. fp16, a set's call with one block per
-// tile and a wait for all fetches per slab before, this after: 48 matrices of
-// ViT-Ti (144 Gram and poly tiles: 4 stages) 251 -> 226 us, ViT-S 511 -> 493,
-// 24 odd shapes up to 1000 x 4100 663 -> 630.
+// take 2 stages and two blocks per CU. fp16, a set's call with a wait for all
+// fetches right after each slab before, this after: ViT-Ti (48 matrices, 144
+// Gram and poly tiles: 4 stages) 261 -> 242 us, ViT-S 565 -> 545, 24 odd shapes
+// up to 1000 x 4100 707 -> 684.
 template <typename T, int BM, int BN, int WGM, int WGN, int NS, int MODE>
 struct TileShape {
   static constexpr int kWaves = WGM * WGN, kThreads = 64 * kWaves;
