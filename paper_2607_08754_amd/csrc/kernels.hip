@@ -785,6 +785,26 @@ void launch_tile(Op op, dim3 grid, const GemmArgs &a, hipStream_t s, const EvPai
   }
 }
 
+// A symmetric product of the chained steps.
+template <typename Tx>
+void launch_sym(const Plan &p, const Launch &l, GemmArgs a, const Tile *tiles, hipStream_t s, const EvPair *ev) {
+  const int cfg = p.pp[kCfg256].count ? kCfg256 : kCfg128;
+  const TileRange r = p.pp[cfg];
+  a.tiles = tiles + r.first;
+  a.ntiles = r.count;
+  a.alpha = l.sym_alpha;
+  a.kap = 0;
+  EvPair first{};
+  if (ev && l.chain == kSymBefore) {       // the pair spans both kernels
+    first.start = ev->start;
+    ev = &first;
+  }
+  const dim3 grid(r.count);
+  if (cfg == kCfg256) go(k_tile<Tx, kSym, kBigTile, kBigTile, 2, 4, 2>, grid, dim3(512), s, ev, a);
+  else if (r.count <= kCus) go(k_tile<Tx, kSym, kTile, kTile, 2, 2, 4>, grid, dim3(256), s, ev, a);
+  else go(k_tile<Tx, kSym, kTile, kTile, 2, 2, 2>, grid, dim3(256), s, ev, a);
+}
+
 // The products on fp32 MFMA.
 template <int BM, int BN, int WGM, int WGN>
 void launch_gemm(Op op, dim3 grid, const GemmArgs &a, hipStream_t s, const EvPair *ev) {
@@ -851,6 +871,7 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
       case Op::Update:
       case Op::Last: {
         GemmArgs a;
+        EvPair second{};
         a.tiles = tiles + l.run_first;
         a.mats = mats;
         a.dyn = dyn;
@@ -870,6 +891,20 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
         a.gpart = reinterpret_cast<float *>(ws + p.off_gpart);
         a.quads = l.run_cfg != l.cfg;
         a.ntiles = l.run_grid;
+        a.pl = l.pl;
+        a.pr = l.pr;
+        a.po = l.po;
+        if (l.chain) {
+          if constexpr (!std::is_same<Tx, float>::value) launch_sym<Tx>(p, l, a, tiles, s, ev);
+          else throw HipError("no chained steps on fp32 MFMA");
+          if (l.chain == kSymInstead) break;
+          if (ev) {
+            second.stop = ev->stop;
+            ev = &second;
+          }
+          a.xin = 0;                               // X_2 = Z X_0
+          a.use_a = 1;
+        }
         const dim3 g(l.run_grid);
         if constexpr (std::is_same<Tx, float>::value) {
           if (l.run_cfg == kCfg256) launch_gemm<kBigTile, kBigTile, 2, 4>(l.op, g, a, s, ev);
@@ -888,6 +923,13 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
            1.0f / sx);
         break;
       case Op::GramReduce:
+        if (l.chain == kNothing) {                 // the chained Gram product has no parts
+          if (ev) {
+            check(hipEventRecord(ev->start, s), "hipEventRecord");
+            check(hipEventRecord(ev->stop, s), "hipEventRecord");
+          }
+          break;
+        }
         go(k_gram_reduce<Tx>, grid, block, s, ev, tiles + l.tile_first, mats, ws,
            reinterpret_cast<const float *>(ws + p.off_gpart), l.alpha);
         break;

@@ -50,6 +50,18 @@ struct Launch {
   int32_t kap;         // first step: coefficients scaled per matrix by powers of kappa
   int32_t set_sum;     // gradient launch: its first block also writes the set total
   float alpha, beta, gamma;  // epilogue coefficients
+  // what the launch runs where it differs from the above (chained steps 1
+  // and 2, see build_plan)
+  int32_t chain;       // Chain
+  int32_t pl, pr, po;  // PpBuf: Poly's A and B; the symmetric product's operands and output
+  float sym_alpha;     // the symmetric product's factor
+};
+
+enum Chain : int32_t {
+  kNoChain = 0,
+  kSymInstead = 1,     // runs the symmetric product po = sym_alpha pl pr in its place
+  kSymBefore = 2,      // runs it before its own kernel, an update from x[0] with the operand A
+  kNothing = 3         // runs nothing
 };
 
 struct TileRange {
@@ -80,6 +92,7 @@ struct Plan {
   TileRange prep;                      // prep tiles over Pp x Qp
   TileRange upd;                       // the 128-tile update list as 256-tiles (empty: not used)
   TileRange gsplit, gred;              // split-K Gram: part entries, reduce entries
+  bool chained = false;                // steps 1 and 2 run on the Gram matrix
   int32_t gram_parts = 0;              // fp32 partial tiles in the workspace
   int32_t trace_slots = 0;             // one per update tile
   int32_t norm_slots = 0;              // one per canonical 64 x 64 tile

@@ -2,8 +2,10 @@
 // checked on the plan built for one weight set: every 128-tile of the update
 // list is covered once by the 256-tiles that run, each of its trace slots is
 // the one that the run tile's slot and Pp / 128 name, and entries stay on one XCD's
-// queue with padding at its end. Input as for plan_check.cpp (stdin); built
+// queue with padding at its end; and the launches' operands and factors, run in
+// scalar arithmetic, give the table's polynomials. Input as for plan_check.cpp (stdin); built
 // by tests/test_run_lists.py.
+#include <cmath>
 #include <cstdio>
 #include <iostream>
 #include <map>
@@ -101,7 +103,51 @@ int main() {
         fail("update run list", l.cfg, l.run_cfg, l.run_grid);
     }
   }
+  // the schedule on a 1 x 1 matrix x: every launch's buffers and factors in
+  // scalar arithmetic, against the table's polynomials
+  const bool scaled = p.dtype == SLORR_BF16 || p.split;
+  const double sx = scaled ? kScaleX16 : 1.0;
+  for (double x0 : {0.02, 0.3, 0.8}) {
+    if (p.prep.count == 0) break;             // no matrix with elements
+    const double nan = std::nan(""), kappa = 1.25;
+    double x[3] = {sx * x0, nan, nan}, pp[3] = {nan, nan, nan}, part = nan;
+    double &scratch = pp[kPpX1];              // the same memory as x[1]
+    auto symmetric = [&](const Launch &l) { pp[l.po] = double(l.sym_alpha) * pp[l.pl] * pp[l.pr]; };
+    for (const Launch &l : p.launches) {
+      const double k = l.kap ? kappa : 1.0;
+      if (l.chain && !p.chained) fail("chain flag", l.chain, int(l.op), 0);
+      if (l.chain == kSymInstead) {
+        symmetric(l);
+        x[1] = nan;
+      } else if (l.op == Op::Gram) {
+        (p.gsplit.count ? part : pp[kPpA]) = (p.gsplit.count ? 1.0 : double(l.alpha)) * x[l.xin] * x[l.xin];
+      } else if (l.op == Op::GramReduce && l.chain != kNothing) {
+        pp[kPpA] = l.alpha * part;
+      } else if (l.op == Op::Poly) {
+        const double A = pp[l.pl], k2 = k * k;
+        pp[l.po] = l.beta * k2 * k * A + l.alpha * k2 * k2 * k * A * A + l.gamma * k;
+        if (l.po == kPpX1) x[1] = nan;
+      } else if (l.op == Op::Update || l.op == Op::Last) {
+        int xin = l.xin, use_a = l.use_a;
+        if (l.chain == kSymBefore) {
+          symmetric(l);
+          xin = 0;
+          use_a = 1;
+        }
+        const double v = double(l.alpha) * (use_a ? pp[kPpA] : pp[kPpB]) * x[xin];
+        x[l.xout] = l.fold ? v : l.beta * k * x[xin] + v * k * k * k;
+        if (l.xout == 1) scratch = nan;
+      }
+    }
+    double want = kappa * x0;
+    for (int t = 0; t < iters; ++t) {
+      const double z = want * want;
+      want *= p.coeffs[3 * t] + z * (p.coeffs[3 * t + 1] + z * p.coeffs[3 * t + 2]);
+    }
+    const double got = x[iters == 0 ? 0 : 1 + ((iters - 1) & 1)] / sx;
+    if (!(std::fabs(got - want) <= 1e-4 * std::fabs(want) + 1e-6)) fail("schedule's value", int(1e6 * got), int(1e6 * want), int(100 * x0));
+  }
   if (bad) return 1;
-  std::printf("OK split=%d run256=%d\n", p.split ? 1 : 0, run);
+  std::printf("OK split=%d run256=%d chained=%d\n", p.split ? 1 : 0, run, p.chained ? 1 : 0);
   return 0;
 }
