@@ -4,6 +4,7 @@
 //
 //   k_tile    one output tile per block, NS LDS stages (Gram, poly, products of
 //             two symmetric matrices; update on 128-tiles)
+//   k_short   a whole step of a set of short matrices
 //   k_upd256  the persistent 256 x 256 update kernel
 //
 // Storage forms
@@ -529,6 +530,262 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_tile(GemmArgs args) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Sets of short matrices (P <= 128, Q <= kMaxShortSlices slices of 128
+// columns): one launch per step.
+//
+// Their products have one tile of rows, so that a launch per product holds a
+// few blocks that start, wait for a tile's fetches and end: 25 launches for 4
+// matrices of 128 x 256. Here a block owns one slice of 128 columns of X for a
+// whole step, all of it in LDS: it adds the matrix's Gram partials (one per
+// slice, from the launch before) to A, forms B (every block of the matrix does:
+// 2 P^3, less than a launch), multiplies its slice, stores it in place and
+// forms the slice's Gram partial for the next launch. The first launch forms
+// X_0's partials.
+//
+// Blocks of 8 waves of 32 x 64. LDS: A, then B (rows of B, K-major slabs), and
+// the slice, first as [k][n] rows (the update's operand), then as K-major rows
+// (the Gram product's): 128 KB in split form, 64 KB in fp16.
+// Partials are added in slice order. 4 matrices of 128 x 256, fp32, T = 5: 182
+// -> 98 us a call; bf16, T = 6: 145 -> 74.
+struct ShortArgs {
+  GemmArgs g;                   // alpha, beta, gamma: poly's; xin, xout: the slice's buffers
+  const float *pin;             // Gram partials read, 128 x 128 at each trace slot
+  float *pout;                  // and written
+  float gram_alpha, upd_alpha;
+};
+enum ShortStep { kShortFirst = 0, kShortStep = 1, kShortLast = 2 };
+
+template <typename T, int STEP>
+__global__ __launch_bounds__(512) void k_short(ShortArgs s) {
+  constexpr int PL = Iter<T>::kPlanes, BK = Iter<T>::kBK, NSLAB = kTile / BK;
+  constexpr int V = 16 / int(sizeof(T)), NT = 512, FN = 2;
+  constexpr uint32_t ES = sizeof(T);
+  constexpr int KNP = kTile * int(sizeof(T));        // bytes per k-row of the slice
+  constexpr int kSlab = kTile * 128;                 // bytes per slab, either layout
+  constexpr int kMat = NSLAB * kSlab;
+  static_assert(BK * KNP == kSlab, "slab sizes");
+  __shared__ __attribute__((aligned(16))) char smem[2 * kMat + kTile * 4 + 64];
+  char *sA = smem, *sX = smem + kMat;
+  float *dsum = reinterpret_cast<float *>(smem + 2 * kMat);
+
+  const Tile tile = s.g.tiles[blockIdx.x];
+  if (tile.mat < 0) return;      // padding of the XCD-ordered list (whole block)
+  const MatDesc d = s.g.mats[tile.mat];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lk = lane >> 5;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int n0 = tile.tn * kTile;
+  const char *Xc = s.g.ws + s.g.mats[tile.mat].x[s.g.xin];
+  char *Xn = s.g.ws + s.g.mats[tile.mat].x[s.g.xout];
+
+  // the slice, global -> LDS: 1 KB per wave instruction, kMat / 1024 in all
+  {
+    const i32x4 rs = buffer_rsrc(Xc, uint32_t(kTile) * uint32_t(d.Qp) * ES);
+    const uint32_t lds0 = lds_offset(smem) + kMat;
+#pragma unroll
+    for (int i = 0; i < kMat / 1024 / 8; ++i) {
+      const int q = wave + 8 * i;                    // 1 KB piece
+      uint32_t voff;
+      if constexpr (STEP == kShortFirst) {           // K-major: 8 rows of a slab
+        const int slab = q / (kTile / 8), row = (q % (kTile / 8)) * 8 + (lane >> 3);
+        voff = (uint32_t(row) * uint32_t(d.Qp) + uint32_t(n0 + slab * BK + ((lane & 7) ^ swz_key(row)) * V)) * ES;
+      } else {                                       // [k][n]: 1024 / KNP k-rows
+        constexpr int CPR = KNP / 16;
+        const int row = q * (1024 / KNP) + lane / CPR;
+        voff = (uint32_t(row) * uint32_t(d.Qp) + uint32_t(n0 + ((lane % CPR) ^ ((row & 3) << 2)) * V)) * ES;
+      }
+      buffer_load_lds16(rs, voff, 0u, lds0 + uint32_t(q) * 1024u);
+    }
+  }
+  // byte of 16-byte chunk (row, columns col .. col + 7, plane) of a K-major matrix in LDS
+  auto at = [&](int row, int col, int plane) {
+    return (col / BK) * kSlab + swz(row, PL == 1 ? (col % BK) >> 3 : plane * 4 + ((col % BK) >> 3));
+  };
+  // Split: the diagonal of X X^T as fp32 sums of squares of whole values (see
+  // k_tile): four threads per row, a quarter of the columns each
+  auto diag_sums = [&](const char *m) {
+    if constexpr (PL == 2) {
+      const int row = tid >> 2, part = tid & 3;
+      float q[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        half8 h[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) h[p] = *reinterpret_cast<const half8 *>(m + at(row, 32 * part + 8 * c, p));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float x = of_planes<Split>(h, j);
+          q[j & 3] = fmaf(x, x, q[j & 3]);
+        }
+      }
+      float v = (q[0] + q[1]) + (q[2] + q[3]);
+      v += __shfl_xor(v, 1);
+      v += __shfl_xor(v, 2);
+      if (part == 0) dsum[row] = v;
+    }
+  };
+  floatx16 acc[1][FN];
+  auto clear = [&]() {
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[0][j][r] = 0.0f;
+  };
+  const int row = wm * 32 + lr, colw = wn * 64 + 4 * lk;   // acc[0][j][4 g + q]: column colw + 32 j + 8 g + q
+  auto fix_diag = [&]() {
+    if constexpr (PL == 2) {
+      const float dv = dsum[row];
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (row == colw + 32 * j + 8 * g + q) acc[0][j][4 * g + q] = dv;
+    }
+  };
+
+  if constexpr (STEP != kShortFirst) {
+    // A = alpha times the partials, 8 columns per thread and task
+    const float *src = s.pin + size_t(d.trace_begin) * (kTile * kTile);
+    const int parts = d.trace_end - d.trace_begin;
+#pragma unroll
+    for (int k = 0; k < kTile * kTile / 8 / NT; ++k) {
+      const int q = tid + k * NT, r = q / (kTile / 8), c = (q % (kTile / 8)) * 8;
+      const float *p = src + r * kTile + c;
+      float4v a = reinterpret_cast<const float4v *>(p)[0], b = reinterpret_cast<const float4v *>(p)[1];
+      for (int e = 1; e < parts; ++e) {
+        const float4v *pe = reinterpret_cast<const float4v *>(p + size_t(e) * (kTile * kTile));
+        const float4v a1 = pe[0], b1 = pe[1];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          a[j] += a1[j];
+          b[j] += b1[j];
+        }
+      }
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        v[j] = s.gram_alpha * a[j];
+        v[4 + j] = s.gram_alpha * b[j];
+      }
+      half8 h[PL];
+      to_planes<T>(v, h);
+#pragma unroll
+      for (int pl = 0; pl < PL; ++pl) *reinterpret_cast<half8 *>(sA + at(r, c, pl)) = h[pl];
+    }
+    __syncthreads();
+    // B = a I + b A + c A A
+    diag_sums(sA);
+    clear();
+#pragma unroll
+    for (int b = 0; b < NSLAB; ++b)
+      compute_slab<T, 1, FN, false, 0>(acc, sA + b * kSlab, sA + b * kSlab, wm * 32, wn * 64, lane);
+    float alpha = s.g.alpha, beta = s.g.beta, gamma = s.g.gamma;
+    if (s.g.kap) {
+      const double kp = s.g.sc[tile.mat].kappa, k2 = kp * kp;
+      alpha = float(double(s.g.alpha) * k2 * k2 * kp);
+      beta = float(double(s.g.beta) * k2 * kp);
+      gamma = float(double(s.g.gamma) * kp);
+    }
+    if constexpr (PL == 2) __syncthreads();          // dsum
+    fix_diag();
+    half4 hb[FN][4][PL];
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int col = colw + 32 * j + 8 * g;
+        half4 a[PL];
+#pragma unroll
+        for (int p = 0; p < PL; ++p) a[p] = *reinterpret_cast<const half4 *>(sA + at(row, col, p) + ((col >> 2) & 1) * 8);
+        float v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          v[q] = fmaf(alpha, acc[0][j][4 * g + q], beta * of_planes<T>(a, q)) + (row == col + q ? gamma : 0.0f);
+        to_planes<T>(v, hb[j][g]);
+      }
+    __syncthreads();                                 // every wave has read A
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int col = colw + 32 * j + 8 * g;
+#pragma unroll
+        for (int p = 0; p < PL; ++p)
+          *reinterpret_cast<half4 *>(sA + at(row, col, p) + ((col >> 2) & 1) * 8) = hb[j][g][p];
+      }
+    vm_wait<0>();                                    // the slice's fetches
+    __syncthreads();
+    // X' = B X on the slice
+    clear();
+#pragma unroll
+    for (int b = 0; b < NSLAB; ++b)
+      compute_slab<T, 1, FN, true, KNP>(acc, sA + b * kSlab, sX + b * kSlab, wm * 32, wn * 64, lane);
+    __syncthreads();                                 // every wave has read X
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int col = colw + 32 * j + 8 * g;
+        float v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = acc[0][j][4 * g + q] * s.upd_alpha;
+        half4 h[PL];
+        to_planes<T>(v, h);
+#pragma unroll
+        for (int p = 0; p < PL; ++p)
+          *reinterpret_cast<half4 *>(sX + at(row, col, p) + ((col >> 2) & 1) * 8) = h[p];
+      }
+    __syncthreads();
+    // the slice to memory, and the trace's partial
+    double tsum = 0.0;
+#pragma unroll
+    for (int k = 0; k < kTile * kTile / 8 / NT; ++k) {
+      const int q = tid + k * NT, r = q / (kTile / 8), c = (q % (kTile / 8)) * 8;
+      half8 h[PL];
+#pragma unroll
+      for (int p = 0; p < PL; ++p) {
+        h[p] = *reinterpret_cast<const half8 *>(sX + at(r, c, p));
+        if (STEP == kShortStep || s.g.write_x)
+          *reinterpret_cast<half8 *>(Xn + byte_of<T>(size_t(r), d.Qp, n0 + c, p)) = h[p];
+      }
+      if constexpr (STEP == kShortLast) {
+        half8 x0[PL];
+#pragma unroll
+        for (int p = 0; p < PL; ++p)
+          x0[p] = *reinterpret_cast<const half8 *>(s.g.ws + d.x[0] + byte_of<T>(size_t(r), d.Qp, n0 + c, p));
+        tsum += trace_planes<T>(h, x0);
+      }
+    }
+    if constexpr (STEP == kShortLast) {
+      const double r = block_sum<NT>(tsum, reinterpret_cast<double *>(sA));   // B is done with
+      if (tid == 0) s.g.tpart[tile.slot] = r;
+    }
+  } else {
+    vm_wait<0>();
+    __syncthreads();
+  }
+  if constexpr (STEP != kShortLast) {
+    diag_sums(sX);
+    clear();
+#pragma unroll
+    for (int b = 0; b < NSLAB; ++b)
+      compute_slab<T, 1, FN, false, 0>(acc, sX + b * kSlab, sX + b * kSlab, wm * 32, wn * 64, lane);
+    if constexpr (PL == 2) __syncthreads();
+    fix_diag();
+    float *out = s.pout + size_t(tile.slot) * (kTile * kTile) + size_t(row) * kTile + colw;
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float4v f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) f[q] = acc[0][j][4 * g + q];
+        *reinterpret_cast<float4v *>(out + 32 * j + 8 * g) = f;
+      }
+  }
+}
 // ---------------------------------------------------------------------------
 // Update / Last on 256 x 256 tiles: a persistent kernel.
 //

@@ -795,7 +795,7 @@ void launch_sym(const Plan &p, const Launch &l, GemmArgs a, const Tile *tiles, h
   a.alpha = l.sym_alpha;
   a.kap = 0;
   EvPair first{};
-  if (ev && l.chain == kSymBefore) {       // the pair spans both kernels
+  if (ev && l.run == kSymBefore) {       // the pair spans both kernels
     first.start = ev->start;
     ev = &first;
   }
@@ -803,6 +803,44 @@ void launch_sym(const Plan &p, const Launch &l, GemmArgs a, const Tile *tiles, h
   if (cfg == kCfg256) go(k_tile<Tx, kSym, kBigTile, kBigTile, 2, 4, 2>, grid, dim3(512), s, ev, a);
   else if (r.count <= kCus) go(k_tile<Tx, kSym, kTile, kTile, 2, 2, 4>, grid, dim3(256), s, ev, a);
   else go(k_tile<Tx, kSym, kTile, kTile, 2, 2, 2>, grid, dim3(256), s, ev, a);
+}
+
+// A step of a set of short matrices (Gram: X_0's partials). Partials pass
+// between launches in two buffers; step t, known by the buffer it reads X from
+// (0, then 1 and 2 in turn), reads buffer t mod 2. The slices of step 1 go from
+// x[0] to the buffer of X_T, where the later steps work in place.
+template <typename Tx>
+void launch_short(const Plan &p, const Launch &l, const GemmArgs &a, char *ws, hipStream_t s, const EvPair *ev) {
+  const TileRange r = p.pq[kCfg128];
+  const int last = 1 + ((p.iters - 1) & 1);
+  const int odd = l.op == Op::Gram ? 1 : l.xin == 1;
+  float *part[2] = {reinterpret_cast<float *>(ws + p.off_short),
+                    reinterpret_cast<float *>(ws + p.off_short) + size_t(kTile) * kTile * p.trace_slots};
+  ShortArgs sa{};
+  sa.g = a;
+  sa.g.tiles = reinterpret_cast<const Tile *>(ws + p.off_tiles) + r.first;
+  sa.g.ntiles = r.count;
+  sa.g.xin = l.xin == 0 ? 0 : last;
+  sa.g.xout = last;
+  sa.pin = part[odd];
+  sa.pout = part[odd ^ 1];
+  sa.gram_alpha = l.gram_alpha;
+  sa.upd_alpha = l.alpha;
+  sa.g.alpha = l.poly_alpha;
+  sa.g.beta = l.poly_beta;
+  sa.g.gamma = l.poly_gamma;
+  sa.g.kap = l.poly_kap;
+  const dim3 grid(r.count), block(512);
+  if (l.op == Op::Gram) go(k_short<Tx, kShortFirst>, grid, block, s, ev, sa);
+  else if (l.op == Op::Update) go(k_short<Tx, kShortStep>, grid, block, s, ev, sa);
+  else go(k_short<Tx, kShortLast>, grid, block, s, ev, sa);
+}
+
+// A launch of the plan's list that has nothing to run.
+void no_launch(hipStream_t s, const EvPair *ev) {
+  if (!ev) return;
+  check(hipEventRecord(ev->start, s), "hipEventRecord");
+  check(hipEventRecord(ev->stop, s), "hipEventRecord");
 }
 
 // The products on fp32 MFMA.
@@ -894,10 +932,19 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
         a.pl = l.pl;
         a.pr = l.pr;
         a.po = l.po;
-        if (l.chain) {
+        if (l.run == kNothing) {
+          no_launch(s, ev);
+          break;
+        }
+        if (l.run == kRunShort) {
+          if constexpr (!std::is_same<Tx, float>::value) launch_short<Tx>(p, l, a, ws, s, ev);
+          else throw HipError("no short-matrix steps on fp32 MFMA");
+          break;
+        }
+        if (l.run) {
           if constexpr (!std::is_same<Tx, float>::value) launch_sym<Tx>(p, l, a, tiles, s, ev);
           else throw HipError("no chained steps on fp32 MFMA");
-          if (l.chain == kSymInstead) break;
+          if (l.run == kSymInstead) break;
           if (ev) {
             second.stop = ev->stop;
             ev = &second;
@@ -923,11 +970,8 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
            1.0f / sx);
         break;
       case Op::GramReduce:
-        if (l.chain == kNothing) {                 // the chained Gram product has no parts
-          if (ev) {
-            check(hipEventRecord(ev->start, s), "hipEventRecord");
-            check(hipEventRecord(ev->stop, s), "hipEventRecord");
-          }
+        if (l.run == kNothing) {
+          no_launch(s, ev);
           break;
         }
         go(k_gram_reduce<Tx>, grid, block, s, ev, tiles + l.tile_first, mats, ws,

@@ -33,6 +33,8 @@ constexpr int kMinSplitSlabs16 = 32, kMinPartSlabs16 = 8;
 constexpr int kMinChainIters = 6;
 constexpr double kChainEll = 1e-3, kChainSafety = 0.01;
 constexpr double kChainGain = 1.5, kChainGainFew = 4.0;
+// sets of short matrices: slices per matrix, and Gram partials read per step
+constexpr int kMaxShortSlices = 8, kMaxShortReads = 1600;
 constexpr int kMinSplitSlabs32 = 8, kMinPartSlabs32 = 4;
 
 Tile make_tile(int32_t mat, int32_t tm, int32_t tn, int32_t slot) {
@@ -396,6 +398,28 @@ void build_plan(Plan &p) {
   }
   p.trace_slots = slot;
 
+  // Sets of short matrices run one launch per step (k_short): every matrix has
+  // one tile of rows and at most kMaxShortSlices of columns, every step is
+  // quintic, and a step reads at most kMaxShortReads Gram partials (each block
+  // all of its matrix's): beyond, the reads and the poly product that every
+  // block forms cost more than the launches they save. Per call, launch per
+  // product -> per step, at partials read, T = 6:
+  //   fp32  384 (24 of 128 x 512) 259 -> 137 us    1600 (100 of them) 426 -> 313
+  //         1920 (30 of 128 x 1024) 317 -> 312     16384 (256 of them) 974 -> 1907
+  //   bf16  384: 163 -> 87    1600: 193 -> 188     4096 (256 of 128 x 512) 298 -> 335
+  // Their partials lie behind the matrices; a set that fits the static scratch
+  // of the no-allocation entry without them and not with them goes step by
+  // step.
+  p.short_set = scaled && !order.empty();
+  int64_t reads = 0;
+  for (int i : order) {
+    const int64_t slices = p.mats[i].Qp / kTile;
+    p.short_set &= p.mats[i].Pp == kTile && slices <= kMaxShortSlices;
+    reads += slices * slices;
+  }
+  p.short_set &= reads <= kMaxShortReads;
+  for (int t = 0; t < T; ++t) p.short_set &= p.coeffs[3 * t + 2] != 0.0;
+
   // Steps 1 and 2 on the Gram matrix: X_2 = B_2 B_1 X_0 is formed without X_1,
   // whose Gram matrix is B_1 A B_1:
   //   A, B_1 as ever;  Y = A B_1;  A' = Y B_1;  B_2 from A';  Z = B_2 B_1;  X_2 = Z X_0
@@ -431,7 +455,7 @@ void build_plan(Plan &p) {
       }
       zbound = bounds[0] * bounds[1];
       const TileRange &r = p.pp[p.pp[kCfg256].count ? kCfg256 : kCfg128];
-      p.chained = !order.empty() && saved >= (r.count > kCus ? kChainGain : kChainGainFew) * added;
+      p.chained = !order.empty() && !p.short_set && saved >= (r.count > kCus ? kChainGain : kChainGainFew) * added;
     }
   }
   // canonical 64 x 64 tiles: the norm (one partial slot each, contiguous per
@@ -494,6 +518,12 @@ void build_plan(Plan &p) {
     d.b = any_quintic ? take(pp) : d.a;
     d.xt = d.x[xbuf(T)];                      // step t reads x[xbuf(t)], writes x[xbuf(t + 1)]
   }
+  p.off_short = off;
+  if (p.short_set) {
+    const size_t with = off + align256(2 * sizeof(float) * size_t(kTile) * kTile * size_t(p.trace_slots));
+    if (off <= size_t(SLORR_SCRATCH_BYTES) && with > size_t(SLORR_SCRATCH_BYTES)) p.short_set = false;
+    else off = with;
+  }
   p.ws_bytes = off;
   // host image of the table region, for the entry point that allocates nothing
   p.image.assign(p.off_scal, 0);
@@ -534,7 +564,7 @@ void build_plan(Plan &p) {
     }
   };
   auto sym = [](Launch &l, PpBuf left, PpBuf right, PpBuf out, double alpha) {
-    l.chain = kSymInstead;
+    l.run = kSymInstead;
     l.pl = left;
     l.pr = right;
     l.po = out;
@@ -557,6 +587,7 @@ void build_plan(Plan &p) {
     Launch g{};
     g.xin = xi;
     g.alpha = float(sa / (double(sx) * sx));
+    if (p.short_set) g.run = t == 0 ? kRunShort : kNothing;
     if (chain2) sym(g, kPpX1, kPpB, kPpA, 1.0 / sb);            // A' = Y B_1
     if (p.gsplit.count) {
       g.op = Op::Gram;
@@ -568,7 +599,7 @@ void build_plan(Plan &p) {
       p.launches.push_back(g);                // fp32 partials
       Launch l = plain(Op::GramReduce, p.gred.count * kRedStripes, p.gred.first);
       l.alpha = g.alpha;
-      if (chain2) l.chain = kNothing;
+      if (chain2 || p.short_set) l.run = kNothing;
       p.launches.push_back(l);
     } else {
       gemm(Op::Gram, p.gram, g);
@@ -584,6 +615,7 @@ void build_plan(Plan &p) {
       l.beta = float(double(sb) * b / sa);
       l.gamma = float(double(sb) * a);
       l.pl = kPpA;
+      if (p.short_set) l.run = kNothing;
       l.po = chain2 ? kPpX1 : kPpB;                             // B_2 in Y's place
       gemm(Op::Poly, p.pp, l);
       // X'_s = (B_s X_s) / s_b
@@ -592,10 +624,18 @@ void build_plan(Plan &p) {
       u.xout = xo;
       u.fold = 1;
       u.alpha = prod;
+      if (p.short_set) {
+        u.run = kRunShort;
+        u.gram_alpha = g.alpha;
+        u.poly_alpha = l.alpha;
+        u.poly_beta = l.beta;
+        u.poly_gamma = l.gamma;
+        u.poly_kap = kap;
+      }
       if (chain1) sym(u, kPpA, kPpB, kPpX1, 1.0 / sb);          // Y = A B_1
       if (chain2) {                                             // Z = B_2 B_1, X_2 = Z X_0
         sym(u, kPpX1, kPpB, kPpA, sz / (double(sb) * sb));
-        u.chain = kSymBefore;
+        u.run = kSymBefore;
         u.alpha = float(1.0 / sz);
       }
       gemm(op, p.pq, u);

@@ -51,17 +51,20 @@ struct Launch {
   int32_t set_sum;     // gradient launch: its first block also writes the set total
   float alpha, beta, gamma;  // epilogue coefficients
   // what the launch runs where it differs from the above (chained steps 1
-  // and 2, see build_plan)
-  int32_t chain;       // Chain
+  // and 2, sets of short matrices: see build_plan)
+  int32_t run;         // Run
   int32_t pl, pr, po;  // PpBuf: Poly's A and B; the symmetric product's operands and output
   float sym_alpha;     // the symmetric product's factor
+  float gram_alpha, poly_alpha, poly_beta, poly_gamma;  // kRunShort: those of the step's Gram
+  int32_t poly_kap;                                     // and poly products
 };
 
-enum Chain : int32_t {
-  kNoChain = 0,
+enum Run : int32_t {
+  kRunOwn = 0,
   kSymInstead = 1,     // runs the symmetric product po = sym_alpha pl pr in its place
   kSymBefore = 2,      // runs it before its own kernel, an update from x[0] with the operand A
-  kNothing = 3         // runs nothing
+  kNothing = 3,        // runs nothing
+  kRunShort = 4        // runs k_short: Gram X_0's partials, update and last the whole step
 };
 
 struct TileRange {
@@ -93,6 +96,7 @@ struct Plan {
   TileRange upd;                       // the 128-tile update list as 256-tiles (empty: not used)
   TileRange gsplit, gred;              // split-K Gram: part entries, reduce entries
   bool chained = false;                // steps 1 and 2 run on the Gram matrix
+  bool short_set = false;              // one launch per step (k_short)
   int32_t gram_parts = 0;              // fp32 partial tiles in the workspace
   int32_t trace_slots = 0;             // one per update tile
   int32_t norm_slots = 0;              // one per canonical 64 x 64 tile
@@ -102,7 +106,7 @@ struct Plan {
   double paper_flops = 0, mfma_flops = 0, weight_bytes = 0;
   // workspace layout (byte offsets)
   size_t off_mats = 0, off_dyn = 0, off_call = 0, off_tiles = 0, off_chunks = 0, off_scal = 0,
-         off_sumsq = 0, off_trace = 0, off_gpart = 0, off_static_end = 0, ws_bytes = 0;
+         off_sumsq = 0, off_trace = 0, off_gpart = 0, off_short = 0, off_static_end = 0, ws_bytes = 0;
   // runtime state (owned by the API layer)
   void *ws = nullptr;
   int device = -1;

@@ -115,13 +115,24 @@ int main() {
     auto symmetric = [&](const Launch &l) { pp[l.po] = double(l.sym_alpha) * pp[l.pl] * pp[l.pr]; };
     for (const Launch &l : p.launches) {
       const double k = l.kap ? kappa : 1.0;
-      if (l.chain && !p.chained) fail("chain flag", l.chain, int(l.op), 0);
-      if (l.chain == kSymInstead) {
+      if ((l.run == kSymInstead || l.run == kSymBefore) && !p.chained) fail("chain flag", l.run, int(l.op), 0);
+      if (l.run == kRunShort && !p.short_set) fail("short-set flag", l.run, int(l.op), 0);
+      if (l.run == kNothing) {
+        continue;
+      } else if (l.run == kRunShort) {        // one slice: X stays in the buffer of X_T from step 1 on
+        const int last = iters == 0 ? 0 : 1 + ((iters - 1) & 1);
+        double &X = x[l.op == Op::Gram || l.xin == 0 ? 0 : last];
+        if (l.op != Op::Gram) {
+          const double kp = l.poly_kap ? kappa : 1.0, k2 = kp * kp, A = l.gram_alpha * part;
+          x[last] = l.alpha * (l.poly_beta * k2 * kp * A + l.poly_alpha * k2 * k2 * kp * A * A + l.poly_gamma * kp) * X;
+        }
+        part = x[l.op == Op::Gram ? 0 : last] * x[l.op == Op::Gram ? 0 : last];
+      } else if (l.run == kSymInstead) {
         symmetric(l);
         x[1] = nan;
       } else if (l.op == Op::Gram) {
         (p.gsplit.count ? part : pp[kPpA]) = (p.gsplit.count ? 1.0 : double(l.alpha)) * x[l.xin] * x[l.xin];
-      } else if (l.op == Op::GramReduce && l.chain != kNothing) {
+      } else if (l.op == Op::GramReduce && l.run != kNothing) {
         pp[kPpA] = l.alpha * part;
       } else if (l.op == Op::Poly) {
         const double A = pp[l.pl], k2 = k * k;
@@ -129,7 +140,7 @@ int main() {
         if (l.po == kPpX1) x[1] = nan;
       } else if (l.op == Op::Update || l.op == Op::Last) {
         int xin = l.xin, use_a = l.use_a;
-        if (l.chain == kSymBefore) {
+        if (l.run == kSymBefore) {
           symmetric(l);
           xin = 0;
           use_a = 1;
@@ -148,6 +159,6 @@ int main() {
     if (!(std::fabs(got - want) <= 1e-4 * std::fabs(want) + 1e-6)) fail("schedule's value", int(1e6 * got), int(1e6 * want), int(100 * x0));
   }
   if (bad) return 1;
-  std::printf("OK split=%d run256=%d chained=%d\n", p.split ? 1 : 0, run, p.chained ? 1 : 0);
+  std::printf("OK split=%d run256=%d chained=%d short=%d\n", p.split ? 1 : 0, run, p.chained ? 1 : 0, p.short_set ? 1 : 0);
   return 0;
 }

@@ -104,3 +104,30 @@ def test_chain_rule(checker, dtype):
 
 def test_no_chain_on_fp32_mfma(checker):
     assert run(checker, [(384, 1024)] * 48, F32, grad=BF16)["chained"] == "0"
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_short_rule(checker, dtype):
+    """One launch per step: every matrix at most 128 x 1024, quintic steps."""
+    def short(*args, **kw):
+        return run(checker, *args, **kw)["short"] == "1"
+
+    for iters in (1, 2, 5, 6):
+        assert short([(128, 256)] * 4, dtype, iters=iters)
+    assert short([(1, 7), (1024, 128), (0, 5), (100, 1000)], dtype)
+    assert not short([(128, 256), (129, 256)], dtype) and not short([(128, 1025)], dtype)
+    assert not short([(0, 5)], dtype) and not short([], dtype)
+    assert not short([(128, 256)], dtype, coeffs=[1.5, -0.5, 0.0] * 6)
+    assert not short([(128, 256)], dtype, coeffs=[2.0, -1.5, 0.5] * 5 + [1.5, -0.5, 0.0])
+    assert short([(128, 256)], dtype, coeffs=[15 / 8, -10 / 8, 3 / 8] * 6)
+    assert short([(128, 128)] * 1600, dtype) and not short([(128, 128)] * 1601, dtype)   # partials read a step
+    # the partials must not take a set out of the 64 MiB static scratch: 1 MiB
+    # of each 128 x 1024 matrix, beside 1.625 (fp32) or 0.8125
+    few, at_limit = (20, 25) if dtype == F32 else (25, None)
+    assert short([(128, 1024)] * few, dtype)
+    if at_limit:
+        assert not short([(128, 1024)] * at_limit, dtype)
+
+
+def test_no_short_steps_on_fp32_mfma(checker):
+    assert run(checker, [(128, 256)] * 4, F32, grad=BF16)["short"] == "0"
