@@ -788,8 +788,8 @@ void launch_tile(Op op, dim3 grid, const GemmArgs &a, hipStream_t s, const EvPai
 // A symmetric product of the chained steps.
 template <typename Tx>
 void launch_sym(const Plan &p, const Launch &l, GemmArgs a, const Tile *tiles, hipStream_t s, const EvPair *ev) {
-  const int cfg = p.pp[kCfg256].count ? kCfg256 : kCfg128;
-  const TileRange r = p.pp[cfg];
+  const int cfg = p.pp64.count ? kCfg64 : p.pp[kCfg256].count ? kCfg256 : kCfg128;
+  const TileRange r = cfg == kCfg64 ? p.pp64 : p.pp[cfg];
   a.tiles = tiles + r.first;
   a.ntiles = r.count;
   a.alpha = l.sym_alpha;
@@ -800,7 +800,8 @@ void launch_sym(const Plan &p, const Launch &l, GemmArgs a, const Tile *tiles, h
     ev = &first;
   }
   const dim3 grid(r.count);
-  if (cfg == kCfg256) go(k_tile<Tx, kSym, kBigTile, kBigTile, 2, 4, 2>, grid, dim3(512), s, ev, a);
+  if (cfg == kCfg64) go(k_tile<Tx, kSym, kSmallTile, kSmallTile, 2, 1, 4>, grid, dim3(128), s, ev, a);
+  else if (cfg == kCfg256) go(k_tile<Tx, kSym, kBigTile, kBigTile, 2, 4, 2>, grid, dim3(512), s, ev, a);
   else if (r.count <= kCus) go(k_tile<Tx, kSym, kTile, kTile, 2, 2, 4>, grid, dim3(256), s, ev, a);
   else go(k_tile<Tx, kSym, kTile, kTile, 2, 2, 2>, grid, dim3(256), s, ev, a);
 }
@@ -956,6 +957,9 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
         if constexpr (std::is_same<Tx, float>::value) {
           if (l.run_cfg == kCfg256) launch_gemm<kBigTile, kBigTile, 2, 4>(l.op, g, a, s, ev);
           else launch_gemm<kTile, kTile, 2, 2>(l.op, g, a, s, ev);
+        } else if (l.run_cfg == kCfg64) {
+          if (l.op == Op::Gram) go(k_tile<Tx, kGram, kSmallTile, kSmallTile, 2, 1, 4>, g, dim3(128), s, ev, a);
+          else go(k_tile<Tx, kPoly, kSmallTile, kSmallTile, 2, 1, 4>, g, dim3(128), s, ev, a);
         } else if (l.run_cfg == kCfg256) {
           launch_tile<Tx, kBigTile, kBigTile, 2, 4, 2>(l.op, g, a, s, ev);
         } else if (l.run_grid <= kCus) {           // at most one block per CU: 4 stages (see k_tile)

@@ -13,6 +13,7 @@ namespace slorr {
 
 constexpr int kTile = 128;       // padding granularity = the small GEMM block tile
 constexpr int kBigTile = 256;    // the large GEMM block tile
+constexpr int kSmallTile = 64;   // the GEMM block tile of launches with few tiles
 constexpr int kPrepTile = 64;    // tile of the normalise / transpose kernel
 constexpr int kChunk = 32768;    // elements per block of the decoupled-update kernel
 constexpr int kThreads = 256;    // threads per block of the non-GEMM kernels

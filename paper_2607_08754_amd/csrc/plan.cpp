@@ -32,9 +32,10 @@ constexpr int kMinSplitSlabs16 = 32, kMinPartSlabs16 = 8;
 // gain in work from which they pay
 constexpr int kMinChainIters = 6;
 constexpr double kChainEll = 1e-3, kChainSafety = 0.01;
-constexpr double kChainGain = 1.5, kChainGainFew = 4.0;
+constexpr double kChainGain = 1.5, kChainGainFew = 2.0;
 // sets of short matrices: slices per matrix, and Gram partials read per step
 constexpr int kMaxShortSlices = 8, kMaxShortReads = 1600;
+constexpr int64_t kMaxSmallTiles = 2 * kCus;   // 64-tiles of a launch
 constexpr int kMinSplitSlabs32 = 8, kMinPartSlabs32 = 4;
 
 Tile make_tile(int32_t mat, int32_t tm, int32_t tn, int32_t slot) {
@@ -328,6 +329,34 @@ void build_plan(Plan &p) {
       p.gred.count = int32_t(reds.size());
     }
   }
+  // Symmetric outputs of few tiles on 16-bit operands run as 64-tiles, up to
+  // two per CU: a tile's k range is serial work on one CU, a quarter of it on a
+  // 64-tile, whose fetches (twice the bytes per product) such launches have
+  // room for. Per call, 128-tiles -> P x P products -> Gram on 64-tiles too:
+  // ResNet-18 in fp32 (61 tiles, 211 64-tiles; its Gram is split) 711 -> 656 us,
+  // ViT-Ti (144, 480) 228 -> 213 -> 203. With up to four per CU: ViT-S (288, 1008)
+  // 487 -> 501 -> 512.
+  p.gram64 = p.pp64 = TileRange{};
+  if (scaled) {
+    int64_t tiles = 0;
+    std::vector<Job> jobs;
+    for (int i : order) {
+      Job j{i, double(p.mats[i].Pp), {}};
+      const int nt = p.mats[i].Pp / kSmallTile;
+      tiles += int64_t(nt) * (nt + 1) / 2;
+      if (tiles > kMaxSmallTiles) break;
+      for (int tm = 0; tm < nt; ++tm)
+        for (int tn = tm; tn < nt; ++tn) j.tiles.push_back(make_tile(i, tm, tn, 0));
+      jobs.push_back(std::move(j));
+    }
+    if (tiles <= kMaxSmallTiles) {
+      p.pp64 = emit(jobs);
+      if (!p.gsplit.count && p.gram[kCfg128].count) {
+        for (Job &j : jobs) j.cost = p.mats[j.mat].Qp;
+        p.gram64 = emit(jobs);
+      }
+    }
+  }
   // Update launches: X' = B X (P x Q, full output). The tiles of the last
   // update own one trace slot each, contiguous per matrix (the same list
   // serves every step). The tiles of one matrix form one job, dispatched
@@ -432,8 +461,8 @@ void build_plan(Plan &p) {
   //   2.6 ViT-B/16 1953 -> 1860 us, in fp32 5036 -> 4722   2.7 ViT-L/16 7.83 -> 7.40 ms
   //   2.3 ViT-S 539 -> 524 us, in fp32 1230 -> 1183    7 ResNet-18 in fp32 768 -> 744 us
   // and kChainGainFew where a launch has at most one tile per CU, whose time
-  // is latency (ResNet-18 above; 1.6 ViT-Ti, 144 tiles, 244 -> 249 us; a set at
-  // 350 us between the two lost 1 %).
+  // is latency: 3.1 the odd shapes 638 -> 607 us, 1.6 ViT-Ti (144 tiles) 244 ->
+  // 249.
   // Precision: X_1's rounding goes, that of A' and Z comes; what A' lacks is
   // absolute and small against the matrix's norm, and B_2 is nearly constant
   // where it matters. Gradients' errors against 64 bits: ViT-B/16 1.96e-3 ->
@@ -555,6 +584,12 @@ void build_plan(Plan &p) {
       l.run_cfg = cfg;
       l.run_first = l.tile_first;
       l.run_grid = l.grid;
+      const TileRange &r64 = op == Op::Gram ? p.gram64 : p.pp64;
+      if ((op == Op::Gram || op == Op::Poly) && r64.count) {
+        l.run_cfg = kCfg64;
+        l.run_first = r64.first;
+        l.run_grid = r64.count;
+      }
       if ((op == Op::Update || op == Op::Last) && p.upd.count) {
         l.run_cfg = kCfg256;
         l.run_first = p.upd.first;

@@ -34,7 +34,8 @@ enum class Op : int {
 enum GemmCfg : int32_t {
   kCfg128 = 0,   // 128 x 128 block tile, 4 waves of 64 x 64
   kCfg256 = 1,   // 256 x 256 block tile, 8 waves of 128 x 64
-  kNumCfg = 2
+  kNumCfg = 2,
+  kCfg64 = 2     // 64 x 64 block tile, 2 waves of 32 x 64: run lists of symmetric outputs
 };
 
 struct Launch {
@@ -43,7 +44,7 @@ struct Launch {
   int32_t tile_first;  // first entry of the launch's tile list (GEMM, prep)
   int32_t cfg;         // GemmCfg of a GEMM launch's tile list
   int32_t run_cfg, run_first, run_grid;  // the kernel instance and list that run: those of
-                       // cfg, or 256-tiles that each cover four 128-tiles of the list
+                       // cfg, or 256- or 64-tiles that cover the list's 128-tiles
   int32_t xin, xout;   // X buffers read / written (MatDesc::x index)
   int32_t use_a;       // update operand is A (cubic step) instead of B
   int32_t fold;        // update: a_t I already folded into B (no a X term)
@@ -94,6 +95,7 @@ struct Plan {
   TileRange pq[kNumCfg];               // P x Q outputs (update, last), per GemmCfg
   TileRange prep;                      // prep tiles over Pp x Qp
   TileRange upd;                       // the 128-tile update list as 256-tiles (empty: not used)
+  TileRange gram64, pp64;              // the symmetric outputs as 64-tiles (empty: not used)
   TileRange gsplit, gred;              // split-K Gram: part entries, reduce entries
   bool chained = false;                // steps 1 and 2 run on the Gram matrix
   bool short_set = false;              // one launch per step (k_short)

@@ -91,9 +91,35 @@ int main() {
         d.b != d.a + (quintic ? pa : 0))
       fail("buffers", i, d.Pp, d.Qp);
   }
+  // the symmetric outputs as 64-tiles: every upper tile once, padding at the
+  // end of each XCD's queue, at most two per CU
+  for (const TileRange &r : {p.gram64, p.pp64}) {
+    if (!r.count) continue;
+    bool pad[kXcds] = {};
+    std::map<std::tuple<int, int, int>, int> seen;
+    for (int e = 0; e < r.count; ++e) {
+      const Tile &t = p.tiles[r.first + e];
+      if (t.mat < 0) {
+        pad[e % kXcds] = true;
+        continue;
+      }
+      if (pad[e % kXcds] || t.k1 != 0) fail("64-tile entry", e, t.mat, t.k1);
+      if (t.tm > t.tn || t.tn * kSmallTile >= p.mats[t.mat].Pp) fail("64-tile", t.mat, t.tm, t.tn);
+      seen[{t.mat, t.tm, t.tn}]++;
+    }
+    size_t want = 0;
+    for (const MatDesc &d : p.mats) want += d.empty ? 0 : size_t(d.Pp / kSmallTile) * (d.Pp / kSmallTile + 1) / 2;
+    if (seen.size() != want || want > size_t(2 * kCus)) fail("64-tiles", int(seen.size()), int(want), 0);
+    for (const auto &kv : seen)
+      if (kv.second != 1) fail("64-tile not covered once", std::get<0>(kv.first), std::get<1>(kv.first), kv.second);
+  }
   int run = 0;
   for (const Launch &l : p.launches) {
-    if (l.op == Op::Gram || l.op == Op::Poly) {
+    const TileRange &r64 = l.op == Op::Gram ? p.gram64 : p.pp64;
+    if ((l.op == Op::Gram || l.op == Op::Poly) && r64.count) {
+      if (l.run_cfg != kCfg64 || l.run_first != r64.first || l.run_grid != r64.count || l.cfg != kCfg128)
+        fail("64-tile run list", l.cfg, l.run_cfg, l.run_grid);
+    } else if (l.op == Op::Gram || l.op == Op::Poly) {
       if (l.run_cfg != l.cfg || l.run_first != l.tile_first || l.run_grid != l.grid) fail("Gram / poly run list", l.cfg, l.run_cfg, 0);
     } else if (l.op == Op::Update || l.op == Op::Last) {
       const bool big = p.upd.count > 0;
@@ -159,6 +185,7 @@ int main() {
     if (!(std::fabs(got - want) <= 1e-4 * std::fabs(want) + 1e-6)) fail("schedule's value", int(1e6 * got), int(1e6 * want), int(100 * x0));
   }
   if (bad) return 1;
-  std::printf("OK split=%d run256=%d chained=%d short=%d\n", p.split ? 1 : 0, run, p.chained ? 1 : 0, p.short_set ? 1 : 0);
+  std::printf("OK split=%d run256=%d chained=%d short=%d small=%d%d\n", p.split ? 1 : 0, run, p.chained ? 1 : 0, p.short_set ? 1 : 0,
+              p.gram64.count > 0, p.pp64.count > 0);
   return 0;
 }

@@ -1,5 +1,6 @@
-"""bf16 sets on 128-tiles: a launch of at most 256 tiles runs with four LDS
-stages, a larger one with two. The products are formed in the same order, so
+"""bf16 sets on 64- and 128-tiles: symmetric outputs of at most 512 64-tiles run
+on these, other launches on 128-tiles with four LDS stages for at most 256 of
+them, else two. The products are formed in the same order, so
 a matrix on its own and among many equal ones gets the same value and gradient
 bit for bit; and both agree with the oracle."""
 import os

@@ -85,7 +85,7 @@ def test_split_needs_fp32_gradients(checker):
 @pytest.mark.parametrize("dtype", [F32, BF16])
 def test_chain_rule(checker, dtype):
     """Steps 1 and 2 on the Gram matrix: the default table of at least 6 steps,
-    1.5 times less work than step by step (4 times for few tiles)."""
+    1.5 times less work than step by step (2 times for few tiles)."""
     def chained(*args, **kw):
         return run(checker, *args, **kw)["chained"] == "1"
 
@@ -93,7 +93,7 @@ def test_chain_rule(checker, dtype):
     assert chained(many, dtype) and chained(many, dtype, iters=8)
     assert not chained(many, dtype, iters=5)
     assert chained([(384, 768)] * 48, dtype) and not chained([(384, 640)] * 48, dtype)     # 1.5, 1.25
-    assert chained([(384, 2048)] * 4, dtype) and not chained([(384, 1920)] * 4, dtype)     # 24 tiles: 4, 3.75
+    assert chained([(384, 1024)] * 4, dtype) and not chained([(384, 896)] * 4, dtype)      # 24 tiles: 2, 1.75
     assert chained([(128, 4096)] * 3, dtype)                   # with a split-K Gram product
     assert chained([(512, 4096)] * 40, dtype)                  # Gram and update on 256-tiles
     assert not chained([(0, 7), (0, 0)], dtype)
@@ -131,3 +131,23 @@ def test_short_rule(checker, dtype):
 
 def test_no_short_steps_on_fp32_mfma(checker):
     assert run(checker, [(128, 256)] * 4, F32, grad=BF16)["short"] == "0"
+
+
+@pytest.mark.parametrize("dtype", [F32, BF16])
+def test_small_tiles(checker, dtype):
+    """Symmetric outputs on 64-tiles: at most 512 of them; a split Gram product
+    stays on its parts; not on fp32 MFMA."""
+    def small(*args, **kw):
+        return run(checker, *args, **kw)["small"]
+
+    assert small([(200, 3000)] * 4, dtype) == "01"
+    assert small([(200, 250)] * 51, dtype)[1] == "1"                              # 510 64-tiles
+    if dtype == BF16:
+        assert small([(200, 250)] * 51, dtype) == "11"
+    assert small([(200, 250)] * 52, dtype) == "00"                                # 520
+    assert small([(1, 130), (7, 13), (0, 5), (150, 200)], dtype)[1] == "1"
+    assert small([(0, 5)], dtype) == "00"
+
+
+def test_no_small_tiles_on_fp32_mfma(checker):
+    assert run(checker, [(200, 250)] * 4, F32, grad=BF16)["small"] == "00"
