@@ -582,6 +582,9 @@ __global__ __launch_bounds__(kThreads) void k_gram_reduce(const Tile *__restrict
 // grad + u. One block per 64 x 64 canonical tile: X_T rows are read 8 at a
 // time, staged in LDS (fp32) and read back along W's rows (transposed for tall
 // W), so that W and grad are accessed 8 consecutive elements at a time.
+// SLORR-Nuc (use_w 0) has s2 = 0 and leaves W unread (a W with a NaN or an
+// infinity has a P of NaN): 170 of 680 MB on ViT-B/16 in bf16, 1796 -> 1787 us a
+// call, in fp32 4510 -> 4462.
 // Contraction is off: each product and sum is rounded on its own, so the
 // result for a factor g equals fl(g * t) added to the buffer afterwards.
 template <typename Tw, typename Tx, typename Tg>
@@ -591,7 +594,7 @@ __global__ __launch_bounds__(kThreads) void k_grad(const Tile *__restrict__ tile
                                                    const Scalars *__restrict__ sc,
                                                    const CallParams *__restrict__ call,
                                                    const char *__restrict__ ws, float inv_sx,
-                                                   int accumulate, int set_sum, int n) {
+                                                   int accumulate, int use_w, int set_sum, int n) {
 #pragma clang fp contract(off)
   __shared__ __attribute__((aligned(16))) float tile[kPrepTile * kPrepPitch];
   if (set_sum && blockIdx.x == 0) {     // the set total (the values are final)
@@ -620,7 +623,7 @@ __global__ __launch_bounds__(kThreads) void k_grad(const Tile *__restrict__ tile
       const int q = threadIdx.x + k * kThreads;
       const int r = q / (kPrepTile / 8), c = (q % (kPrepTile / 8)) * 8;
       const size_t o = size_t(r0 + r) * d.cols + c0 + c;
-      ld8(w + o, wv[k]);
+      if (use_w) ld8(w + o, wv[k]);
       if (accumulate) ld8(g + o, old[k]);
     }
   } else {
@@ -630,7 +633,7 @@ __global__ __launch_bounds__(kThreads) void k_grad(const Tile *__restrict__ tile
       const int r = q / (kPrepTile / 8), c = (q % (kPrepTile / 8)) * 8;
       const int nv = (r0 + r < rlim) ? max(0, min(8, clim - (c0 + c))) : 0;
       const size_t o = size_t(r0 + r) * d.cols + c0 + c;
-      get8(w + o, nv, wv[k]);
+      if (use_w) get8(w + o, nv, wv[k]);
       if (accumulate) get8(g + o, nv, old[k]);
     }
   }
@@ -656,7 +659,7 @@ __global__ __launch_bounds__(kThreads) void k_grad(const Tile *__restrict__ tile
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const float p = d.tall ? tile[(c + j) * kPrepPitch + r] : tile[r * kPrepPitch + c + j];
-      const float tj = s1 * p - s2 * wv[k][j];
+      const float tj = use_w ? s1 * p - s2 * wv[k][j] : s1 * p;
       v[j] = gs * tj;
       if constexpr (sizeof(Tg) == 2) v[j] = to_f(from_f<Tg>(v[j]));   // u rounded to bf16
     }
@@ -873,12 +876,13 @@ void launch_grad(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev
   const CallParams *call = reinterpret_cast<const CallParams *>(ws + p.off_call);
   const float inv_sx = 1.0f / (std::is_same<Tx, float>::value ? 1.0f : kScaleX16);
   const int acc = (p.flags & SLORR_ACCUMULATE) ? 1 : 0;
+  const int use_w = p.kind == SLORR_HOYER ? 1 : 0;
   if (p.grad_dtype == SLORR_BF16)
     go(k_grad<Tw, Tx, bf16_t>, dim3(l.grid), dim3(kThreads), s, ev, tiles, mats, dyn, sc, call, ws, inv_sx, acc,
-       l.set_sum, p.n);
+       use_w, l.set_sum, p.n);
   else
     go(k_grad<Tw, Tx, float>, dim3(l.grid), dim3(kThreads), s, ev, tiles, mats, dyn, sc, call, ws, inv_sx, acc,
-       l.set_sum, p.n);
+       use_w, l.set_sum, p.n);
 }
 
 template <typename Tw, typename Tx>
