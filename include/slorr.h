@@ -72,7 +72,8 @@ typedef enum { SLORR_HOYER = 0, SLORR_NUCLEAR = 1 } slorr_kind_t;
 /* Storage type of the weights. F32: the iteration holds every value as two
  * scaled fp16 numbers (23 to 24 significand bits together) and forms products
  * as three fp16 MFMAs with fp32 accumulation; with an explicit coefficient
- * table whose iterates may leave fp16's range it runs on fp32 MFMA.
+ * table whose iterates may leave fp16's range, or bf16 gradients, it runs on
+ * fp32 MFMA.
  * BF16: the iteration runs on fp16 MFMA operands with power-of-two scaling and
  * fp32 accumulation; norms and traces are accumulated in fp32 or wider. */
 typedef enum { SLORR_F32 = 0, SLORR_BF16 = 1 } slorr_dtype_t;
@@ -309,7 +310,8 @@ typedef struct {
   int64_t gemm_tiles;      /* output tiles over all GEMM launches of one call        */
   double paper_flops;      /* T * sum_i (4 P_i^2 Q_i + 2 P_i^3) (Sec. 3)             */
   double mfma_flops;       /* flops of the products per call (padded tiles; a product
-                              formed as three MFMAs counted once)                    */
+                              formed as three MFMAs counted once; as if every step
+                              ran by itself)                                         */
   double weight_bytes;     /* sum_i rows_i * cols_i * sizeof(dtype)                  */
   size_t workspace_bytes;
 } slorr_plan_info_t;

@@ -542,16 +542,29 @@ __global__ __launch_bounds__(kThreads) void k_gram_reduce(const Tile *__restrict
   char *A = ws + d.a;
   const int m0 = e.tm * kTile + stripe * R, n0 = e.tn * kTile;
   const float *src = gpart + size_t(e.slot) * (kTile * kTile) + stripe * R * kTile;
-  for (int q = threadIdx.x; q < R * kTile / 4; q += kThreads) {
-    float4v acc = reinterpret_cast<const float4v *>(src)[q];
-    for (int s = 1; s < e.parts; ++s) {
-      const float4v v = reinterpret_cast<const float4v *>(src + size_t(s) * (kTile * kTile))[q];
+  // all of a thread's pieces of several parts are in flight together (with 4
+  // stripes per tile and a part after the other: 12.8 us a launch on ResNet-18 in
+  // fp32, 61 tiles of up to 8 parts; its call 653 -> 629 us)
+  constexpr int NQ = R * kTile / 4 / kThreads;
+  static_assert(NQ * kThreads * 4 == R * kTile, "reduce task split");
+  float4v acc[NQ];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] += v[j];
+  for (int k = 0; k < NQ; ++k) acc[k] = reinterpret_cast<const float4v *>(src)[threadIdx.x + k * kThreads];
+#pragma unroll 4
+  for (int s = 1; s < e.parts; ++s) {
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+      const float4v v =
+          reinterpret_cast<const float4v *>(src + size_t(s) * (kTile * kTile))[threadIdx.x + k * kThreads];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[k][j] += v[j];
     }
-    const int r = (4 * q) / kTile, c = (4 * q) % kTile;
+  }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) t[r][c + j] = alpha * acc[j];
+  for (int k = 0; k < NQ; ++k) {
+    const int q = threadIdx.x + k * kThreads, r = (4 * q) / kTile, c = (4 * q) % kTile;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[r][c + j] = alpha * acc[k][j];
   }
   __syncthreads();
   const bool diag = e.tm == e.tn;

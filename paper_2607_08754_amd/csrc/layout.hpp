@@ -19,7 +19,7 @@ constexpr int kChunk = 32768;    // elements per block of the decoupled-update k
 constexpr int kThreads = 256;    // threads per block of the non-GEMM kernels
 constexpr int kXcds = 8;         // XCDs of an MI355X; workgroup b runs on XCD b % 8
 constexpr int kCus = 256;        // compute units of an MI355X
-constexpr int kRedStripes = 4;   // split-K Gram reduce: blocks (row stripes) per tile
+constexpr int kRedStripes = 8;   // split-K Gram reduce: blocks (row stripes) per tile
 
 // Power-of-two operand scales of the fp16 iterate (bf16 weights) and of the
 // split iterate (fp32 weights: two fp16 numbers per value). With the

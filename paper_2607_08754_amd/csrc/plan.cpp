@@ -25,8 +25,8 @@ constexpr int64_t kMinGramUnits = 2 * kCus; // Gram blocks wanted per launch (tw
 constexpr int kMaxGramParts = 16;           // k parts per Gram tile at most
 // split only Gram tiles this many k-slabs long, into parts of at least this
 // many slabs: fp16 slabs (64 values of k) are bound by their load latency
-// (about 0.7 us on a 128-tile), fp32 slabs (32 values) by the fp32 MFMA rate
-// (about 1.7 us), and a reduce launch costs about 7 us
+// (about 0.7 us on a 128-tile), fp32 slabs (32 values) by their MFMAs (0.75 us
+// in split form, 1.7 us on fp32 MFMA), and a reduce launch costs about 7 us
 constexpr int kMinSplitSlabs16 = 32, kMinPartSlabs16 = 8;
 // chained steps 1 and 2: the built-in table they were measured with, and the
 // gain in work from which they pay
@@ -337,7 +337,7 @@ void build_plan(Plan &p) {
   // ViT-Ti (144, 480) 228 -> 213 -> 203. With up to four per CU: ViT-S (288, 1008)
   // 487 -> 501 -> 512.
   p.gram64 = p.pp64 = TileRange{};
-  if (scaled) {
+  if (scaled && !p.lean) {
     int64_t tiles = 0;
     std::vector<Job> jobs;
     for (int i : order) {
@@ -554,6 +554,13 @@ void build_plan(Plan &p) {
     else off = with;
   }
   p.ws_bytes = off;
+  // a set that fits the static scratch without the 64-tile lists goes without
+  const size_t lists = sizeof(Tile) * size_t(p.gram64.count + p.pp64.count);
+  if (lists && off > size_t(SLORR_SCRATCH_BYTES) && off - lists - 256 <= size_t(SLORR_SCRATCH_BYTES)) {
+    p.lean = true;
+    build_plan(p);                            // (with the table built above)
+    return;
+  }
   // host image of the table region, for the entry point that allocates nothing
   p.image.assign(p.off_scal, 0);
   if (p.n) std::memcpy(p.image.data() + p.off_mats, p.mats.data(), sizeof(MatDesc) * p.n);
@@ -631,10 +638,17 @@ void build_plan(Plan &p) {
       g.cfg = g.run_cfg = kCfg128;
       g.run_first = g.tile_first;
       g.run_grid = g.grid;
+      // one part per tile: the tiles are stored whole, the reduce launch would
+      // copy (ViT-S in fp32, 288 tiles: 1136 -> 1096 us a call)
+      const bool whole = p.gram_parts == p.gred.count;
+      if (whole) {
+        g.run_first = p.gram[kCfg128].first;
+        g.run_grid = p.gram[kCfg128].count;
+      }
       p.launches.push_back(g);                // fp32 partials
       Launch l = plain(Op::GramReduce, p.gred.count * kRedStripes, p.gred.first);
       l.alpha = g.alpha;
-      if (chain2 || p.short_set) l.run = kNothing;
+      if (chain2 || p.short_set || whole) l.run = kNothing;
       p.launches.push_back(l);
     } else {
       gemm(Op::Gram, p.gram, g);

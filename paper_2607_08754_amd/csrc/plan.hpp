@@ -98,6 +98,7 @@ struct Plan {
   TileRange gram64, pp64;              // the symmetric outputs as 64-tiles (empty: not used)
   TileRange gsplit, gred;              // split-K Gram: part entries, reduce entries
   bool chained = false;                // steps 1 and 2 run on the Gram matrix
+  bool lean = false;                   // no 64-tile lists
   bool short_set = false;              // one launch per step (k_short)
   int32_t gram_parts = 0;              // fp32 partial tiles in the workspace
   int32_t trace_slots = 0;             // one per update tile

@@ -119,6 +119,10 @@ int main() {
     if ((l.op == Op::Gram || l.op == Op::Poly) && r64.count) {
       if (l.run_cfg != kCfg64 || l.run_first != r64.first || l.run_grid != r64.count || l.cfg != kCfg128)
         fail("64-tile run list", l.cfg, l.run_cfg, l.run_grid);
+    } else if (l.op == Op::Gram && p.gsplit.count && p.gram_parts == p.gred.count) {
+      // one part per tile: the whole tiles
+      if (l.run_cfg != kCfg128 || l.run_first != p.gram[kCfg128].first || l.run_grid != p.gram[kCfg128].count)
+        fail("whole Gram tiles", l.run_cfg, l.run_first, l.run_grid);
     } else if (l.op == Op::Gram || l.op == Op::Poly) {
       if (l.run_cfg != l.cfg || l.run_first != l.tile_first || l.run_grid != l.grid) fail("Gram / poly run list", l.cfg, l.run_cfg, 0);
     } else if (l.op == Op::Update || l.op == Op::Last) {
@@ -157,7 +161,8 @@ int main() {
         symmetric(l);
         x[1] = nan;
       } else if (l.op == Op::Gram) {
-        (p.gsplit.count ? part : pp[kPpA]) = (p.gsplit.count ? 1.0 : double(l.alpha)) * x[l.xin] * x[l.xin];
+        const bool parts = p.gsplit.count && p.gram_parts != p.gred.count;
+        (parts ? part : pp[kPpA]) = (parts ? 1.0 : double(l.alpha)) * x[l.xin] * x[l.xin];
       } else if (l.op == Op::GramReduce && l.run != kNothing) {
         pp[kPpA] = l.alpha * part;
       } else if (l.op == Op::Poly) {
