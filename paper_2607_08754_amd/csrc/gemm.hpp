@@ -52,7 +52,7 @@ struct Mfma {
   }
 };
 
-enum GemmMode { kGram = 0, kPoly = 1, kUpdate = 2, kLast = 3, kSym = 4 };
+enum GemmMode { kGram = 0, kPoly = 1, kUpdate = 2, kLast = 3 };
 
 struct GemmArgs {
   const Tile *tiles;
@@ -70,7 +70,6 @@ struct GemmArgs {
   float *gpart;   // Gram parts (split K): fp32 partial tiles, BM x BN each, at tile.slot
   int quads;      // k_upd256 over a list of 128-tiles: a trace slot per 128 x 128 quadrant
                   // (slot of the first, Pp / 128 slots from one column of quadrants to the next)
-  int pl, pr, po; // P x P buffers (PpBuf): Poly's A (pl) and B (po); kSym: po = alpha pl pr
   int ntiles;     // entries of the tile list (a persistent kernel's grid can be smaller)
 };
 

@@ -2,8 +2,8 @@
 // for both storage forms of the iterate (device code, included by kernels.hip
 // after gemm.hpp, inside namespace slorr):
 //
-//   k_tile    one output tile per block, NS LDS stages (Gram, poly, products of
-//             two symmetric matrices; update on 128-tiles)
+//   k_tile    one output tile per block, NS LDS stages (Gram, poly; update on
+//             128-tiles)
 //   k_short   a whole step of a set of short matrices
 //   k_upd256  the persistent 256 x 256 update kernel
 //
@@ -232,17 +232,16 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_tile(GemmArgs args) {
   using S = TileShape<T, BM, BN, WGM, WGN, NS, MODE>;
   constexpr int PL = S::PL, BK = S::BK, FM = S::FM, FN = S::FN, WTM = S::WTM, WTN = S::WTN;
   constexpr int V = 16 / int(sizeof(T));            // storage units per 16 bytes
-  constexpr bool SYM = MODE == kGram || MODE == kPoly || MODE == kSym;
+  constexpr bool SYM = MODE == kGram || MODE == kPoly;
   __shared__ __attribute__((aligned(16))) char smem[S::kSmem];
 
   const Tile tile = args.tiles[blockIdx.x];
   if (tile.mat < 0) return;      // padding of the XCD-ordered list (whole block)
   // a Gram part (split K) covers k in [k0, k1) and stores its raw fp32 partial
   const bool part = MODE == kGram && tile.k1 > 0;
-  // diagonal tile of a symmetric output; of a matrix with itself: one row
-  // panel, read for both operands
+  // diagonal tile of a product of a matrix with itself: one row panel, read
+  // for both operands
   const bool diag = SYM && tile.tm == tile.tn;
-  const bool same = diag && MODE != kSym;
   const MatDesc d = args.mats[tile.mat];
   const int m0 = tile.tm * BM, n0 = tile.tn * BN;
   // X buffer offsets read from the table in memory (a run-time index into the
@@ -251,7 +250,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_tile(GemmArgs args) {
   char *Xn = args.ws + args.mats[tile.mat].x[args.xout];
   // (their order in memory is x[0], x[1], x[2], a, b: see MatDesc)
   char *Am = args.ws + d.a, *Bm = args.ws + d.b;
-  auto pp_buf = [&](int id) { return id == kPpA ? Am : id == kPpB ? Bm : args.ws + args.mats[tile.mat].x[1]; };
   const char *Ap, *Bp;
   int lda, ldb, K;
   if (MODE == kGram) {                               // A = X X^T
@@ -259,11 +257,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_tile(GemmArgs args) {
     lda = ldb = d.Qp;
     K = part ? tile.k1 - tile.k0 : d.Qp;
   } else if (MODE == kPoly) {                        // A A
-    Ap = Bp = pp_buf(args.pl);
-    lda = ldb = K = d.Pp;
-  } else if (MODE == kSym) {                         // L R, R symmetric: its rows are its columns
-    Ap = pp_buf(args.pl);
-    Bp = pp_buf(args.pr);
+    Ap = Bp = Am;
     lda = ldb = K = d.Pp;
   } else {                                           // B X or A X
     Ap = args.use_a ? Am : Bm;
@@ -307,7 +301,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_tile(GemmArgs args) {
       for (int i = 0; i < S::kLoadsB; ++i)
         buffer_load_lds16(rb, voff, (uint32_t(k0) + uint32_t(i * S::RPX * S::kFW)) * uint32_t(ldb) * uint32_t(sizeof(T)),
                           sB + (wave + i * S::kFW) * 1024);
-    } else if (!same) {
+    } else if (!diag) {
       fetch_rows(Bp, bbytes, ldb, n0, k0, sB);
     }
   };
@@ -350,13 +344,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_tile(GemmArgs args) {
     if (q < nk) dload(q * BK, q);
   for (int kt = 0, st = 0; kt < nk; ++kt, st = st + 1 == NS ? 0 : st + 1) {
     const int ahead = min(NS - 2, nk - 1 - kt);      // slabs fetched after slab kt so far
-    if (same) vm_wait_slabs<S::kLoadsA, NS - 2>(ahead);
+    if (diag) vm_wait_slabs<S::kLoadsA, NS - 2>(ahead);
     else vm_wait_slabs<S::kLoadsA + S::kLoadsB, NS - 2>(ahead);
     __syncthreads();                 // slab kt is published; slab kt - 1 is done
     if (kt + NS - 1 < nk) dload((kt + NS - 1) * BK, st == 0 ? NS - 1 : st - 1);
     const char *sA = smem + st * S::kStage;
     if (S::kDiagSq && diag) diag_slab(sA);
-    compute_slab<T, FM, FN, S::KN, S::KNP>(acc, sA, same ? sA : sA + S::kStageA, wm * WTM, wn * WTN, lane);
+    compute_slab<T, FM, FN, S::KN, S::KNP>(acc, sA, diag ? sA : sA + S::kStageA, wm * WTM, wn * WTN, lane);
     // instruction order: the first k-step's fragment reads, then the MFMAs of
     // a step with the next step's reads spread among them (as in k_upd256).
     // ViT-Ti 234 -> 227 us a call, ViT-S in fp32 1092 -> 1077, ResNet-18 in fp32
@@ -406,7 +400,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_tile(GemmArgs args) {
   // Symmetric outputs are stored exactly symmetric: off-diagonal tiles also
   // store their transpose; a diagonal tile stores its upper triangle and the
   // transpose of it below the diagonal.
-  char *Sym = MODE == kGram ? Am : pp_buf(args.po);
+  char *Sym = MODE == kGram ? Am : Bm;
   double tsum = 0.0;
   constexpr int NTASK = 32 * 8 / 64;                // 8-column pieces per lane and block
   // poly: A's values of the b A term; last: the X_0' values of the trace. A

@@ -801,27 +801,6 @@ void launch_tile(Op op, dim3 grid, const GemmArgs &a, hipStream_t s, const EvPai
   }
 }
 
-// A symmetric product of the chained steps.
-template <typename Tx>
-void launch_sym(const Plan &p, const Launch &l, GemmArgs a, const Tile *tiles, hipStream_t s, const EvPair *ev) {
-  const int cfg = p.pp64.count ? kCfg64 : p.pp[kCfg256].count ? kCfg256 : kCfg128;
-  const TileRange r = cfg == kCfg64 ? p.pp64 : p.pp[cfg];
-  a.tiles = tiles + r.first;
-  a.ntiles = r.count;
-  a.alpha = l.sym_alpha;
-  a.kap = 0;
-  EvPair first{};
-  if (ev && l.run == kSymBefore) {       // the pair spans both kernels
-    first.start = ev->start;
-    ev = &first;
-  }
-  const dim3 grid(r.count);
-  if (cfg == kCfg64) go(k_tile<Tx, kSym, kSmallTile, kSmallTile, 2, 1, 4>, grid, dim3(128), s, ev, a);
-  else if (cfg == kCfg256) go(k_tile<Tx, kSym, kBigTile, kBigTile, 2, 4, 2>, grid, dim3(512), s, ev, a);
-  else if (r.count <= kCus) go(k_tile<Tx, kSym, kTile, kTile, 2, 2, 4>, grid, dim3(256), s, ev, a);
-  else go(k_tile<Tx, kSym, kTile, kTile, 2, 2, 2>, grid, dim3(256), s, ev, a);
-}
-
 // A step of a set of short matrices (Gram: X_0's partials). Partials pass
 // between launches in two buffers; step t, known by the buffer it reads X from
 // (0, then 1 and 2 in turn), reads buffer t mod 2. The slices of step 1 go from
@@ -927,7 +906,6 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
       case Op::Update:
       case Op::Last: {
         GemmArgs a;
-        EvPair second{};
         a.tiles = tiles + l.run_first;
         a.mats = mats;
         a.dyn = dyn;
@@ -947,9 +925,6 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
         a.gpart = reinterpret_cast<float *>(ws + p.off_gpart);
         a.quads = l.run_cfg != l.cfg;
         a.ntiles = l.run_grid;
-        a.pl = l.pl;
-        a.pr = l.pr;
-        a.po = l.po;
         if (l.run == kNothing) {
           no_launch(s, ev);
           break;
@@ -958,17 +933,6 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
           if constexpr (!std::is_same<Tx, float>::value) launch_short<Tx>(p, l, a, ws, s, ev);
           else throw HipError("no short-matrix steps on fp32 MFMA");
           break;
-        }
-        if (l.run) {
-          if constexpr (!std::is_same<Tx, float>::value) launch_sym<Tx>(p, l, a, tiles, s, ev);
-          else throw HipError("no chained steps on fp32 MFMA");
-          if (l.run == kSymInstead) break;
-          if (ev) {
-            second.stop = ev->stop;
-            ev = &second;
-          }
-          a.xin = 0;                               // X_2 = Z X_0
-          a.use_a = 1;
         }
         const dim3 g(l.run_grid);
         if constexpr (std::is_same<Tx, float>::value) {

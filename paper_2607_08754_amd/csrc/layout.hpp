@@ -32,10 +32,6 @@ constexpr float kScaleX16 = 4096.0f;
 constexpr float kScaleA16 = 4096.0f;
 constexpr float kScaleB16 = 1024.0f;
 
-// The P x P buffers of a matrix: A, B, and the first P x P values of x[1],
-// which the chained first two steps leave free (see Chain in plan.hpp).
-enum PpBuf : int32_t { kPpA = 0, kPpB = 1, kPpX1 = 2 };
-
 struct MatDesc {
   int32_t rows, cols;          // original shape
   int32_t P, Q, Pp, Qp;        // canonical and padded canonical shape

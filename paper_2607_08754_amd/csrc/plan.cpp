@@ -28,11 +28,6 @@ constexpr int kMaxGramParts = 16;           // k parts per Gram tile at most
 // (about 0.7 us on a 128-tile), fp32 slabs (32 values) by their MFMAs (0.75 us
 // in split form, 1.7 us on fp32 MFMA), and a reduce launch costs about 7 us
 constexpr int kMinSplitSlabs16 = 32, kMinPartSlabs16 = 8;
-// chained steps 1 and 2: the built-in table they were measured with, and the
-// gain in work from which they pay
-constexpr int kMinChainIters = 6;
-constexpr double kChainEll = 1e-3, kChainSafety = 0.01;
-constexpr double kChainGain = 1.5, kChainGainFew = 2.0;
 // sets of short matrices: slices per matrix, and Gram partials read per step
 constexpr int kMaxShortSlices = 8, kMaxShortReads = 1600;
 constexpr int64_t kMaxSmallTiles = 2 * kCus;   // 64-tiles of a launch
@@ -63,8 +58,7 @@ int32_t xbuf(int t) { return t == 0 ? 0 : 1 + ((t - 1) & 1); }
 // first step). The scales (4096, 4096, 1024) leave fp16 (65504) room for
 // u <= 3.5 and |B_ij| <= 58. The built-in schedules stay below 2.1 and 9;
 // an explicit table that may exceed the range keeps the fp32 MFMA kernels.
-// `bounds` receives the steps' bounds on |B_ij|.
-bool split_fits(const std::vector<double> &coeffs, int iters, std::vector<double> *bounds = nullptr) {
+bool split_fits(const std::vector<double> &coeffs, int iters) {
   constexpr double kMaxX = 3.5, kMaxB = 58.0;
   double u = 1.0;
   for (int t = 0; t < iters; ++t) {
@@ -74,7 +68,6 @@ bool split_fits(const std::vector<double> &coeffs, int iters, std::vector<double
     double gmax = std::max(g(0.0), g(z1));
     if (c != 0.0 && -b / (2 * c) > 0.0 && -b / (2 * c) < z1) gmax = std::max(gmax, g(-b / (2 * c)));
     gmax *= t == 0 ? 2.0 : 1.0;
-    if (bounds) bounds->push_back(gmax);
     if (gmax > kMaxB) return false;
     // extrema of p on [0, u]: a + 3 b z + 5 c z^2 = 0
     double pmax = u * g(z1);
@@ -113,8 +106,7 @@ void build_plan(Plan &p) {
   if (p.grad_dtype != SLORR_F32 && p.grad_dtype != SLORR_BF16)
     throw std::domain_error("unsupported gradient dtype");
   if (!(p.safety >= 0.0 && p.safety < 1.0)) throw std::invalid_argument("safety must be in [0, 1)");
-  const bool built_in = p.coeffs.empty();
-  if (built_in) {
+  if (p.coeffs.empty()) {
     // the built-in schedule, stabilised: every step but the last evaluates its
     // polynomial at x / (1 + safety), i.e. (a / s, b / s^3, c / s^5), so that a
     // singular value the iterate's rounding pushes slightly past the step's
@@ -449,44 +441,6 @@ void build_plan(Plan &p) {
   p.short_set &= reads <= kMaxShortReads;
   for (int t = 0; t < T; ++t) p.short_set &= p.coeffs[3 * t + 2] != 0.0;
 
-  // Steps 1 and 2 on the Gram matrix: X_2 = B_2 B_1 X_0 is formed without X_1,
-  // whose Gram matrix is B_1 A B_1:
-  //   A, B_1 as ever;  Y = A B_1;  A' = Y B_1;  B_2 from A';  Z = B_2 B_1;  X_2 = Z X_0
-  // All factors are polynomials of A, so every product is symmetric (only its
-  // upper triangle is formed). Three P x P products (3 P^2 (P + 128) with the
-  // whole diagonal tiles) take the place of one update and one Gram product
-  // (3 P^2 Q), at a lower rate. Chained when that work is kChainGain times
-  // less; per call, step by step -> chained, at work ratio:
-  //   1.5 LLM-135M 2984 -> 2992 us    1.6 LLM-560M 15.72 -> 15.42 ms
-  //   2.6 ViT-B/16 1953 -> 1860 us, in fp32 5036 -> 4722   2.7 ViT-L/16 7.83 -> 7.40 ms
-  //   2.3 ViT-S 539 -> 524 us, in fp32 1230 -> 1183    7 ResNet-18 in fp32 768 -> 744 us
-  // and kChainGainFew where a launch has at most one tile per CU, whose time
-  // is latency: 3.1 the odd shapes 638 -> 607 us, 1.6 ViT-Ti (144 tiles) 244 ->
-  // 249.
-  // Precision: X_1's rounding goes, that of A' and Z comes; what A' lacks is
-  // absolute and small against the matrix's norm, and B_2 is nearly constant
-  // where it matters. Gradients' errors against 64 bits: ViT-B/16 1.96e-3 ->
-  // 1.83e-3, in fp32 2.95e-6 -> 2.74e-6, odd shapes 2.88e-3 -> 2.81e-3, a spectrum
-  // of three decades (emulated) 9.5e-3 -> 4.7e-3. Chaining later steps, more
-  // than two, or tables of fewer than 6 steps loses precision (steps 3 and 4 of
-  // a square matrix: 1.8e-3 -> 7.7e-3), so it is tied to the default table.
-  p.chained = false;
-  double zbound = 0.0;
-  {
-    std::vector<double> bounds;
-    const bool table = built_in && p.degree == 5 && T >= kMinChainIters && p.ell == kChainEll && p.safety == kChainSafety;
-    if (table && scaled && split_fits(p.coeffs, T, &bounds)) {
-      double saved = 0.0, added = 0.0;
-      for (int i : order) {
-        const MatDesc &d = p.mats[i];
-        saved += 3.0 * d.Pp * d.Pp * d.Qp;
-        added += 3.0 * d.Pp * d.Pp * (d.Pp + kTile);
-      }
-      zbound = bounds[0] * bounds[1];
-      const TileRange &r = p.pp[p.pp[kCfg256].count ? kCfg256 : kCfg128];
-      p.chained = !order.empty() && !p.short_set && saved >= (r.count > kCus ? kChainGain : kChainGainFew) * added;
-    }
-  }
   // canonical 64 x 64 tiles: the norm (one partial slot each, contiguous per
   // matrix in canonical row-major tile order, which is the order they are
   // summed in), the normalisation and the gradient; element runs of the
@@ -605,22 +559,11 @@ void build_plan(Plan &p) {
       p.launches.push_back(l);
     }
   };
-  auto sym = [](Launch &l, PpBuf left, PpBuf right, PpBuf out, double alpha) {
-    l.run = kSymInstead;
-    l.pl = left;
-    l.pr = right;
-    l.po = out;
-    l.sym_alpha = float(alpha);
-  };
-  // the scale of Z, of which |Z_ij| <= zbound: fp16's range, as for B
-  double sz = sb;
-  while (p.chained && sz * zbound > 60000.0) sz *= 0.5;
   const float prod = float(1.0 / sb);           // (B_s X_s) / s_b keeps X's scale
   for (int t = 0; t < T; ++t) {
     const double a = p.coeffs[3 * t], b = p.coeffs[3 * t + 1], c = p.coeffs[3 * t + 2];
     const int32_t xi = xbuf(t), xo = xbuf(t + 1);
     const bool quintic = c != 0.0;
-    const bool chain1 = p.chained && t == 0, chain2 = p.chained && t == 1;
     // the first step runs on X_0' = W / 2^e: its coefficients are scaled per
     // matrix by kappa, kappa^3, kappa^5 (kappa = 2^e / (f + eps), read by the
     // kernels), so that it computes p_1(X_0) with X_0 = kappa X_0'
@@ -630,7 +573,6 @@ void build_plan(Plan &p) {
     g.xin = xi;
     g.alpha = float(sa / (double(sx) * sx));
     if (p.short_set) g.run = t == 0 ? kRunShort : kNothing;
-    if (chain2) sym(g, kPpX1, kPpB, kPpA, 1.0 / sb);            // A' = Y B_1
     if (p.gsplit.count) {
       g.op = Op::Gram;
       g.grid = p.gsplit.count;
@@ -648,7 +590,7 @@ void build_plan(Plan &p) {
       p.launches.push_back(g);                // fp32 partials
       Launch l = plain(Op::GramReduce, p.gred.count * kRedStripes, p.gred.first);
       l.alpha = g.alpha;
-      if (chain2 || p.short_set || whole) l.run = kNothing;
+      if (p.short_set || whole) l.run = kNothing;
       p.launches.push_back(l);
     } else {
       gemm(Op::Gram, p.gram, g);
@@ -663,9 +605,7 @@ void build_plan(Plan &p) {
       l.alpha = float(double(sb) * c / (double(sa) * sa));
       l.beta = float(double(sb) * b / sa);
       l.gamma = float(double(sb) * a);
-      l.pl = kPpA;
       if (p.short_set) l.run = kNothing;
-      l.po = chain2 ? kPpX1 : kPpB;                             // B_2 in Y's place
       gemm(Op::Poly, p.pp, l);
       // X'_s = (B_s X_s) / s_b
       Launch u{};
@@ -680,12 +620,6 @@ void build_plan(Plan &p) {
         u.poly_beta = l.beta;
         u.poly_gamma = l.gamma;
         u.poly_kap = kap;
-      }
-      if (chain1) sym(u, kPpA, kPpB, kPpX1, 1.0 / sb);          // Y = A B_1
-      if (chain2) {                                             // Z = B_2 B_1, X_2 = Z X_0
-        sym(u, kPpX1, kPpB, kPpA, sz / (double(sb) * sb));
-        u.run = kSymBefore;
-        u.alpha = float(1.0 / sz);
       }
       gemm(op, p.pq, u);
     } else {

@@ -51,21 +51,17 @@ struct Launch {
   int32_t kap;         // first step: coefficients scaled per matrix by powers of kappa
   int32_t set_sum;     // gradient launch: its first block also writes the set total
   float alpha, beta, gamma;  // epilogue coefficients
-  // what the launch runs where it differs from the above (chained steps 1
-  // and 2, sets of short matrices: see build_plan)
+  // what the launch runs where it differs from the above (sets of short
+  // matrices, split Gram products of one part per tile: see build_plan)
   int32_t run;         // Run
-  int32_t pl, pr, po;  // PpBuf: Poly's A and B; the symmetric product's operands and output
-  float sym_alpha;     // the symmetric product's factor
   float gram_alpha, poly_alpha, poly_beta, poly_gamma;  // kRunShort: those of the step's Gram
   int32_t poly_kap;                                     // and poly products
 };
 
 enum Run : int32_t {
   kRunOwn = 0,
-  kSymInstead = 1,     // runs the symmetric product po = sym_alpha pl pr in its place
-  kSymBefore = 2,      // runs it before its own kernel, an update from x[0] with the operand A
-  kNothing = 3,        // runs nothing
-  kRunShort = 4        // runs k_short: Gram X_0's partials, update and last the whole step
+  kNothing = 1,        // runs nothing
+  kRunShort = 2        // runs k_short: Gram X_0's partials, update and last the whole step
 };
 
 struct TileRange {
@@ -97,7 +93,6 @@ struct Plan {
   TileRange upd;                       // the 128-tile update list as 256-tiles (empty: not used)
   TileRange gram64, pp64;              // the symmetric outputs as 64-tiles (empty: not used)
   TileRange gsplit, gred;              // split-K Gram: part entries, reduce entries
-  bool chained = false;                // steps 1 and 2 run on the Gram matrix
   bool lean = false;                   // no 64-tile lists
   bool short_set = false;              // one launch per step (k_short)
   int32_t gram_parts = 0;              // fp32 partial tiles in the workspace

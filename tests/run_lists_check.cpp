@@ -140,12 +140,9 @@ int main() {
   for (double x0 : {0.02, 0.3, 0.8}) {
     if (p.prep.count == 0) break;             // no matrix with elements
     const double nan = std::nan(""), kappa = 1.25;
-    double x[3] = {sx * x0, nan, nan}, pp[3] = {nan, nan, nan}, part = nan;
-    double &scratch = pp[kPpX1];              // the same memory as x[1]
-    auto symmetric = [&](const Launch &l) { pp[l.po] = double(l.sym_alpha) * pp[l.pl] * pp[l.pr]; };
+    double x[3] = {sx * x0, nan, nan}, A = nan, B = nan, part = nan;
     for (const Launch &l : p.launches) {
       const double k = l.kap ? kappa : 1.0;
-      if ((l.run == kSymInstead || l.run == kSymBefore) && !p.chained) fail("chain flag", l.run, int(l.op), 0);
       if (l.run == kRunShort && !p.short_set) fail("short-set flag", l.run, int(l.op), 0);
       if (l.run == kNothing) {
         continue;
@@ -153,32 +150,21 @@ int main() {
         const int last = iters == 0 ? 0 : 1 + ((iters - 1) & 1);
         double &X = x[l.op == Op::Gram || l.xin == 0 ? 0 : last];
         if (l.op != Op::Gram) {
-          const double kp = l.poly_kap ? kappa : 1.0, k2 = kp * kp, A = l.gram_alpha * part;
-          x[last] = l.alpha * (l.poly_beta * k2 * kp * A + l.poly_alpha * k2 * k2 * kp * A * A + l.poly_gamma * kp) * X;
+          const double kp = l.poly_kap ? kappa : 1.0, k2 = kp * kp, G = l.gram_alpha * part;
+          x[last] = l.alpha * (l.poly_beta * k2 * kp * G + l.poly_alpha * k2 * k2 * kp * G * G + l.poly_gamma * kp) * X;
         }
         part = x[l.op == Op::Gram ? 0 : last] * x[l.op == Op::Gram ? 0 : last];
-      } else if (l.run == kSymInstead) {
-        symmetric(l);
-        x[1] = nan;
       } else if (l.op == Op::Gram) {
         const bool parts = p.gsplit.count && p.gram_parts != p.gred.count;
-        (parts ? part : pp[kPpA]) = (parts ? 1.0 : double(l.alpha)) * x[l.xin] * x[l.xin];
+        (parts ? part : A) = (parts ? 1.0 : double(l.alpha)) * x[l.xin] * x[l.xin];
       } else if (l.op == Op::GramReduce && l.run != kNothing) {
-        pp[kPpA] = l.alpha * part;
+        A = l.alpha * part;
       } else if (l.op == Op::Poly) {
-        const double A = pp[l.pl], k2 = k * k;
-        pp[l.po] = l.beta * k2 * k * A + l.alpha * k2 * k2 * k * A * A + l.gamma * k;
-        if (l.po == kPpX1) x[1] = nan;
+        const double k2 = k * k;
+        B = l.beta * k2 * k * A + l.alpha * k2 * k2 * k * A * A + l.gamma * k;
       } else if (l.op == Op::Update || l.op == Op::Last) {
-        int xin = l.xin, use_a = l.use_a;
-        if (l.run == kSymBefore) {
-          symmetric(l);
-          xin = 0;
-          use_a = 1;
-        }
-        const double v = double(l.alpha) * (use_a ? pp[kPpA] : pp[kPpB]) * x[xin];
-        x[l.xout] = l.fold ? v : l.beta * k * x[xin] + v * k * k * k;
-        if (l.xout == 1) scratch = nan;
+        const double v = double(l.alpha) * (l.use_a ? A : B) * x[l.xin];
+        x[l.xout] = l.fold ? v : l.beta * k * x[l.xin] + v * k * k * k;
       }
     }
     double want = kappa * x0;
@@ -190,7 +176,6 @@ int main() {
     if (!(std::fabs(got - want) <= 1e-4 * std::fabs(want) + 1e-6)) fail("schedule's value", int(1e6 * got), int(1e6 * want), int(100 * x0));
   }
   if (bad) return 1;
-  std::printf("OK split=%d run256=%d chained=%d short=%d small=%d%d\n", p.split ? 1 : 0, run, p.chained ? 1 : 0, p.short_set ? 1 : 0,
-              p.gram64.count > 0, p.pp64.count > 0);
+  std::printf("OK split=%d run256=%d short=%d small=%d%d\n", p.split ? 1 : 0, run, p.short_set ? 1 : 0, p.gram64.count > 0, p.pp64.count > 0);
   return 0;
 }

@@ -83,30 +83,6 @@ def test_split_needs_fp32_gradients(checker):
 
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
-def test_chain_rule(checker, dtype):
-    """Steps 1 and 2 on the Gram matrix: the default table of at least 6 steps,
-    1.5 times less work than step by step (2 times for few tiles)."""
-    def chained(*args, **kw):
-        return run(checker, *args, **kw)["chained"] == "1"
-
-    many = [(384, 1024)] * 48                                  # 288 tiles; work ratio 2
-    assert chained(many, dtype) and chained(many, dtype, iters=8)
-    assert not chained(many, dtype, iters=5)
-    assert chained([(384, 768)] * 48, dtype) and not chained([(384, 640)] * 48, dtype)     # 1.5, 1.25
-    assert chained([(384, 1024)] * 4, dtype) and not chained([(384, 896)] * 4, dtype)      # 24 tiles: 2, 1.75
-    assert chained([(128, 4096)] * 3, dtype)                   # with a split-K Gram product
-    assert chained([(512, 4096)] * 40, dtype)                  # Gram and update on 256-tiles
-    assert not chained([(0, 7), (0, 0)], dtype)
-    table = [15 / 8, -10 / 8, 3 / 8] * 6                       # an explicit table
-    assert not chained(many, dtype, coeffs=table)
-    assert run(checker, many, dtype, coeffs=[1.5, -0.5, 0.0] * 6)["chained"] == "0"
-
-
-def test_no_chain_on_fp32_mfma(checker):
-    assert run(checker, [(384, 1024)] * 48, F32, grad=BF16)["chained"] == "0"
-
-
-@pytest.mark.parametrize("dtype", [F32, BF16])
 def test_short_rule(checker, dtype):
     """One launch per step: every matrix at most 128 x 1024, quintic steps."""
     def short(*args, **kw):
