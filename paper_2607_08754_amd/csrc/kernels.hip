@@ -274,13 +274,15 @@ __device__ __forceinline__ void iter_ld8_stream(const char *x, size_t row, size_
 constexpr int kPrepPitch = kPrepTile + 4;
 
 // Loads canonical tile t of W into LDS: tile[r * kPrepPitch + c] holds the
-// canonical element (m0 + r, n0 + c) of W (W^T for tall W), 0 outside it.
+// canonical element (m0 + r, n0 + c) of W (W^T for tall W) times scale and
+// scale2, 0 outside it.
 // Full tiles read W non-temporally: no later launch of the schedule before
 // the gradient needs W, while the first Gram product reads the X_0' written
 // here, which then keeps its place in the caches (measured on ViT-B/16: the
 // Gram launches 3 us faster on average, the call about 10 us).
 template <typename Tw>
-__device__ __forceinline__ void stage_tile(float *tile, const Tile &t, const MatDesc &d, const Tw *w, float scale) {
+__device__ __forceinline__ void stage_tile(float *tile, const Tile &t, const MatDesc &d, const Tw *w, float scale,
+                                           float scale2) {
   const int m0 = t.tm * kPrepTile, n0 = t.tn * kPrepTile;
   // source rows of W covered by the tile: wide -> canonical rows m, tall -> canonical columns n
   const int r0 = d.tall ? n0 : m0, c0 = d.tall ? m0 : n0;
@@ -288,10 +290,10 @@ __device__ __forceinline__ void stage_tile(float *tile, const Tile &t, const Mat
   auto put = [&](int r, int c, const float (&v)[8]) {
     if (d.tall) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) tile[(c + j) * kPrepPitch + r] = v[j] * scale;
+      for (int j = 0; j < 8; ++j) tile[(c + j) * kPrepPitch + r] = v[j] * scale * scale2;
     } else {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) tile[r * kPrepPitch + c + j] = v[j] * scale;
+      for (int j = 0; j < 8; ++j) tile[r * kPrepPitch + c + j] = v[j] * scale * scale2;
     }
   };
   constexpr int kTasks = kPrepTile * kPrepTile / 8 / kThreads;
@@ -395,13 +397,18 @@ __global__ __launch_bounds__(kThreads) void k_norm_fin(const MatDesc *__restrict
     sc[i].sumsq = s;
     sc[i].f = f;
     sc[i].feps = fe;
+    sc[i].pexp = 0;
     if (fe > 0.0 && isfinite(fe)) {
       int e;
       const double m = frexp(fe, &e);      // fe = m 2^e, m in [0.5, 1)
       if (m == 0.5) --e;                   // fe is a power of two: 2^e = fe
       sc[i].kappa = ldexp(1.0, e) / fe;
       sc[i].two_e = ldexp(1.0, e);
-      sc[i].pscale = float(ldexp(double(sx), -e));
+      // in two factors where their product leaves fp32's range (with the scale
+      // 4096: norms below 2^-115)
+      const int k = ilogb(double(sx)) - e;
+      sc[i].pscale = float(ldexp(1.0, min(k, 127)));
+      sc[i].pexp = max(k - 127, 0);
     } else {
       // zero matrix: X_0 = 0 (value and gradient 0); NaN / Inf: propagate
       sc[i].kappa = fe > 0.0 ? 1.0 : 0.0;
@@ -424,8 +431,8 @@ __global__ __launch_bounds__(kThreads) void k_prep(const Tile *__restrict__ tile
   __shared__ __attribute__((aligned(16))) float tile[kPrepTile * kPrepPitch];
   const Tile t = tiles[blockIdx.x];
   const MatDesc d = mats[t.mat];
-  // a power of two: the scaling of W is exact
-  stage_tile(tile, t, d, static_cast<const Tw *>(dyn[t.mat].w), sc[t.mat].pscale);
+  // powers of two: the scaling of W is exact
+  stage_tile(tile, t, d, static_cast<const Tw *>(dyn[t.mat].w), sc[t.mat].pscale, ldexpf(1.0f, sc[t.mat].pexp));
   const int m0 = t.tm * kPrepTile, n0 = t.tn * kPrepTile;
   __syncthreads();
   for (int q = threadIdx.x; q < kPrepTile * kPrepTile / 8; q += kThreads) {

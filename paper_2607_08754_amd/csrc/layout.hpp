@@ -83,8 +83,8 @@ struct Scalars {
   double kappa;                // 2^e / (f + eps); 0 when f + eps == 0
   double two_e;                // 2^e: W = 2^e X_0' exactly, so the trace sum(W * P)
                                // is 2^e sum(X_0' * P) over the canonical buffers
-  float pscale;                // 2^-e times the iterate's scale: X_0 = W pscale
-  float pad;
+  float pscale;                // the iterate's scale times 2^-e, which X_0' multiplies W
+  int32_t pexp;                // by, is pscale 2^pexp (pexp > 0: beyond fp32's 2^127)
 };
 
 }  // namespace slorr

@@ -70,3 +70,25 @@ def test_table_outside_the_split_range():
     vals, grads, _ = run_gpu(arrs, "f32", "nuclear", 3, coeffs=table)
     refs = run_oracle(arrs, "f32", "nuclear", 3, table=table)
     compare(vals, grads, refs, "nuclear", "f32", label="outside the split range")
+
+
+@pytest.mark.parametrize("kind", ["hoyer", "nuclear"])
+def test_tiny_norms(kind):
+    """Norms down to 2^-125, down to the last bit of fp32's smallest numbers:
+    the iterate's scale times 2^-e exceeds fp32's range from 2^-115. The scaling
+    is by powers of two and so exact: bit for bit the results of the unscaled
+    weights (Hoyer's gradient grows by the inverse and leaves fp32: values)."""
+    shapes = [(100, 200), (300, 130), (384, 1536)]
+    # 8 significand bits, so that the scaled values are exact
+    arrs = [(np.round(gaussian(s, seed=23, std=1.0, dtype="f32", index=i) * 64) / 4096).astype(np.float32)
+            for i, s in enumerate(shapes)]
+    v0, g0, _ = run_gpu(arrs, "f32", kind, 6)
+    for k in (-100, -118, -126):
+        small = [np.ldexp(a, k).astype(np.float32) for a in arrs]
+        assert all(np.array_equal(np.ldexp(s.astype(np.float64), -k), a) for s, a in zip(small, arrs))
+        v1, g1, _ = run_gpu(small, "f32", kind, 6)
+        n = len(shapes)
+        assert np.array_equal(v1[:n], v0[:n] * (2.0 ** k if kind == "nuclear" else 1.0)), k
+        if kind == "nuclear":
+            for a, b in zip(g1, g0):
+                assert np.array_equal(a, b), k
