@@ -65,13 +65,32 @@ struct GemmArgs {
   int use_a;      // update operand is A (cubic step)
   int write_x;    // Last: store X_T (the gradient kernel reads it)
   int fold;       // Update / Last: a_t I is folded into the operand (no a X term)
-  int kap;        // first step: coefficients times powers of the matrix's kappa
+  int kap;        // coefficients per matrix (step_scale): kKappa in the first step, kRescale
+  int grow0, grow1;  // Launch::grow0, grow1
   float alpha, beta, gamma, inv_sx;
   float *gpart;   // Gram parts (split K): fp32 partial tiles, BM x BN each, at tile.slot
   int quads;      // k_upd256 over a list of 128-tiles: a trace slot per 128 x 128 quadrant
                   // (slot of the first, Pp / 128 slots from one column of quadrants to the next)
   int ntiles;     // entries of the tile list (a persistent kernel's grid can be smaller)
 };
+
+// The step's coefficients for the iterate as it is held: X_t = k X^_t, so that
+// X^' = m (a + b k^2 A^ + c k^4 A^^2) X^ with m = k over the next iterate's k.
+// First step: k = kappa 2^-h, all others 2^-h_t (see Scalars).
+enum KapBits { kKappa = 1, kRescale = 2 };
+struct StepScale {
+  double k2, m;
+};
+__device__ __forceinline__ StepScale step_scale(const GemmArgs &a, int mat) {
+  const Scalars &s = a.sc[mat];
+  double k = a.kap & kKappa ? s.kappa : 1.0, m = k;
+  if (a.kap & kRescale) {
+    const int h0 = max(0, s.shift - a.grow0), h1 = max(0, s.shift - a.grow1);
+    k = ldexp(k, -h0);
+    m = ldexp(m, h1 - h0);
+  }
+  return {k * k, m};
+}
 
 template <int BM, int BN, int WGM, int WGN>
 struct GemmShape {
@@ -459,17 +478,17 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_gemm(GemmArgs args) {
   constexpr int P = S::kEpiPitch;
   constexpr int CG = WTN / 8;                     // 8-column groups per staged row
   float *ep = reinterpret_cast<float *>(smem + wave * S::kEpiWave);
-  // per-matrix coefficients of the first step (kappa = 2^e / (f + eps))
+  // per-matrix coefficients
   float alpha = args.alpha, beta = args.beta, gamma = args.gamma;
   if (args.kap) {
-    const double kp = args.sc[tile.mat].kappa, k2 = kp * kp;
+    const StepScale s = step_scale(args, tile.mat);
     if (MODE == kPoly) {
-      alpha = float(double(args.alpha) * k2 * k2 * kp);
-      beta = float(double(args.beta) * k2 * kp);
-      gamma = float(double(args.gamma) * kp);
+      alpha = float(double(args.alpha) * s.k2 * s.k2 * s.m);
+      beta = float(double(args.beta) * s.k2 * s.m);
+      gamma = float(double(args.gamma) * s.m);
     } else {
-      alpha = float(double(args.alpha) * k2 * kp);
-      beta = float(double(args.beta) * kp);
+      alpha = float(double(args.alpha) * s.k2 * s.m);
+      beta = float(double(args.beta) * s.m);
     }
   }
   // symmetric output and where it goes

@@ -384,17 +384,17 @@ __global__ __launch_bounds__(64 * WGM * WGN) void k_tile(GemmArgs args) {
   // A for the b A term.
   char *eh = smem + wave * S::kEpiWave;
   float *ef = reinterpret_cast<float *>(eh + PL * S::kHalf);
-  // per-matrix coefficients of the first step (kappa = 2^e / (f + eps))
+  // per-matrix coefficients
   float alpha = args.alpha, beta = args.beta, gamma = args.gamma;
   if (args.kap) {
-    const double kp = args.sc[tile.mat].kappa, k2 = kp * kp;
+    const StepScale s = step_scale(args, tile.mat);
     if (MODE == kPoly) {
-      alpha = float(double(args.alpha) * k2 * k2 * kp);
-      beta = float(double(args.beta) * k2 * kp);
-      gamma = float(double(args.gamma) * kp);
+      alpha = float(double(args.alpha) * s.k2 * s.k2 * s.m);
+      beta = float(double(args.beta) * s.k2 * s.m);
+      gamma = float(double(args.gamma) * s.m);
     } else {
-      alpha = float(double(args.alpha) * k2 * kp);
-      beta = float(double(args.beta) * kp);
+      alpha = float(double(args.alpha) * s.k2 * s.m);
+      beta = float(double(args.beta) * s.m);
     }
   }
   // Symmetric outputs are stored exactly symmetric: off-diagonal tiles also
@@ -731,10 +731,10 @@ __global__ __launch_bounds__(512) void k_short(ShortArgs s) {
       compute_slab<T, 1, FN, false, 0>(acc, sA + b * kSlab, sA + b * kSlab, wm * 32, wn * 64, lane);
     float alpha = s.g.alpha, beta = s.g.beta, gamma = s.g.gamma;
     if (s.g.kap) {
-      const double kp = s.g.sc[tile.mat].kappa, k2 = kp * kp;
-      alpha = float(double(s.g.alpha) * k2 * k2 * kp);
-      beta = float(double(s.g.beta) * k2 * kp);
-      gamma = float(double(s.g.gamma) * kp);
+      const StepScale c = step_scale(s.g, tile.mat);
+      alpha = float(double(s.g.alpha) * c.k2 * c.k2 * c.m);
+      beta = float(double(s.g.beta) * c.k2 * c.m);
+      gamma = float(double(s.g.gamma) * c.m);
     }
     if constexpr (PL == 2) __syncthreads();          // dsum
     fix_diag();
@@ -1109,10 +1109,10 @@ __global__ __launch_bounds__(512) void k_upd256(GemmArgs args) {
 
     // ---------------------------------------------------------- epilogue
     float alpha = args.alpha, beta = args.beta;
-    if (args.kap) {                        // first (cubic) step: kappa^3 a, kappa b
-      const double kp = args.sc[cur.mat].kappa;
-      alpha = float(double(args.alpha) * kp * kp * kp);
-      beta = float(double(args.beta) * kp);
+    if (args.kap) {                        // a cubic step's coefficients per matrix
+      const StepScale s = step_scale(args, cur.mat);
+      alpha = float(double(args.alpha) * s.k2 * s.m);
+      beta = float(double(args.beta) * s.m);
     }
     const int row_w = cur.m0 + wm * U::WTM, col_w = cur.n0 + wn * U::WTN;
     double tsum = 0.0;

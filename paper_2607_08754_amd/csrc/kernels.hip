@@ -385,7 +385,7 @@ __global__ __launch_bounds__(kThreads) void k_sumsq(const Tile *__restrict__ til
 __global__ __launch_bounds__(kThreads) void k_norm_fin(const MatDesc *__restrict__ mats,
                                                        Scalars *__restrict__ sc,
                                                        const double *__restrict__ part, int n,
-                                                       float eps, float sx) {
+                                                       float eps, float sx, int by_norm) {
   const int i = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (i >= n) return;
   const MatDesc d = mats[i];
@@ -397,12 +397,18 @@ __global__ __launch_bounds__(kThreads) void k_norm_fin(const MatDesc *__restrict
     sc[i].sumsq = s;
     sc[i].f = f;
     sc[i].feps = fe;
-    sc[i].pexp = 0;
+    sc[i].pexp = sc[i].shift = 0;
     if (fe > 0.0 && isfinite(fe)) {
-      int e;
-      const double m = frexp(fe, &e);      // fe = m 2^e, m in [0.5, 1)
-      if (m == 0.5) --e;                   // fe is a power of two: 2^e = fe
+      auto ceil_log2 = [](double x) {
+        int e;
+        return frexp(x, &e) == 0.5 ? e - 1 : e;      // x = m 2^e, m in [0.5, 1)
+      };
+      int e = ceil_log2(fe);
       sc[i].kappa = ldexp(1.0, e) / fe;
+      if (by_norm && f > 0.0) {            // the split iterate: X_0' of f's size
+        sc[i].shift = int16_t(e - ceil_log2(f));
+        e -= sc[i].shift;
+      }
       sc[i].two_e = ldexp(1.0, e);
       // in two factors where their product leaves fp32's range (with the scale
       // 4096: norms below 2^-115)
@@ -453,7 +459,7 @@ __global__ __launch_bounds__(kThreads) void k_prep(const Tile *__restrict__ tile
 __global__ __launch_bounds__(64) void k_finalize(const MatDesc *__restrict__ mats, Scalars *sc,
                                                  const double *__restrict__ tpart,
                                                  const CallParams *__restrict__ call, int n, int kind,
-                                                 int aux, float inv_sx) {
+                                                 int aux, float inv_sx, int grow) {
   const int i = blockIdx.x, lane = threadIdx.x;
   float *out = call->out_vals;
   const MatDesc d = mats[i];
@@ -462,8 +468,10 @@ __global__ __launch_bounds__(64) void k_finalize(const MatDesc *__restrict__ mat
   nh = wave_sum(nh);
   if (lane != 0) return;
   // the partials hold sum(X_0s * P_s) of the scaled canonical buffers:
-  // sum(W * P) = 2^e sum(X_0' * P) = 2^e / s_x^2 sum(X_0s * P_s), powers of two
-  if (!d.empty) nh *= sc[i].two_e * double(inv_sx) * double(inv_sx);
+  // sum(W * P) = 2^e sum(X_0' * P) = 2^e / s_x^2 sum(X_0s * P_s), powers of two;
+  // P itself is held 2^h_T times as large (Scalars::shift)
+  const double held = d.empty ? 1.0 : ldexp(1.0, -max(0, sc[i].shift - grow));
+  if (!d.empty) nh *= sc[i].two_e * double(inv_sx) * double(inv_sx) * held;
   const double fe = d.empty ? 0.0 : sc[i].feps;
   double L = 0.0, s1 = 0.0, s2 = 0.0;
   if (d.empty || fe == 0.0) {
@@ -479,7 +487,7 @@ __global__ __launch_bounds__(64) void k_finalize(const MatDesc *__restrict__ mat
   }
   sc[i].nhat = nh;
   sc[i].value = L;
-  sc[i].s1 = s1;
+  sc[i].s1 = s1 * held;
   sc[i].s2 = s2;
   out[i] = float(L);
   if (aux) {
@@ -808,6 +816,8 @@ void launch_tile(Op op, dim3 grid, const GemmArgs &a, hipStream_t s, const EvPai
   }
 }
 
+int kap_bits(int32_t kap, const Launch &l) { return (kap ? kKappa : 0) | (l.rescale ? kRescale : 0); }
+
 // A step of a set of short matrices (Gram: X_0's partials). Partials pass
 // between launches in two buffers; step t, known by the buffer it reads X from
 // (0, then 1 and 2 in turn), reads buffer t mod 2. The slices of step 1 go from
@@ -832,7 +842,7 @@ void launch_short(const Plan &p, const Launch &l, const GemmArgs &a, char *ws, h
   sa.g.alpha = l.poly_alpha;
   sa.g.beta = l.poly_beta;
   sa.g.gamma = l.poly_gamma;
-  sa.g.kap = l.poly_kap;
+  sa.g.kap = kap_bits(l.poly_kap, l);
   const dim3 grid(r.count), block(512);
   if (l.op == Op::Gram) go(k_short<Tx, kShortFirst>, grid, block, s, ev, sa);
   else if (l.op == Op::Update) go(k_short<Tx, kShortStep>, grid, block, s, ev, sa);
@@ -903,7 +913,7 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
            dyn, sumsq, l.grid);                    // l.grid: tiles, one wave each
         break;
       case Op::NormFin:
-        go(k_norm_fin, grid, block, s, ev, mats, sc, sumsq, p.n, p.eps, sx);   // 4 matrices per block
+        go(k_norm_fin, grid, block, s, ev, mats, sc, sumsq, p.n, p.eps, sx, p.growth.empty() ? 0 : 1);   // 4 matrices per block
         break;
       case Op::Prep:
         go(k_prep<Tw, Tx>, grid, block, s, ev, tiles + l.tile_first, mats, dyn, sc, ws);
@@ -924,7 +934,9 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
         a.use_a = l.use_a;
         a.write_x = (p.flags & SLORR_VALUES_ONLY) ? 0 : 1;
         a.fold = l.fold;
-        a.kap = l.kap;
+        a.kap = kap_bits(l.kap, l);
+        a.grow0 = l.grow0;
+        a.grow1 = l.grow1;
         a.alpha = l.alpha;
         a.beta = l.beta;
         a.gamma = l.gamma;
@@ -959,7 +971,7 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
       }
       case Op::Finalize:
         go(k_finalize, grid, dim3(64), s, ev, mats, sc, trace, call, p.n, int(p.kind), (p.flags & SLORR_AUX) ? 1 : 0,
-           1.0f / sx);
+           1.0f / sx, p.growth.empty() ? 0 : p.growth.back());
         break;
       case Op::GramReduce:
         if (l.run == kNothing) {

@@ -77,14 +77,23 @@ struct Chunk {                 // a contiguous run of a matrix's elements
 // scaling, so X_0' holds W's values without rounding); the remaining factor
 // kappa = 2^e / (f + eps), in [1, 2), is applied by the first step's
 // coefficients: p_1(kappa x) = (a kappa) x + (b kappa^3) x^3 + (c kappa^5) x^5.
+//
+// The split iterate has a smallest value (2^-24 in its scale), so where eps is
+// large against f its X_0' is W / 2^(e - h), with 2^(e - h) the smallest power
+// of two >= f: X_0' has f's size, and X_0 = kappa 2^-h X_0'. Each step's iterate
+// is held as 2^h_t X_t, h_t = max(0, h - g_t), g_t the steps' largest growth in
+// powers of two so far (Plan::growth): as much of h as the bound on X_t allows,
+// until the iterate has grown to its ordinary size. h = 0 where eps <= f's
+// distance to the next power of two, and for the other iterates.
 struct Scalars {
   double sumsq, f, feps, nhat, value;
   double s1, s2;               // gradient = g (s1 P - s2 W)
   double kappa;                // 2^e / (f + eps); 0 when f + eps == 0
-  double two_e;                // 2^e: W = 2^e X_0' exactly, so the trace sum(W * P)
-                               // is 2^e sum(X_0' * P) over the canonical buffers
-  float pscale;                // the iterate's scale times 2^-e, which X_0' multiplies W
-  int32_t pexp;                // by, is pscale 2^pexp (pexp > 0: beyond fp32's 2^127)
+  double two_e;                // 2^(e - h): W = two_e X_0', so the trace sum(W * P)
+                               // is two_e sum(X_0' * P) over the canonical buffers
+  float pscale;                // the iterate's scale over two_e, which X_0' multiplies W
+  int16_t pexp;                // by, is pscale 2^pexp (pexp > 0: beyond fp32's 2^127)
+  int16_t shift;               // split iterate: h, see above
 };
 
 }  // namespace slorr

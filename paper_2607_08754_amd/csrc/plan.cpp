@@ -58,9 +58,13 @@ int32_t xbuf(int t) { return t == 0 ? 0 : 1 + ((t - 1) & 1); }
 // first step). The scales (4096, 4096, 1024) leave fp16 (65504) room for
 // u <= 3.5 and |B_ij| <= 58. The built-in schedules stay below 2.1 and 9;
 // an explicit table that may exceed the range keeps the fp32 MFMA kernels.
-bool split_fits(const std::vector<double> &coeffs, int iters) {
+// `growth` receives g_0 .. g_T: 2^g_t bounds ||X_t|| over the power of two that
+// Scalars::shift takes out of X_0 (the product of the steps' |B|, which is 2^-h
+// kappa ||X_0'|| at the start, kappa < 2 in the first step's).
+bool split_fits(const std::vector<double> &coeffs, int iters, std::vector<int32_t> *growth = nullptr) {
   constexpr double kMaxX = 3.5, kMaxB = 58.0;
-  double u = 1.0;
+  double u = 1.0, grown = 0.0;
+  if (growth) growth->assign(1, 0);
   for (int t = 0; t < iters; ++t) {
     const double a = coeffs[3 * t], b = coeffs[3 * t + 1], c = coeffs[3 * t + 2];
     auto g = [&](double z) { return std::fabs(a + z * (b + z * c)); };   // |p(x) / x|, z = x^2
@@ -69,6 +73,8 @@ bool split_fits(const std::vector<double> &coeffs, int iters) {
     if (c != 0.0 && -b / (2 * c) > 0.0 && -b / (2 * c) < z1) gmax = std::max(gmax, g(-b / (2 * c)));
     gmax *= t == 0 ? 2.0 : 1.0;
     if (gmax > kMaxB) return false;
+    grown += std::log2(std::max(gmax, 1e-300));
+    if (growth) growth->push_back(int32_t(std::ceil(grown)));
     // extrema of p on [0, u]: a + 3 b z + 5 c z^2 = 0
     double pmax = u * g(z1);
     const double disc = 9 * b * b - 20 * a * c;
@@ -130,7 +136,10 @@ void build_plan(Plan &p) {
   // differ by 5e-6, which moves 1 gradient in 700 to the next bf16 number
   // (2e-4 of the gradient, 40 times the forms' difference), and such sets'
   // results stay bit for bit.
-  p.split = p.dtype == SLORR_F32 && p.grad_dtype == SLORR_F32 && split_fits(p.coeffs, p.iters);
+  std::vector<int32_t> growth;
+  p.split = p.dtype == SLORR_F32 && p.grad_dtype == SLORR_F32 && split_fits(p.coeffs, p.iters, &growth);
+  p.growth.clear();
+  if (p.split && p.eps > 0.0f) p.growth = growth;
   const bool scaled = f16 || p.split;      // 16-bit MFMA operands
   const float sx = scaled ? kScaleX16 : 1.0f, sa = scaled ? kScaleA16 : 1.0f, sb = scaled ? kScaleB16 : 1.0f;
   bool any_quintic = false;
@@ -560,6 +569,12 @@ void build_plan(Plan &p) {
     }
   };
   const float prod = float(1.0 / sb);           // (B_s X_s) / s_b keeps X's scale
+  auto rescale = [&](Launch &l, int t) {
+    if (p.growth.empty()) return;
+    l.rescale = 1;
+    l.grow0 = p.growth[size_t(t)];
+    l.grow1 = p.growth[size_t(t) + 1];
+  };
   for (int t = 0; t < T; ++t) {
     const double a = p.coeffs[3 * t], b = p.coeffs[3 * t + 1], c = p.coeffs[3 * t + 2];
     const int32_t xi = xbuf(t), xo = xbuf(t + 1);
@@ -602,6 +617,7 @@ void build_plan(Plan &p) {
       Launch l{};
       l.xin = xi;
       l.kap = kap;
+      rescale(l, t);
       l.alpha = float(double(sb) * c / (double(sa) * sa));
       l.beta = float(double(sb) * b / sa);
       l.gamma = float(double(sb) * a);
@@ -620,6 +636,7 @@ void build_plan(Plan &p) {
         u.poly_beta = l.beta;
         u.poly_gamma = l.gamma;
         u.poly_kap = kap;
+        rescale(u, t);
       }
       gemm(op, p.pq, u);
     } else {
@@ -629,6 +646,7 @@ void build_plan(Plan &p) {
       u.xout = xo;
       u.use_a = 1;
       u.kap = kap;
+      rescale(u, t);
       u.alpha = float(b / sa);
       u.beta = float(a);
       gemm(op, p.pq, u);

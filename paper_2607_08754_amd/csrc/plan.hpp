@@ -49,6 +49,8 @@ struct Launch {
   int32_t use_a;       // update operand is A (cubic step) instead of B
   int32_t fold;        // update: a_t I already folded into B (no a X term)
   int32_t kap;         // first step: coefficients scaled per matrix by powers of kappa
+  int32_t rescale;     // coefficients scaled by the powers of two that the iterates
+  int32_t grow0, grow1;  // read and written are held in: growth before, after the step
   int32_t set_sum;     // gradient launch: its first block also writes the set total
   float alpha, beta, gamma;  // epilogue coefficients
   // what the launch runs where it differs from the above (sets of short
@@ -95,6 +97,7 @@ struct Plan {
   TileRange gsplit, gred;              // split-K Gram: part entries, reduce entries
   bool lean = false;                   // no 64-tile lists
   bool short_set = false;              // one launch per step (k_short)
+  std::vector<int32_t> growth;         // split sets with eps > 0: g_0 .. g_T of Scalars::shift (else empty)
   int32_t gram_parts = 0;              // fp32 partial tiles in the workspace
   int32_t trace_slots = 0;             // one per update tile
   int32_t norm_slots = 0;              // one per canonical 64 x 64 tile

@@ -5,6 +5,7 @@
 // queue with padding at its end; and the launches' operands and factors, run in
 // scalar arithmetic, give the table's polynomials. Input as for plan_check.cpp (stdin); built
 // by tests/test_run_lists.py.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <iostream>
@@ -37,6 +38,7 @@ int main() {
   }
   int grad_dtype;
   if (std::cin >> grad_dtype) p.grad_dtype = grad_dtype;     // optional; fp32 otherwise
+  if (!(std::cin >> p.eps)) p.eps = 0.0f;                    // optional
   p.mats.resize(size_t(n));
   build_plan(p);
   int bad = 0;
@@ -137,12 +139,20 @@ int main() {
   // scalar arithmetic, against the table's polynomials
   const bool scaled = p.dtype == SLORR_BF16 || p.split;
   const double sx = scaled ? kScaleX16 : 1.0;
+  // (eps > 0: X_0 a factor 2^-h smaller, the iterates held in powers of two)
+  for (int h : {0, 1, 3, 9, 30})
   for (double x0 : {0.02, 0.3, 0.8}) {
     if (p.prep.count == 0) break;             // no matrix with elements
+    if (h && p.growth.empty()) break;
+    if (!p.growth.empty() && p.growth.size() != size_t(iters) + 1) fail("growth entries", int(p.growth.size()), iters, 0);
     const double nan = std::nan(""), kappa = 1.25;
     double x[3] = {sx * x0, nan, nan}, A = nan, B = nan, part = nan;
     for (const Launch &l : p.launches) {
-      const double k = l.kap ? kappa : 1.0;
+      const double c = l.kap || l.poly_kap ? kappa : 1.0;
+      const int h0 = l.rescale ? std::max(0, h - l.grow0) : 0, h1 = l.rescale ? std::max(0, h - l.grow1) : 0;
+      const double k = std::ldexp(c, -h0), m = std::ldexp(c, h1 - h0), k2 = k * k;
+      if (l.rescale != (p.growth.empty() ? 0 : l.op == Op::Poly || (l.run == kRunShort && l.op != Op::Gram) || l.use_a))
+        fail("rescale", int(l.op), l.run, l.rescale);
       if (l.run == kRunShort && !p.short_set) fail("short-set flag", l.run, int(l.op), 0);
       if (l.run == kNothing) {
         continue;
@@ -150,8 +160,8 @@ int main() {
         const int last = iters == 0 ? 0 : 1 + ((iters - 1) & 1);
         double &X = x[l.op == Op::Gram || l.xin == 0 ? 0 : last];
         if (l.op != Op::Gram) {
-          const double kp = l.poly_kap ? kappa : 1.0, k2 = kp * kp, G = l.gram_alpha * part;
-          x[last] = l.alpha * (l.poly_beta * k2 * kp * G + l.poly_alpha * k2 * k2 * kp * G * G + l.poly_gamma * kp) * X;
+          const double G = l.gram_alpha * part;
+          x[last] = l.alpha * (l.poly_beta * k2 * m * G + l.poly_alpha * k2 * k2 * m * G * G + l.poly_gamma * m) * X;
         }
         part = x[l.op == Op::Gram ? 0 : last] * x[l.op == Op::Gram ? 0 : last];
       } else if (l.op == Op::Gram) {
@@ -160,20 +170,24 @@ int main() {
       } else if (l.op == Op::GramReduce && l.run != kNothing) {
         A = l.alpha * part;
       } else if (l.op == Op::Poly) {
-        const double k2 = k * k;
-        B = l.beta * k2 * k * A + l.alpha * k2 * k2 * k * A * A + l.gamma * k;
+        B = l.beta * k2 * m * A + l.alpha * k2 * k2 * m * A * A + l.gamma * m;
+        if (scaled && !(std::fabs(B) < 65504.0)) fail("B beyond fp16", int(B), h, 0);
       } else if (l.op == Op::Update || l.op == Op::Last) {
         const double v = double(l.alpha) * (l.use_a ? A : B) * x[l.xin];
-        x[l.xout] = l.fold ? v : l.beta * k * x[l.xin] + v * k * k * k;
+        x[l.xout] = l.fold ? v : l.beta * m * x[l.xin] + v * k2 * m;
+        if (scaled && !(std::fabs(x[l.xout]) < 65504.0)) fail("X beyond fp16", int(x[l.xout]), h, 0);
+        // held no smaller than a step's ordinary iterate, or as large as its bound allows
+        if (h1 && !(std::fabs(x[l.xout]) >= 0.02 * x0 * sx)) fail("X held too small", int(1e6 * x[l.xout]), h, h1);
       }
     }
-    double want = kappa * x0;
+    double want = std::ldexp(kappa * x0, -h);
     for (int t = 0; t < iters; ++t) {
       const double z = want * want;
       want *= p.coeffs[3 * t] + z * (p.coeffs[3 * t + 1] + z * p.coeffs[3 * t + 2]);
     }
-    const double got = x[iters == 0 ? 0 : 1 + ((iters - 1) & 1)] / sx;
-    if (!(std::fabs(got - want) <= 1e-4 * std::fabs(want) + 1e-6)) fail("schedule's value", int(1e6 * got), int(1e6 * want), int(100 * x0));
+    const int hT = p.growth.empty() ? 0 : std::max(0, h - p.growth.back());
+    const double got = std::ldexp(x[iters == 0 ? 0 : 1 + ((iters - 1) & 1)] / sx, -hT);
+    if (!(std::fabs(got - want) <= 1e-4 * std::fabs(want) + (h ? 0.0 : 1e-6))) fail("schedule's value", int(1e6 * got), int(1e6 * want), int(100 * x0));
   }
   if (bad) return 1;
   std::printf("OK split=%d run256=%d short=%d small=%d%d\n", p.split ? 1 : 0, run, p.short_set ? 1 : 0, p.gram64.count > 0, p.pp64.count > 0);

@@ -92,3 +92,42 @@ def test_tiny_norms(kind):
         if kind == "nuclear":
             for a, b in zip(g1, g0):
                 assert np.array_equal(a, b), k
+
+
+# per product with one tile of rows and with several, a launch per step, a
+# split Gram product, 256-tile updates
+@pytest.mark.parametrize("shapes", [[(100, 200), (128, 1000)], [(384, 1536), (300, 130)], [(100, 4000), (700, 300)],
+                                    [(512, 2048)] * 32])
+@pytest.mark.parametrize("kind", ["hoyer", "nuclear"])
+def test_eps_above_the_norm(shapes, kind):
+    """eps up to 1e8 times the norm: X_0 is small against 1, and the iterate is
+    held in powers of two that keep its significand. 8e-6: the bound of the other
+    fp32 sets on this form (split: 2e-5 for T = 6 at eps = 0, less here, where B
+    is a I and little else)."""
+    import torch
+    from paper_2607_08754_amd import Plan
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(41)
+    W = [torch.randn(s, generator=gen, device="cuda:0") * 0.02 for s in shapes]
+    f = [float(w.double().norm()) for w in W]
+    table = default_table(6)
+    for r in (1e-2, 1.0, 3.0, 1e2, 1e3, 1e4, 1e5, 1e6, 1e8):
+        eps = float(np.float32(r * min(f)))
+        G = [torch.full(s, float("nan"), device="cuda:0") for s in shapes]
+        vals = Plan(shapes, dtype="f32", kind=kind, eps=eps)(W, G).double()
+        worst = [0.0, 0.0]
+        for i in (0, 1):
+            w = W[i].double()
+            y = w if w.shape[0] <= w.shape[1] else w.t().contiguous()
+            fe = y.norm() + eps
+            x = y / fe
+            for a, b, c in table:
+                s = x @ x.t()
+                x = a * x + (b * s + c * (s @ s)) @ x
+            nh = (y * x).sum()
+            v, g = (nh, x) if kind == "nuclear" else ((nh / fe) ** 2, 2 * nh / fe ** 2 * x - 2 * nh ** 2 / fe ** 4 * y)
+            g = g if w.shape[0] <= w.shape[1] else g.t()
+            worst[0] = max(worst[0], float((G[i].double() - g).norm() / g.norm()))
+            worst[1] = max(worst[1], float(abs(vals[i] - v) / v))
+        print(f"{shapes[0]} {kind} eps/f {r:g}: gradient {worst[0]:.1e} value {worst[1]:.1e}", flush=True)
+        assert worst[0] <= 8e-6 and worst[1] <= 1e-6, r

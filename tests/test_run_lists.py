@@ -29,11 +29,11 @@ def checker(tmp_path_factory):
     return exe
 
 
-def run(checker, shapes, dtype, iters=6, coeffs=None, grad=F32):
+def run(checker, shapes, dtype, iters=6, coeffs=None, grad=F32, eps=0.0):
     head = f"{dtype} 0 {iters} 0 {1 if coeffs is not None else 0}\n"
     if coeffs is not None:
         head += " ".join(repr(float(c)) for c in coeffs) + "\n"
-    body = f"{len(shapes)}\n" + "".join(f"{r} {c}\n" for r, c in shapes) + f"{grad}\n"
+    body = f"{len(shapes)}\n" + "".join(f"{r} {c}\n" for r, c in shapes) + f"{grad} {eps!r}\n"
     r = subprocess.run([checker], input=head + body, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.startswith("OK"), r.stdout[-4000:] + r.stderr[-2000:]
     return dict(kv.split("=") for kv in r.stdout.split()[1:])
@@ -74,6 +74,18 @@ def test_run_lists_edges(checker):
 def test_split_rule(checker, coeffs, split):
     assert run(checker, [(64, 96)], F32, iters=len(coeffs) // 3, coeffs=coeffs)["split"] == str(split)
     assert run(checker, [(64, 96)], BF16, iters=len(coeffs) // 3, coeffs=coeffs)["split"] == "0"
+
+
+@pytest.mark.parametrize("shapes", [[(200, 300)] * 3, [(100, 256)] * 4, [(512, 2048)] * 32])
+@pytest.mark.parametrize("iters", [1, 5, 6, 12])
+def test_scales_at_large_eps(checker, shapes, iters):
+    """eps > 0 on the split form: every iterate held in the power of two that its
+    bound allows, the schedule's value that of the table at X_0 2^-h."""
+    run(checker, shapes, F32, iters=iters, eps=0.5)
+    run(checker, shapes, BF16, iters=iters, eps=0.5)
+    run(checker, shapes, F32, iters=iters, eps=0.5, coeffs=[15 / 8, -10 / 8, 3 / 8] * iters)
+    run(checker, shapes, F32, iters=iters, eps=0.5, coeffs=[1.5, -0.5, 0.0] * iters)
+    run(checker, shapes, F32, iters=iters, eps=0.5, grad=BF16)
 
 
 def test_split_needs_fp32_gradients(checker):
