@@ -57,13 +57,18 @@ int32_t xbuf(int t) { return t == 0 ? 0 : 1 + ((t - 1) & 1); }
 // and |B_ij| <= max |a + b x^2 + c x^4| on [0, u] (times kappa < 2 in the
 // first step). The scales (4096, 4096, 1024) leave fp16 (65504) room for
 // u <= 3.5 and |B_ij| <= 58. The built-in schedules stay below 2.1 and 9;
-// an explicit table that may exceed the range keeps the fp32 MFMA kernels.
+// an explicit table that may exceed the range keeps the fp32 MFMA kernels. So
+// does one whose linear terms, which the small singular values follow, shrink
+// the iterate below half of X_0 on the way (or at the end): it would come near
+// the split form's smallest value, 2^-36, which fp32 does not have (1e-4 times
+// X_0 and back by the next steps, 200 x 300: gradient off by 1.0e-5 against
+// 2.6e-7). The built-in linear terms are all above 1.
 // `growth` receives g_0 .. g_T: 2^g_t bounds ||X_t|| over the power of two that
 // Scalars::shift takes out of X_0 (the product of the steps' |B|, which is 2^-h
 // kappa ||X_0'|| at the start, kappa < 2 in the first step's).
 bool split_fits(const std::vector<double> &coeffs, int iters, std::vector<int32_t> *growth = nullptr) {
   constexpr double kMaxX = 3.5, kMaxB = 58.0;
-  double u = 1.0, grown = 0.0;
+  double u = 1.0, grown = 0.0, linear = 1.0;
   if (growth) growth->assign(1, 0);
   for (int t = 0; t < iters; ++t) {
     const double a = coeffs[3 * t], b = coeffs[3 * t + 1], c = coeffs[3 * t + 2];
@@ -73,6 +78,8 @@ bool split_fits(const std::vector<double> &coeffs, int iters, std::vector<int32_
     if (c != 0.0 && -b / (2 * c) > 0.0 && -b / (2 * c) < z1) gmax = std::max(gmax, g(-b / (2 * c)));
     gmax *= t == 0 ? 2.0 : 1.0;
     if (gmax > kMaxB) return false;
+    linear *= std::fabs(a);
+    if (!(linear >= 0.5)) return false;
     grown += std::log2(std::max(gmax, 1e-300));
     if (growth) growth->push_back(int32_t(std::ceil(grown)));
     // extrema of p on [0, u]: a + 3 b z + 5 c z^2 = 0

@@ -59,7 +59,8 @@ def test_run_lists_edges(checker):
     assert run(checker, [(512, 2048)] * 32, F32, coeffs=cubic)["run256"] == "0"
 
 
-# the range rule of the split form: |X| <= 3.5 and |B| <= 58 over the whole
+# the range rule of the split form: |X| <= 3.5, |B| <= 58 and linear terms that
+# leave at least half of X_0 over the whole
 # table (twice |B| in the first step, whose matrix is scaled by kappa < 2)
 @pytest.mark.parametrize("coeffs,split", [
     ([15 / 8, -10 / 8, 3 / 8] * 2, 1),          # Newton-Schulz
@@ -70,6 +71,11 @@ def test_run_lists_edges(checker):
     ([28.0, -40.0, 13.0, 1.0, 0.0, 0.0], 0),    # an interior extremum of X beyond the range
     ([30.0, -100.0, 71.0, 1.0, 0.0, 0.0], 0),   # 2 |B| up to 60 at x = 0
     ([1.0, 0.0, 0.0, 1.0, 60.0, -61.0], 0),     # interior extrema in a later step
+    ([0.6, 0.0, 0.0, 2.0, 0.0, 0.0], 1),        # shrinks X, not below half
+    ([0.4, 0.0, 0.0, 2.5, 0.0, 0.0], 0),        # below half in the first step
+    ([0.6, 0.0, 0.0, -0.6, 0.0, 0.0, 3.0, 0.0, 0.0], 0),   # over two steps
+    ([2.0, 0.0, 0.0, 0.2, 0.0, 0.0], 0),        # at the end
+    ([0.0, 1.0, 0.0, 2.0, 0.0, 0.0], 0),        # no linear term
 ])
 def test_split_rule(checker, coeffs, split):
     assert run(checker, [(64, 96)], F32, iters=len(coeffs) // 3, coeffs=coeffs)["split"] == str(split)
