@@ -525,8 +525,10 @@ void build_plan(Plan &p) {
   }
   p.ws_bytes = off;
   // a set that fits the static scratch without the 64-tile lists goes without
+  // (p.off_short: the size without the partials of short matrices, which such a
+  // set goes without too if need be)
   const size_t lists = sizeof(Tile) * size_t(p.gram64.count + p.pp64.count);
-  if (lists && off > size_t(SLORR_SCRATCH_BYTES) && off - lists - 256 <= size_t(SLORR_SCRATCH_BYTES)) {
+  if (lists && p.off_short > size_t(SLORR_SCRATCH_BYTES) && p.off_short - lists - 256 <= size_t(SLORR_SCRATCH_BYTES)) {
     p.lean = true;
     build_plan(p);                            // (with the table built above)
     return;

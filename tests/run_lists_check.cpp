@@ -190,6 +190,7 @@ int main() {
     if (!(std::fabs(got - want) <= 1e-4 * std::fabs(want) + (h ? 0.0 : 1e-6))) fail("schedule's value", int(1e6 * got), int(1e6 * want), int(100 * x0));
   }
   if (bad) return 1;
-  std::printf("OK split=%d run256=%d short=%d small=%d%d\n", p.split ? 1 : 0, run, p.short_set ? 1 : 0, p.gram64.count > 0, p.pp64.count > 0);
+  std::printf("OK split=%d run256=%d short=%d small=%d%d lean=%d ws=%zu\n", p.split ? 1 : 0, run, p.short_set ? 1 : 0, p.gram64.count > 0,
+              p.pp64.count > 0, p.lean ? 1 : 0, p.ws_bytes);
   return 0;
 }

@@ -143,5 +143,18 @@ def test_small_tiles(checker, dtype):
     assert small([(0, 5)], dtype) == "00"
 
 
+@pytest.mark.parametrize("dtype,shapes", [
+    (BF16, [(512, 1792)] * 10 + [(128, 1792)]),
+    # short matrices, whose partials must not hide that the set fits without the lists
+    (F32, [(128, 128)] * 151 + [(128, 1024)] * 4 + [(0, 5)] * 120),
+    (F32, [(128, 128)] * 147 + [(128, 384)] * 10 + [(0, 5)] * 130),
+])
+def test_sets_that_fit_the_scratch_without_64_tiles(checker, dtype, shapes):
+    """A set that the no-allocation entry's 64 MiB hold without the 64-tile lists
+    goes without them."""
+    got = run(checker, shapes, dtype)
+    assert int(got["ws"]) <= 64 << 20 and got["lean"] == "1" and got["small"] == "00" and got["short"] == "0"
+
+
 def test_no_small_tiles_on_fp32_mfma(checker):
     assert run(checker, [(200, 250)] * 4, F32, grad=BF16)["small"] == "00"
