@@ -26,17 +26,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}     # dense MFMA: fp16/bf16 operands, fp32 operands
+# dense MFMA on fp16 operands: one per product for bf16 sets, three for fp32 sets
+PEAK_TFLOPS = {"bf16": 2500.0, "f32": 2500.0 / 3}
 GEMM_OPS = ("gram", "poly", "update", "last")
-
-
-def kernel_instance(op, edge):
-    """Name of the GEMM kernel instance a launch runs: mode and block tile (the
-    256-tile update and last launches of the fp16 iterate run the persistent
-    kernel k_upd256)."""
-    if op in ("update", "last") and edge == 256:
-        return f"k_upd256<{op}>"
-    return f"k_tile<{op}, {edge}x{edge}>"
 
 
 def _alg_bytes_per_launch(shapes, dtype, op):
@@ -304,9 +296,9 @@ def main():
         W.append(t.to(dev))
     G = [torch.empty(a.shape, dtype=torch.float32, device=dev) for a in arrs]
     plan = Plan(cfg.shapes, dtype=cfg.dtype, kind=args.kind, iters=cfg.iters, device=dev)
-    info = plan.info()
+    kernels = plan.kernels()
     print(f"[bench] {cfg.name}: {cfg.n} matrices, inputs ready in {time.perf_counter() - t_gen:.1f} s, "
-          f"{info['launches']} launches per step", file=sys.stderr, flush=True)
+          f"{sum(bool(k) for k, _ in kernels)} launches per step", file=sys.stderr, flush=True)
 
     stream = torch.cuda.current_stream(dev)
     for _ in range(args.warmup):
@@ -326,20 +318,19 @@ def main():
     print(f"[bench] timed {args.steps} steps: {ms:.4f} ms/step", file=sys.stderr, flush=True)
 
     # per-launch durations: HIP events on the launch stream that take each
-    # kernel's start and end timestamps; the library
-    # reports each launch's kind and algorithmic flops (its products counted
-    # in full on the unpadded shapes)
-    sched = plan.launches()
+    # kernel's start and end timestamps; the library reports the kernel that
+    # each entry of the schedule runs and the algorithmic flops of its products
+    # (counted in full on the unpadded shapes)
     per_op, per_op_flops = {}, {}
     per_k, per_k_flops = {}, {}
     for _ in range(args.profile_steps):
         _, launches = plan.profiled(W, G)
-        for (op, t), (op2, fl, edge) in zip(launches, sched):
-            assert op == op2
+        for (op, t), (k, fl) in zip(launches, kernels):
+            if not k:
+                continue
             per_op.setdefault(op, []).append(t)
             per_op_flops.setdefault(op, []).append(fl)
-            if edge:
-                k = kernel_instance(op, edge)
+            if fl:
                 per_k.setdefault(k, []).append(t)
                 per_k_flops.setdefault(k, []).append(fl)
     torch.cuda.synchronize()

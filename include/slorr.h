@@ -306,29 +306,41 @@ typedef struct {
   int32_t n;               /* matrices in the plan                                  */
   int32_t groups;          /* distinct canonical (P, Q) shapes                       */
   int32_t iters;           /* T                                                      */
-  int32_t launches;        /* kernels per call                                       */
-  int64_t gemm_tiles;      /* output tiles over all GEMM launches of one call        */
+  int32_t launches;        /* entries of the launch schedule (slorr_plan_get_launches);
+                              an entry whose work another entry's kernel does runs
+                              nothing (slorr_plan_get_kernels)                       */
+  int64_t gemm_tiles;      /* tile-list entries over all product launches of the schedule */
   double paper_flops;      /* T * sum_i (4 P_i^2 Q_i + 2 P_i^3) (Sec. 3)             */
-  double mfma_flops;       /* flops of the products per call (padded tiles; a product
-                              formed as three MFMAs counted once; as if every step
-                              ran by itself)                                         */
+  double mfma_flops;       /* flops of the schedule's products per call (padded tiles;
+                              a product formed as three MFMAs counted once)          */
   double weight_bytes;     /* sum_i rows_i * cols_i * sizeof(dtype)                  */
   size_t workspace_bytes;
 } slorr_plan_info_t;
 
 SLORR_API slorr_status_t slorr_plan_get_info(slorr_plan_t plan, slorr_plan_info_t *info);
 
-/* The launch schedule, in launch order: host arrays of
- * slorr_plan_info_t.launches entries. ops[i] is the
- * kernel kind (slorr_op_t) of launch i; alg_flops[i] its algorithmic work:
- * the products it performs, on the unpadded shapes and counted in full
- * (2 m n k each, symmetric outputs not halved): A = X X^T and B X 2 P^2 Q,
- * the poly's A A 2 P^3; 0 for
- * the memory-bound and reduction kernels. tile_edge[i] is the block tile edge
- * of a product launch (128 or 256: the kernel instance a profiler names), 0
- * for the others. Any of the three arrays may be NULL. Host only. */
+/* The launch schedule, in launch order, one product per entry: host arrays of
+ * slorr_plan_info_t.launches entries. ops[i] is the kind (slorr_op_t) of entry
+ * i; alg_flops[i] its algorithmic work: its product, on the unpadded shapes and
+ * counted in full (2 m n k, symmetric outputs not halved): A = X X^T and B X
+ * 2 P^2 Q, the poly's A A 2 P^3; 0 for the memory-bound and reduction kernels.
+ * tile_edge[i] is 256 for a product that runs on 256-tiles, 128 for the other
+ * products, 0 for the rest. Which kernel an entry runs, and what that kernel
+ * does, is slorr_plan_get_kernels' to say. Any of the three arrays may be NULL.
+ * Host only. */
 SLORR_API slorr_status_t slorr_plan_get_launches(slorr_plan_t plan, int32_t *ops, double *alg_flops,
                                                  int32_t *tile_edge);
+
+/* What the schedule's entries run: host arrays of slorr_plan_info_t.launches
+ * entries. names[i] is the kernel of entry i with its mode and block tile
+ * ("k_tile<poly, 64x64>"), or "" for an entry that runs nothing: a set of short
+ * matrices runs each step as one kernel, in the update's entry, and a split
+ * Gram product of one part per tile needs no reduce. The strings live as long
+ * as the plan. alg_flops[i] are the products that the kernel forms, counted as
+ * in slorr_plan_get_launches; over a call both sum to the same. The entries are
+ * those of slorr_reg_fwd_bwd_profiled, where one that runs nothing takes 0 ms.
+ * Either array may be NULL. Host only. */
+SLORR_API slorr_status_t slorr_plan_get_kernels(slorr_plan_t plan, const char **names, double *alg_flops);
 
 /* Name of a status code (static string). */
 SLORR_API const char *slorr_status_string(slorr_status_t status);

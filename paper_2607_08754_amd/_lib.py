@@ -37,7 +37,8 @@ EXPORTED = ("slorr_default_options", "slorr_pe_coefficients", "slorr_plan", "slo
             "slorr_cache_clear",
             "slorr_plan_set_workspace", "slorr_reg_fwd_bwd", "slorr_reg_grad", "slorr_decoupled_apply",
             "slorr_reg_fwd_bwd_profiled", "slorr_reg_fwd_bwd_noalloc",
-            "slorr_plan_destroy", "slorr_plan_get_info", "slorr_plan_get_launches", "slorr_status_string",
+            "slorr_plan_destroy", "slorr_plan_get_info", "slorr_plan_get_launches",
+            "slorr_plan_get_kernels", "slorr_status_string",
             "slorr_last_error")
 
 
@@ -116,6 +117,8 @@ def lib() -> ctypes.CDLL:
         L.slorr_plan_get_launches.argtypes = [vp, ctypes.POINTER(i32), ctypes.POINTER(ctypes.c_double),
                                               ctypes.POINTER(i32)]
         L.slorr_plan_get_launches.restype = ctypes.c_int
+        L.slorr_plan_get_kernels.argtypes = [vp, ctypes.POINTER(ctypes.c_char_p), ctypes.POINTER(ctypes.c_double)]
+        L.slorr_plan_get_kernels.restype = ctypes.c_int
         L.slorr_status_string.argtypes = [ctypes.c_int]
         L.slorr_status_string.restype = ctypes.c_char_p
         L.slorr_last_error.argtypes = []

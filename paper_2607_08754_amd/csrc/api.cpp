@@ -10,7 +10,6 @@
 #include <stdexcept>
 #include <string>
 #include <utility>
-#include <set>
 #include <vector>
 
 #include "kernels.hpp"
@@ -474,20 +473,25 @@ slorr_status_t slorr_plan_get_launches(slorr_plan_t plan, int32_t *ops, double *
                         l.op == slorr::Op::Last;
       if (ops) ops[i] = int32_t(l.op);
       if (tile_edge) tile_edge[i] = gemm ? (l.run_cfg == slorr::kCfg256 ? 256 : 128) : 0;
+      if (alg_flops) alg_flops[i] = p.product_flops(l.op);
+    }
+    return SLORR_OK;
+  });
+}
+
+slorr_status_t slorr_plan_get_kernels(slorr_plan_t plan, const char **names, double *alg_flops) {
+  return guarded([&]() -> slorr_status_t {
+    if (!plan) throw std::invalid_argument("plan is NULL");
+    using slorr::Op;
+    const slorr::Plan &p = plan->p;
+    for (size_t i = 0; i < p.launches.size(); ++i) {
+      const slorr::Launch &l = p.launches[i];
+      if (names) names[i] = p.kernels[i].c_str();
       if (!alg_flops) continue;
-      double f = 0.0;
-      if (gemm) {
-        std::set<int32_t> mats;       // matrices of the launch (one product each)
-        for (int k = 0; k < l.grid; ++k) {
-          const slorr::Tile &t = p.tiles[l.tile_first + k];
-          if (t.mat >= 0) mats.insert(t.mat);
-        }
-        for (int32_t m : mats) {
-          const slorr::MatDesc &d = p.mats[m];
-          const double P = d.P, Q = d.Q;
-          f += l.op == slorr::Op::Poly ? 2.0 * P * P * P : 2.0 * P * P * Q;
-        }
-      }
+      double f = l.run == slorr::kNothing ? 0.0 : p.product_flops(l.op);
+      // a whole step: the poly and update products, and the next step's Gram
+      if (l.run == slorr::kRunShort && l.op != Op::Gram) f += p.product_flops(Op::Poly);
+      if (l.run == slorr::kRunShort && l.op == Op::Update) f += p.product_flops(Op::Gram);
       alg_flops[i] = f;
     }
     return SLORR_OK;
@@ -622,8 +626,9 @@ slorr_status_t slorr_reg_fwd_bwd_profiled(slorr_plan_t plan, int32_t n,
     p.state_ready = !(p.flags & SLORR_VALUES_ONLY);
     hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
     for (size_t i = 0; i < nl; ++i) {
-      float ms = 0.0f;
-      hip_check(hipEventElapsedTime(&ms, ev[2 * i], ev[2 * i + 1]), "hipEventElapsedTime");
+      float ms = 0.0f;                  // (an entry that runs nothing records no events)
+      if (!p.kernels[i].empty())
+        hip_check(hipEventElapsedTime(&ms, ev[2 * i], ev[2 * i + 1]), "hipEventElapsedTime");
       launch_ms[i] = ms;
       if (launch_op) launch_op[i] = int32_t(p.launches[i].op);
     }

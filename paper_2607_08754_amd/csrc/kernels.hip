@@ -849,13 +849,6 @@ void launch_short(const Plan &p, const Launch &l, const GemmArgs &a, char *ws, h
   else go(k_short<Tx, kShortLast>, grid, block, s, ev, sa);
 }
 
-// A launch of the plan's list that has nothing to run.
-void no_launch(hipStream_t s, const EvPair *ev) {
-  if (!ev) return;
-  check(hipEventRecord(ev->start, s), "hipEventRecord");
-  check(hipEventRecord(ev->stop, s), "hipEventRecord");
-}
-
 // The products on fp32 MFMA.
 template <int BM, int BN, int WGM, int WGN>
 void launch_gemm(Op op, dim3 grid, const GemmArgs &a, hipStream_t s, const EvPair *ev) {
@@ -905,7 +898,7 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
   double *sumsq = reinterpret_cast<double *>(ws + p.off_sumsq);
   double *trace = reinterpret_cast<double *>(ws + p.off_trace);
   const float sx = std::is_same<Tx, float>::value ? 1.0f : kScaleX16;
-  {
+  if (l.run != kNothing) {
     const dim3 grid(l.grid), block(kThreads);
     switch (l.op) {
       case Op::SumSq:
@@ -944,10 +937,6 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
         a.gpart = reinterpret_cast<float *>(ws + p.off_gpart);
         a.quads = l.run_cfg != l.cfg;
         a.ntiles = l.run_grid;
-        if (l.run == kNothing) {
-          no_launch(s, ev);
-          break;
-        }
         if (l.run == kRunShort) {
           if constexpr (!std::is_same<Tx, float>::value) launch_short<Tx>(p, l, a, ws, s, ev);
           else throw HipError("no short-matrix steps on fp32 MFMA");
@@ -974,10 +963,6 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
            1.0f / sx, p.growth.empty() ? 0 : p.growth.back());
         break;
       case Op::GramReduce:
-        if (l.run == kNothing) {
-          no_launch(s, ev);
-          break;
-        }
         go(k_gram_reduce<Tx>, grid, block, s, ev, tiles + l.tile_first, mats, ws,
            reinterpret_cast<const float *>(ws + p.off_gpart), l.alpha);
         break;

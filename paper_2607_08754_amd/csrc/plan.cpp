@@ -101,6 +101,16 @@ bool split_fits(const std::vector<double> &coeffs, int iters, std::vector<int32_
 
 }  // namespace
 
+double Plan::product_flops(Op op) const {
+  double f = 0.0;
+  for (const MatDesc &d : mats) {
+    const double P = d.P, Q = d.Q;
+    if (op == Op::Poly) f += 2.0 * P * P * P;
+    else if (op == Op::Gram || op == Op::Update || op == Op::Last) f += 2.0 * P * P * Q;
+  }
+  return f;
+}
+
 size_t Plan::dyn_bytes() const { return off_call + sizeof(CallParams) - off_dyn; }
 
 void build_plan(Plan &p) {
@@ -678,7 +688,27 @@ void build_plan(Plan &p) {
     else if (grad_now) p.launches.back().set_sum = 1;
   }
 
-  // MFMA work the launches execute (padded, symmetric tiles counted once)
+  // the kernel of each launch
+  p.kernels.clear();
+  for (const Launch &l : p.launches) {
+    static const char *const simple[] = {"k_sumsq", "k_norm_fin", "k_prep", "", "", "", "",
+                                         "k_finalize", "k_grad", "k_setsum", "k_gram_reduce"};
+    const bool product = l.op == Op::Gram || l.op == Op::Poly || l.op == Op::Update || l.op == Op::Last;
+    const char *mode = l.op == Op::Gram ? "gram" : l.op == Op::Poly ? "poly" : l.op == Op::Update ? "update" : "last";
+    std::string name;
+    if (l.run == kRunShort) {
+      name = l.op == Op::Gram ? "k_short<first>" : l.op == Op::Update ? "k_short<step>" : "k_short<last>";
+    } else if (l.run != kNothing && product) {
+      const std::string edge = l.run_cfg == kCfg64 ? "64" : l.run_cfg == kCfg256 ? "256" : "128";
+      if (scaled && l.run_cfg == kCfg256 && l.op != Op::Gram && l.op != Op::Poly) name = std::string("k_upd256<") + mode + ">";
+      else name = std::string(scaled ? "k_tile<" : "k_gemm<") + mode + ", " + edge + "x" + edge + ">";
+    } else if (l.run != kNothing) {
+      name = simple[int(l.op)];
+    }
+    p.kernels.push_back(name);
+  }
+
+  // MFMA work of the schedule's products (padded, symmetric tiles counted once)
   p.mfma_flops = 0;
   for (const Launch &l : p.launches) {
     if (l.op != Op::Gram && l.op != Op::Poly && l.op != Op::Update && l.op != Op::Last) continue;

@@ -104,6 +104,7 @@ struct Plan {
   std::vector<Chunk> chunks;           // original-layout element runs
   std::vector<Launch> launches;
   std::vector<Launch> grad_launches;   // the gradient launch (after finalize)
+  std::vector<std::string> kernels;    // per launch: the kernel that runs ("" for none)
   double paper_flops = 0, mfma_flops = 0, weight_bytes = 0;
   // workspace layout (byte offsets)
   size_t off_mats = 0, off_dyn = 0, off_call = 0, off_tiles = 0, off_chunks = 0, off_scal = 0,
@@ -130,6 +131,9 @@ struct Plan {
   size_t elem_bytes() const { return dtype == SLORR_BF16 ? 2 : 4; }     // weights
   size_t grad_bytes() const { return grad_dtype == SLORR_BF16 ? 2 : 4; }  // gradients
   size_t iter_bytes() const { return dtype == SLORR_BF16 ? 2 : 4; }     // X, A, B (fp16 / fp32)
+  // algorithmic flops of the schedule's product of kind `op` (every matrix of
+  // the plan, on the unpadded shapes)
+  double product_flops(Op op) const;
   size_t dyn_bytes() const;                                            // dyn table + call params
 };
 

@@ -211,15 +211,24 @@ class Plan:
     # ------------------------------------------------------------------ info
     def launches(self) -> list:
         """The schedule in launch order: [(op name, algorithmic flops, tile
-        edge), ...] (the products each launch performs, counted in full on the
-        unpadded shapes, 0 for the memory-bound kernels; the block tile edge of
-        a product launch, 0 for the others)."""
+        edge), ...], one product per entry (counted in full on the unpadded
+        shapes, 0 for the memory-bound kernels; the edge 256 or 128 of a product,
+        0 for the others). kernels() says what the entries run."""
         nl = self.info()["launches"]
         ops = (ctypes.c_int32 * max(1, nl))()
         fl = (ctypes.c_double * max(1, nl))()
         te = (ctypes.c_int32 * max(1, nl))()
         check(lib().slorr_plan_get_launches(self._handle, ops, fl, te), "slorr_plan_get_launches")
         return [(_lib.OPS[ops[i]], float(fl[i]), int(te[i])) for i in range(nl)]
+
+    def kernels(self) -> list:
+        """What the entries of launches() run: [(kernel, algorithmic flops of its
+        products), ...]; the kernel is "" for an entry that runs nothing."""
+        nl = self.info()["launches"]
+        names = (ctypes.c_char_p * max(1, nl))()
+        fl = (ctypes.c_double * max(1, nl))()
+        check(lib().slorr_plan_get_kernels(self._handle, names, fl), "slorr_plan_get_kernels")
+        return [(names[i].decode(), float(fl[i])) for i in range(nl)]
 
     def info(self) -> dict:
         inf = _lib.PlanInfo()

@@ -165,6 +165,55 @@ def test_plan_launch_work(L):
     assert lib.slorr_plan_get_launches(None, None, None, None) == L.ERR_INVALID_ARGUMENT
 
 
+def test_plan_kernels(L):
+    """slorr_plan_get_kernels: the kernel that each entry of the schedule runs and
+    the products it forms; the products of a call sum to the schedule's."""
+    lib = L.lib()
+
+    def kernels(shapes, dtype, grad=None, iters=6, flags=0):
+        opts = L.Options()
+        lib.slorr_default_options(ctypes.byref(opts))
+        opts.iters, opts.flags = iters, flags
+        if grad is not None:
+            opts.grad_dtype = grad
+        st, h, _, _ = _plan(L, shapes, dtype, L.HOYER, opts)
+        assert st == L.OK
+        info = L.PlanInfo()
+        lib.slorr_plan_get_info(h, ctypes.byref(info))
+        nl = info.launches
+        names, fl, sched = (ctypes.c_char_p * nl)(), (ctypes.c_double * nl)(), (ctypes.c_double * nl)()
+        assert lib.slorr_plan_get_kernels(h, names, fl) == L.OK
+        assert lib.slorr_plan_get_kernels(h, None, None) == L.OK
+        assert lib.slorr_plan_get_launches(h, None, sched, None) == L.OK
+        got = [(n.decode(), f) for n, f in zip(names, fl)]
+        assert sum(fl) == pytest.approx(sum(sched), rel=1e-12)
+        assert all(f == 0 for n, f in got if not n.startswith(("k_tile", "k_upd256", "k_gemm", "k_short")))
+        lib.slorr_plan_destroy(h)
+        return got
+
+    # the ViT-B/16 set: every entry runs its own product
+    names = [n for n, _ in kernels(CONFIGS["vit_b16"].shapes, L.BF16)]
+    step = ["k_tile<gram, 256x256>", "k_tile<poly, 128x128>", "k_upd256<update>"]
+    assert names == ["k_sumsq", "k_norm_fin", "k_prep"] + step * 5 + step[:2] + ["k_upd256<last>", "k_finalize", "k_grad"]
+    # short matrices: one kernel per step
+    got = kernels([(128, 256)] * 4, L.F32)
+    assert [n for n, _ in got if n] == (["k_sumsq", "k_norm_fin", "k_prep", "k_short<first>"] + ["k_short<step>"] * 5
+                                        + ["k_short<last>", "k_finalize", "k_grad"])
+    gram, poly = 4 * 2.0 * 128 * 128 * 256, 4 * 2.0 * 128 ** 3
+    work = {"k_short<first>": gram, "k_short<step>": 2 * gram + poly, "k_short<last>": gram + poly}
+    assert all(f == work.get(n, 0.0) for n, f in got)
+    # few tiles: 64-tiles; a split Gram product and its reduce; one part per tile: none
+    assert "k_tile<gram, 64x64>" in [n for n, _ in kernels([(200, 300)] * 4, L.BF16)]
+    names = [n for n, _ in kernels([(384, 2048), (2048, 384), (256, 2304)], L.BF16)]
+    assert names.count("k_gram_reduce") == 6 and names.count("k_tile<gram, 128x128>") == 6
+    names = [n for n, _ in kernels([(384, 1536)] * 48, L.F32)]
+    assert names.count("k_gram_reduce") == 0 and names.count("") == 6 and names.count("k_tile<gram, 128x128>") == 6
+    # fp32 MFMA; no gradient launch
+    names = [n for n, _ in kernels([(128, 256)] * 4, L.F32, grad=L.BF16, flags=L.VALUES_ONLY)]
+    assert names.count("k_gemm<update, 128x128>") == 5 and names[-1] == "k_setsum"
+    assert lib.slorr_plan_get_kernels(None, None, None) == L.ERR_INVALID_ARGUMENT
+
+
 def test_empty_plans(L):
     st, h, ws, _ = _plan(L, [])
     assert st == L.OK and ws > 0

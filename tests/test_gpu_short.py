@@ -105,3 +105,24 @@ def test_short_options(dtype):
     assert bool(torch.isnan(v3[0])) and v3[3] == 0 and bool((G3[3] == 0).all())
     for i in (2, 4):
         assert v3[i] == v[i] and torch.equal(G3[i], G[i])
+
+
+@pytest.mark.parametrize("shapes", [[(128, 256)] * 4, [(384, 1536)] * 48])
+def test_profiled_entries_without_a_kernel(shapes):
+    """A profiled call times the kernels that run; entries that run nothing (the
+    products of a step that runs as one kernel, the reduce of a Gram product of
+    one part per tile) take 0 ms; the results are the call's."""
+    import torch
+    from paper_2607_08754_amd import Plan
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(37)
+    W = [torch.randn(s, generator=gen, device="cuda:0") * 0.02 for s in shapes]
+    G = [[torch.empty(s, device="cuda:0") for s in shapes] for _ in range(2)]
+    plan = Plan(shapes, dtype="f32")
+    v = plan(W, G[0]).clone()
+    v2, launches = plan.profiled(W, G[1])
+    assert torch.equal(v, v2) and all(torch.equal(a, b) for a, b in zip(*G))
+    kernels = plan.kernels()
+    assert len(launches) == len(kernels) and any(not k for k, _ in kernels)
+    for (op, ms), (k, _) in zip(launches, kernels):
+        assert (ms > 0.0) if k else (ms == 0.0), (op, k, ms)
