@@ -61,6 +61,20 @@ def run_oracle(arrs, dtype, kind="hoyer", iters=6, eps=0.0, g=1.0, table=None):
     return [fwd_bwd(widen(a, dtype), kind, table, eps, g) for a in arrs]
 
 
+def exact64(w, kind, table, eps=0.0):
+    """Value and gradient of one matrix by the iteration in float64 torch, on w's
+    device (large matrices; the oracle is the reference elsewhere)."""
+    y = w.double() if w.shape[0] <= w.shape[1] else w.double().t().contiguous()
+    fe = y.norm() + eps
+    x = y / fe
+    for a, b, c in table:
+        s = x @ x.t()
+        x = a * x + (b * s + c * (s @ s)) @ x
+    n = (y * x).sum()
+    v, g = (n, x) if kind == "nuclear" else ((n / fe) ** 2, 2 * n / fe ** 2 * x - 2 * n ** 2 / fe ** 4 * y)
+    return v, (g if w.shape[0] <= w.shape[1] else g.t())
+
+
 def first_term(ref, kind, g=1.0):
     """s1 P_ref, the first term of the gradient."""
     s1 = (2.0 * g * ref.n_hat / ref.f_eps ** 2) if (kind == "hoyer" and ref.f_eps > 0) else g

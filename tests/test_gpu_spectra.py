@@ -10,19 +10,11 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 from oracle.pe_schedule import default_table  # noqa: E402
+from parity_util import exact64  # noqa: E402
 
 pytestmark = pytest.mark.gpu
-
-
-def exact(w, table):
-    """Value and gradient of SLORR-Nuc."""
-    y = w if w.shape[0] <= w.shape[1] else w.t().contiguous()
-    x = y / y.norm()
-    for a, b, c in table:
-        sq = x @ x.t()
-        x = a * x + (b * sq + c * (sq @ sq)) @ x
-    return (y * x).sum(), (x if w.shape[0] <= w.shape[1] else x.t())
 
 
 SPECTRA = {
@@ -58,7 +50,7 @@ def test_dominated_spectra(dtype, spectrum):
     vals = Plan(shapes, dtype=dtype, kind="nuclear")(W, G).double()
     gtol, vtol = (2 * 18 ** 0.5 * 2.0 ** -11, 2.0 ** -11) if dtype == "bf16" else (8e-6, 1e-6)
     for i, w in enumerate(W):
-        v, g = exact(w.double(), default_table(6))
+        v, g = exact64(w, "nuclear", default_table(6))
         ge, ve = float((G[i].double() - g).norm() / g.norm()), float(abs(vals[i] - v) / v)
         print(f"{spectrum} {dtype} {shapes[i]}: gradient {ge:.2e} value {ve:.2e}", flush=True)
         assert ge <= gtol and ve <= vtol, i
