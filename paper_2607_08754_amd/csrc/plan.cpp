@@ -31,6 +31,9 @@ constexpr int kMinSplitSlabs16 = 32, kMinPartSlabs16 = 8;
 // sets of short matrices: slices per matrix, and Gram partials read per step
 constexpr int kMaxShortSlices = 8, kMaxShortReads = 1600;
 constexpr int64_t kMaxSmallTiles = 2 * kCus;   // 64-tiles of a launch
+// a 64-tile's start and end in values of k, and the time of an XCD's queue of
+// them over that of the longest tile, up to which they are used
+constexpr double kSmallTileFixed = 500.0, kMaxQueueSpan = 1.3;
 constexpr int kMinSplitSlabs32 = 8, kMinPartSlabs32 = 4;
 
 Tile make_tile(int32_t mat, int32_t tm, int32_t tn, int32_t slot) {
@@ -354,6 +357,13 @@ void build_plan(Plan &p) {
   // ResNet-18 in fp32 (61 tiles, 211 64-tiles; its Gram is split) 711 -> 656 us,
   // ViT-Ti (144, 480) 228 -> 213 -> 203. With up to four per CU: ViT-S (288, 1008)
   // 487 -> 501 -> 512.
+  // And only while the longest XCD's queue (a matrix's tiles stay together, so
+  // queues are uneven) ends soon after its longest tile: a second round costs more
+  // than the quarter saves. At a span of at most 1.2 times the longest tile (a
+  // tile takes about as long to start and end as 500 values of k) all of 324
+  // lists of random sets gained, 1 to 13 % of a call; between 1.4 and 1.6 one of
+  // 6 lost; from 1.6 all but one of 44 lost, up to 14 % (bf16: 51 matrices of 256
+  // x 768, 70 tiles in a queue, 271 -> 310 us; 9 of 640 x 1920 432 -> 536).
   p.gram64 = p.pp64 = TileRange{};
   if (scaled && !p.lean) {
     int64_t tiles = 0;
@@ -367,11 +377,31 @@ void build_plan(Plan &p) {
         for (int tn = tm; tn < nt; ++tn) j.tiles.push_back(make_tile(i, tm, tn, 0));
       jobs.push_back(std::move(j));
     }
+    auto emit64 = [&]() {                       // costs per matrix as set in jobs
+      const TileRange r = emit(jobs);
+      std::map<int, double> cost;
+      for (const Job &j : jobs) cost[j.mat] = j.cost + kSmallTileFixed;
+      double span = 0.0, longest = 0.0;
+      for (int x = 0; x < kXcds; ++x) {
+        std::vector<double> end(2 * kCus / kXcds, 0.0);      // of the blocks that the XCD holds
+        for (int e = x; e < r.count; e += kXcds) {
+          const Tile &t = p.tiles[size_t(r.first) + e];
+          if (t.mat < 0) continue;
+          auto first = std::min_element(end.begin(), end.end());
+          *first += cost[t.mat];
+          span = std::max(span, *first);
+          longest = std::max(longest, cost[t.mat]);
+        }
+      }
+      if (span <= kMaxQueueSpan * longest) return r;
+      p.tiles.resize(size_t(r.first));
+      return TileRange{};
+    };
     if (tiles <= kMaxSmallTiles) {
-      p.pp64 = emit(jobs);
+      p.pp64 = emit64();
       if (!p.gsplit.count && p.gram[kCfg128].count) {
         for (Job &j : jobs) j.cost = p.mats[j.mat].Qp;
-        p.gram64 = emit(jobs);
+        p.gram64 = emit64();
       }
     }
   }

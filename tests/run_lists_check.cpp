@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <iostream>
 #include <map>
+#include <set>
 #include <tuple>
 
 #include "plan.hpp"
@@ -94,11 +95,28 @@ int main() {
       fail("buffers", i, d.Pp, d.Qp);
   }
   // the symmetric outputs as 64-tiles: every upper tile once, padding at the
-  // end of each XCD's queue, at most two per CU
+  // end of each XCD's queue, at most two per CU; and a queue, two tiles on each
+  // of its 32 CUs at a time, ends by 1.3 times the longest tile (k and 500)
   for (const TileRange &r : {p.gram64, p.pp64}) {
     if (!r.count) continue;
     bool pad[kXcds] = {};
     std::map<std::tuple<int, int, int>, int> seen;
+    std::multiset<double> end[kXcds];
+    double longest = 0.0;
+    for (int x = 0; x < kXcds; ++x)
+      for (int i = 0; i < 64; ++i) end[x].insert(0.0);
+    for (int e = 0; e < r.count; ++e) {
+      const Tile &t = p.tiles[r.first + e];
+      if (t.mat < 0) continue;
+      const MatDesc &d = p.mats[t.mat];
+      const double c = 500.0 + (p.gram64.count && r.first == p.gram64.first ? d.Qp : d.Pp);
+      const double start = *end[e % kXcds].begin();
+      end[e % kXcds].erase(end[e % kXcds].begin());
+      end[e % kXcds].insert(start + c);
+      longest = std::max(longest, c);
+    }
+    for (int x = 0; x < kXcds; ++x)
+      if (*end[x].rbegin() > 1.3 * longest) fail("64-tile queue", x, int(*end[x].rbegin()), int(longest));
     for (int e = 0; e < r.count; ++e) {
       const Tile &t = p.tiles[r.first + e];
       if (t.mat < 0) {

@@ -129,16 +129,20 @@ def test_no_short_steps_on_fp32_mfma(checker):
 
 @pytest.mark.parametrize("dtype", [F32, BF16])
 def test_small_tiles(checker, dtype):
-    """Symmetric outputs on 64-tiles: at most 512 of them; a split Gram product
-    stays on its parts; not on fp32 MFMA."""
+    """Symmetric outputs on 64-tiles: at most 512 of them and no XCD's queue with a
+    second round (510 equal tiles of 51 matrices: 70 on the longest queue, which
+    holds 64); a split Gram product stays on its parts; not on fp32 MFMA."""
     def small(*args, **kw):
         return run(checker, *args, **kw)["small"]
 
     assert small([(200, 3000)] * 4, dtype) == "01"
-    assert small([(200, 250)] * 51, dtype)[1] == "1"                              # 510 64-tiles
+    assert small([(200, 250)] * 48, dtype)[1] == "1"                              # 480 64-tiles, queues of 60
     if dtype == BF16:
-        assert small([(200, 250)] * 51, dtype) == "11"
-    assert small([(200, 250)] * 52, dtype) == "00"                                # 520
+        assert small([(200, 250)] * 48, dtype) == "11"
+    assert small([(200, 250)] * 51, dtype) == "00"                                # 510, queues of up to 70
+    assert small([(640, 1920)] * 9, dtype)[1] == "0"                              # 495
+    for k in range(40, 53):                                                       # mixed sets around the limit
+        small([(200, 250 + 31 * i) for i in range(k)] + [(60, 700)] * (52 - k), dtype)
     assert small([(1, 130), (7, 13), (0, 5), (150, 200)], dtype)[1] == "1"
     assert small([(0, 5)], dtype) == "00"
 
