@@ -71,9 +71,11 @@ typedef enum { SLORR_HOYER = 0, SLORR_NUCLEAR = 1 } slorr_kind_t;
 
 /* Storage type of the weights. F32: the iteration holds every value as two
  * scaled fp16 numbers (23 to 24 significand bits together) and forms products
- * as three fp16 MFMAs with fp32 accumulation; with an explicit coefficient
- * table whose iterates may leave fp16's range, or bf16 gradients, it runs on
- * fp32 MFMA.
+ * as three fp16 MFMAs with fp32 accumulation. Such a value ends at 2^-36 of the
+ * iterate's size, so weights below about 2^-12 ||W||_F lose bits (a matrix with
+ * one row 1e5 times the rest: gradient off by 1e-5). With an explicit coefficient
+ * table whose iterates may leave that range at either end, or bf16 gradients, it
+ * runs on fp32 MFMA.
  * BF16: the iteration runs on fp16 MFMA operands with power-of-two scaling and
  * fp32 accumulation; norms and traces are accumulated in fp32 or wider. */
 typedef enum { SLORR_F32 = 0, SLORR_BF16 = 1 } slorr_dtype_t;
@@ -250,7 +252,7 @@ SLORR_API slorr_status_t slorr_decoupled_apply(slorr_plan_t plan, int32_t n, voi
 typedef enum {
   SLORR_OP_SUMSQ = 0,     /* partial sums of W^2 per chunk               */
   SLORR_OP_NORM = 1,      /* ||W||_F, ||W||_F + eps and the split of its  */
-                          /* inverse into 2^-e and kappa, per matrix      */
+                          /* inverse into powers of two and kappa         */
   SLORR_OP_PREP = 2,      /* X_0' = W / 2^e, short-side layout (the first */
                           /* step applies kappa = 2^e / (||W||_F + eps))  */
   SLORR_OP_GRAM = 3,      /* A = X X^T                                    */

@@ -12,18 +12,19 @@
 //   Last    X_T = B X, stored like an update, with the per-tile partial
 //           sums of X_0' * P over the canonical tile: P = X_T as stored
 //           (rounded to the iterate type, the values the gradient kernel
-//           reads) and X_0' = W / 2^e, which holds W's values exactly, so
-//           that 2^e times the sum is the trace sum(W * P) of Sec. 3
+//           reads) and X_0' = W / 2^e as stored, so that 2^e times the sum
+//           is the trace sum(W * P) of Sec. 3
 //
 // The first step runs on X_0' = W / 2^e and applies kappa = 2^e / (f + eps)
-// through its coefficients (per matrix: kappa a, kappa^3 b, kappa^5 c).
+// through its coefficients (per matrix: kappa a, kappa^3 b, kappa^5 c). Split sets
+// with eps > 0 hold every iterate in a power of two of its own (step_scale).
 //
 // Gram and Poly outputs are symmetric: only tiles with tm <= tn are computed
 // and off-diagonal tiles are also stored transposed (mirror).
 //
 // This file holds what the kernels share and k_gemm, the products on fp32
-// MFMA: fp32 sets outside the split form's range, and those whose gradients
-// are bf16. gemm_pipe.hpp has the products on 16-bit operands.
+// MFMA: fp32 sets whose table the split form does not fit, and those whose
+// gradients are bf16. gemm_pipe.hpp has the products on 16-bit operands.
 //
 // k_gemm's LDS layout: each operand row of a k-slab is 128 bytes (32 values
 // of consecutive k) split into eight 16-byte chunks stored at chunk index
@@ -67,7 +68,7 @@ struct GemmArgs {
   int fold;       // Update / Last: a_t I is folded into the operand (no a X term)
   int kap;        // coefficients per matrix (step_scale): kKappa in the first step, kRescale
   int grow0, grow1;  // Launch::grow0, grow1
-  float alpha, beta, gamma, inv_sx;
+  float alpha, beta, gamma;
   float *gpart;   // Gram parts (split K): fp32 partial tiles, BM x BN each, at tile.slot
   int quads;      // k_upd256 over a list of 128-tiles: a trace slot per 128 x 128 quadrant
                   // (slot of the first, Pp / 128 slots from one column of quadrants to the next)

@@ -16,7 +16,8 @@
 //             case, and all of them for three values in four. A product of
 //             two values is formed as lo hi + hi lo + hi hi, three fp16 MFMAs
 //             with fp32 accumulation; the dropped lo lo is below 2^-22 of the
-//             product.
+//             product. Both planes end at fp16's smallest number: values of X
+//             below 2^-12 (in its scale: below 1) lose bits, down to 2^-36.
 //
 // Why the split: fp32 MFMA runs at 1/16 of the fp16 rate, so three fp16
 // products cost 3/16 of one fp32 product, and per byte fetched or read from
@@ -25,10 +26,19 @@
 // values of k and term instead of once per 2 values, which outweighs the
 // operands' last bit. Measured against 64 bits, fp32 MFMA / split: gradients
 // 2.3e-6 / 1.5e-6 (200 x 260), 6.4e-6 / 4.1e-6 (512 x 2048), 5.0e-6 / 3.3e-6
-// (ViT-B/16 in fp32); values 1e-7 both.
+// (ViT-B/16 in fp32); values 1e-7 both. Also nearer on spectra that one value
+// dominates (300 times the rest: 3.2e-6 / 2.2e-6), of six decades (3.9e-5 /
+// 2.6e-5), rows and columns of six decades, heavy tails, sparse, square and long
+// matrices, T = 1 to 10. Further off where a row carries the norm and leaves the
+// others at the smallest number: 1e3 times the rest 9.0e-7 / 5.8e-7, 1e5 times
+// 2.5e-7 / 9.7e-6 (384 x 1536; the bar of fp32 sets is 1e-4).
 // One fp32 call, fp32 MFMA -> split: ViT-B/16 12.7 -> 4.7 ms, ViT-S (with the
 // decoupled update) 2.41 -> 1.14 ms, ResNet-18 1.58 -> 0.71 ms, 4 matrices of
 // 128 x 256 (T = 5) 250 -> 177 us.
+//
+// Call times "before -> after" in these files are pairs taken in turn on one
+// machine for the step that the comment describes; machines differ by some
+// percent and later steps shortened the same calls, so pairs do not add up.
 #pragma once
 
 struct Split {

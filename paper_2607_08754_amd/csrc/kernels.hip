@@ -378,10 +378,10 @@ __global__ __launch_bounds__(kThreads) void k_sumsq(const Tile *__restrict__ til
 
 // f, f + eps, kappa and the X_0 scale per matrix: one wave per matrix sums its
 // chunk partials (lane-strided, then a fixed butterfly). The iterate starts
-// from X_0' = W / 2^e, 2^e the smallest power of two >= f + eps: a scaling by
-// a power of two, so X_0' holds W's values exactly (bf16 values fit fp16's
-// significand); kappa = 2^e / (f + eps) in [1, 2) goes into the first step's
-// coefficients.
+// from X_0' = W / 2^e, 2^e the smallest power of two >= f + eps (by_norm: >= f,
+// see Scalars): a scaling by a power of two, so that only the iterate's type
+// rounds W (bf16 values fit fp16's significand); kappa = 2^e / (f + eps) in
+// [1, 2) goes into the first step's coefficients.
 __global__ __launch_bounds__(kThreads) void k_norm_fin(const MatDesc *__restrict__ mats,
                                                        Scalars *__restrict__ sc,
                                                        const double *__restrict__ part, int n,
@@ -933,7 +933,6 @@ void launch_one(const Plan &p, const Launch &l, hipStream_t s, const EvPair *ev,
         a.alpha = l.alpha;
         a.beta = l.beta;
         a.gamma = l.gamma;
-        a.inv_sx = 1.0f / sx;
         a.gpart = reinterpret_cast<float *>(ws + p.off_gpart);
         a.quads = l.run_cfg != l.cfg;
         a.ntiles = l.run_grid;

@@ -72,9 +72,11 @@ struct Chunk {                 // a contiguous run of a matrix's elements
   int32_t mat, begin, len, pad;
 };
 
-// Per matrix, written by the kernels. The iterate starts from the exact
-// X_0' = W / 2^e with 2^e the smallest power of two >= f + eps (a power-of-two
-// scaling, so X_0' holds W's values without rounding); the remaining factor
+// Per matrix, written by the kernels. The iterate starts from X_0' = W / 2^e with
+// 2^e the smallest power of two >= f + eps. The scaling rounds nothing; what X_0'
+// then holds of W is up to the iterate's type: bf16 weights in fp16 and fp32
+// weights in fp32 whole (fp16: down to 2^-36 of 2^e), the split form 23 or 24 bits
+// of them, down to the same smallest value. The remaining factor
 // kappa = 2^e / (f + eps), in [1, 2), is applied by the first step's
 // coefficients: p_1(kappa x) = (a kappa) x + (b kappa^3) x^3 + (c kappa^5) x^5.
 //
@@ -87,12 +89,12 @@ struct Chunk {                 // a contiguous run of a matrix's elements
 // distance to the next power of two, and for the other iterates.
 struct Scalars {
   double sumsq, f, feps, nhat, value;
-  double s1, s2;               // gradient = g (s1 P - s2 W)
+  double s1, s2;               // gradient = g (s1 P - s2 W), P as it is held
   double kappa;                // 2^e / (f + eps); 0 when f + eps == 0
   double two_e;                // 2^(e - h): W = two_e X_0', so the trace sum(W * P)
                                // is two_e sum(X_0' * P) over the canonical buffers
-  float pscale;                // the iterate's scale over two_e, which X_0' multiplies W
-  int16_t pexp;                // by, is pscale 2^pexp (pexp > 0: beyond fp32's 2^127)
+  float pscale;                // W times pscale 2^pexp is X_0' in the iterate's scale
+  int16_t pexp;                // (pexp > 0 where the product exceeds fp32's 2^127)
   int16_t shift;               // split iterate: h, see above
 };
 

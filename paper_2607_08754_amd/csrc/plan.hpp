@@ -19,7 +19,7 @@ void greedy_schedule(double ell, int degree, int iters, double *out);
 enum class Op : int {
   SumSq = SLORR_OP_SUMSQ,        // partial sums of squares per canonical tile
   NormFin = SLORR_OP_NORM,       // f, f + eps, kappa and the X_0 scale per matrix
-  Prep = SLORR_OP_PREP,          // X_0 = W / 2^e, canonical, padded
+  Prep = SLORR_OP_PREP,          // X_0' = W / 2^e, canonical, padded
   Gram = SLORR_OP_GRAM,          // A = X X^T
   Poly = SLORR_OP_POLY,          // B = a I + b A + c A A
   Update = SLORR_OP_UPDATE,      // X' = B X               (or a X + b A X when c = 0)

@@ -1,6 +1,7 @@
 """fp32 sets iterated in split form (two fp16 numbers per value) against the
-oracle at the edges of its tiles, the 256-tile kernels against 64-bit torch,
-and a table outside the split form's range, which keeps fp32 MFMA."""
+oracle at the edges of its tiles, the 256-tile kernels against 64-bit torch;
+the ends of the form's range (tiny norms, eps far above the norm, a row that
+carries the norm); and tables outside it, which keep fp32 MFMA."""
 import os
 import sys
 
@@ -122,9 +123,9 @@ def test_tiny_norms(kind):
 @pytest.mark.parametrize("kind", ["hoyer", "nuclear"])
 def test_eps_above_the_norm(shapes, kind):
     """eps up to 1e8 times the norm: X_0 is small against 1, and the iterate is
-    held in powers of two that keep its significand. 8e-6: the bound of the other
-    fp32 sets on this form (split: 2e-5 for T = 6 at eps = 0, less here, where B
-    is a I and little else)."""
+    held in powers of two that keep its significand. 8e-6 and 1e-6 as at eps = 0,
+    where these matrices are off by up to 5.4e-6 (Hoyer's difference of two terms);
+    less above, where B is a I and little else."""
     import torch
     from paper_2607_08754_amd import Plan
     gen = torch.Generator(device="cuda:0")

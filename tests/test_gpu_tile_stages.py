@@ -1,5 +1,5 @@
-"""bf16 sets on 64- and 128-tiles: symmetric outputs of at most 512 64-tiles run
-on these, other launches on 128-tiles with four LDS stages for at most 256 of
+"""bf16 sets on 64- and 128-tiles: symmetric outputs whose 64-tiles fit one round
+run on these, other launches on 128-tiles with four LDS stages for at most 256 of
 them, else two. The products are formed in the same order, so
 a matrix on its own and among many equal ones gets the same value and gradient
 bit for bit; and both agree with the oracle."""
