@@ -5,7 +5,9 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <map>
+#include <queue>
 #include <stdexcept>
 #include <utility>
 
@@ -200,6 +202,12 @@ void build_plan(Plan &p) {
     if (!p.mats[i].empty) order.push_back(i);
   auto tsize = [](int cfg) { return cfg == kCfg128 ? kTile : kBigTile; };
   p.tiles.clear();
+  size_t entries = 64;                    // about what the lists below hold together
+  for (int i : order) {
+    const size_t nm = size_t(p.mats[i].Pp / kTile), nn = size_t(p.mats[i].Qp / kTile);
+    entries += 6 * nm * nn + 4 * nm * (nm + 1);
+  }
+  p.tiles.reserve(entries);
 
   // XCD-aware order. Workgroup b of a launch runs on XCD b % kXcds, so list
   // entry b is taken from XCD (b % kXcds)'s own sequence: every matrix's tiles
@@ -379,18 +387,21 @@ void build_plan(Plan &p) {
     }
     auto emit64 = [&]() {                       // costs per matrix as set in jobs
       const TileRange r = emit(jobs);
-      std::map<int, double> cost;
-      for (const Job &j : jobs) cost[j.mat] = j.cost + kSmallTileFixed;
+      std::vector<double> cost(size_t(p.n), 0.0);
+      for (const Job &j : jobs) cost[size_t(j.mat)] = j.cost + kSmallTileFixed;
       double span = 0.0, longest = 0.0;
       for (int x = 0; x < kXcds; ++x) {
-        std::vector<double> end(2 * kCus / kXcds, 0.0);      // of the blocks that the XCD holds
+        // when each of the blocks that the XCD holds ends, the first on top
+        std::priority_queue<double, std::vector<double>, std::greater<double>> end(
+            std::greater<double>(), std::vector<double>(2 * kCus / kXcds, 0.0));
         for (int e = x; e < r.count; e += kXcds) {
           const Tile &t = p.tiles[size_t(r.first) + e];
           if (t.mat < 0) continue;
-          auto first = std::min_element(end.begin(), end.end());
-          *first += cost[t.mat];
-          span = std::max(span, *first);
-          longest = std::max(longest, cost[t.mat]);
+          const double at = end.top() + cost[size_t(t.mat)];
+          end.pop();
+          end.push(at);
+          span = std::max(span, at);
+          longest = std::max(longest, cost[size_t(t.mat)]);
         }
       }
       if (span <= kMaxQueueSpan * longest) return r;
