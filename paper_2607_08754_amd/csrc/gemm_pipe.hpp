@@ -31,7 +31,9 @@
 // 2.6e-5), rows and columns of six decades, heavy tails, sparse, square and long
 // matrices, T = 1 to 10. Further off where a row carries the norm and leaves the
 // others at the smallest number: 1e3 times the rest 9.0e-7 / 5.8e-7, 1e5 times
-// 2.5e-7 / 9.7e-6 (384 x 1536; the bar of fp32 sets is 1e-4).
+// 2.5e-7 / 9.7e-6 (384 x 1536; the bar of fp32 sets is 1e-4); and by the operands'
+// last bit on matrices of a few rows, whose sums are short (up to 16 rows, T = 6
+// and 8: 1.1 to 3.0e-7 / 2.2 to 3.9e-7).
 // One fp32 call, fp32 MFMA -> split: ViT-B/16 12.7 -> 4.7 ms, ViT-S (with the
 // decoupled update) 2.41 -> 1.14 ms, ResNet-18 1.58 -> 0.71 ms, 4 matrices of
 // 128 x 256 (T = 5) 250 -> 177 us.
